@@ -78,6 +78,18 @@ def test_edge_cases():
     check(rng.integers(-1, 2, size=(2049, 56)).astype(np.int32), 2048)  # ragged last block
 
 
+@pytest.mark.parametrize("nv,C,B,scale", [
+    (1000, 3, 48, 3.0),     # 21 block rows per wave, the last block row 40 values: steps of both lengths
+    (1025, 32, 64, 3.0),    # two block rows per wave, a last block of one value
+    (1040, 33, 16, 3.0),    # one block row per wave, whole steps only
+    (70, 1, 17, 3.0),       # blocks one value longer than a step
+    (4100, 56, 512, 3e4),   # codes longer than one word's window, refills outrun
+    (2000, 5, 2000, 0.05),  # runs across many steps, one block per channel
+])
+def test_block_shapes_and_code_lengths(nv, C, B, scale):
+    check(laplace_matrix(nv, C, seed=nv + B, scale=scale), B)
+
+
 @pytest.mark.parametrize("B", [256, 4096])
 def test_codec_coefficients(B):
     # the quantized coefficients of a frame coded by the GPU codec
