@@ -146,14 +146,36 @@ __device__ inline void wsync()
     __builtin_amdgcn_wave_barrier();
 }
 
+// The rotation (c, s) that zeroes A[p][q] (the smaller angle of the symmetric Schur decomposition of
+// Golub and Van Loan: t = tan = 2 apq sgn(d) / (|d| + sqrt(d^2 + 4 apq^2)), d = aqq - app), apq != 0. The
+// angle is taken in FP32 (of d and 2 apq scaled to their larger exponent), c = 1 / sqrt(1 + t^2) then to
+// FP64 round-off by two Newton steps, s = t c: the rotation is orthogonal to FP64, and an angle off
+// by 1e-7 of itself leaves 1e-7 of A[p][q] for the next sweep. It has no FP64 division or square root.
+__device__ inline void jacobi_rotation(double app, double aqq, double apq, double &c, double &s)
+{
+    const double d = aqq - app, e = 2.0 * apq;
+    const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(e)));
+    const float x = (float)__builtin_amdgcn_ldexp(d, -ex), y = (float)__builtin_amdgcn_ldexp(e, -ex);
+    const float t = (x < 0.f ? -y : y) * __builtin_amdgcn_rcpf(fabsf(x) + __builtin_amdgcn_sqrtf(x * x + y * y));
+    const double T = (double)t, h = 1.0 + T * T;
+    double r = (double)__builtin_amdgcn_rsqf((float)h);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) r = r * (1.5 - 0.5 * h * r * r);
+    c = r;
+    s = T * r;
+}
+
 // Cyclic Jacobi on the symmetric 16x16 matrix A (index 15 a zero padding row and column), one
 // wave: each step applies 8 rotations on disjoint index pairs (round-robin order, 15 steps per
-// sweep), rows first, then columns, then the eigenvector matrix V (starting as I). A rotation
-// zeroes A[p][q] (the symmetric Schur decomposition of Golub and Van Loan). Sweeps stop when
+// sweep). Lane 8 i + j owns the 2 x 2 block A[pair i][pair j] and the rows 2i, 2i + 1 of V (starting as
+// I) in the columns of pair j; it reads the three entries that give each of the two pairs'
+// rotations itself, so a step is one LDS round trip: read, both rotations, both sides of its
+// block, write. A chain of about 100 such steps bounds the launch (3 waves in all). Sweeps stop when
 // the off-diagonal energy is below 1e-26 of the diagonal's, or after JACOBI_SWEEPS_MAX.
-__device__ inline void jacobi16(double (*A)[COL_F], double (*V)[COL_F], double *s_c, double *s_s, uint32_t *s_pq)
+constexpr int COL_P = COL_F + 1;  // LDS row pitch
+__device__ inline void jacobi16(double (*A)[COL_P], double (*V)[COL_P])
 {
-    const uint32_t lane = lane_id();
+    const uint32_t lane = lane_id(), bi = lane >> 3, bj = lane & 7u;
     for (uint32_t i = lane; i < COL_F * COL_F; i += WAVE) V[i / COL_F][i % COL_F] = (i / COL_F == i % COL_F) ? 1.0 : 0.0;
     wsync();
     for (int sweep = 0; sweep < JACOBI_SWEEPS_MAX; ++sweep) {
@@ -168,67 +190,47 @@ __device__ inline void jacobi16(double (*A)[COL_F], double (*V)[COL_F], double *
             dia += __shfl_xor(dia, o, WAVE);
         }
         if (off <= 1e-26 * dia || off == 0.0) break;
-        for (int step = 0; step < COL_F - 1; ++step) {
-            if (lane < 8) {
-                // players: 0 fixed, the others rotated by the step; pair i = (players[i], players[15 - i])
-                auto player = [&](uint32_t j) -> uint32_t { return j == 0 ? 0u : 1u + (j - 1u + (uint32_t)step) % (COL_F - 1); };
-                uint32_t p = player(lane), q = player(COL_F - 1 - lane);
-                if (p > q) {
-                    const uint32_t t = p;
-                    p = q;
-                    q = t;
-                }
-                double c = 1.0, s = 0.0;
-                const double apq = A[p][q];
-                if (q < (uint32_t)COL_AC && apq != 0.0) {
-                    const double tau = (A[q][q] - A[p][p]) / (2.0 * apq);
-                    const double t = tau >= 0.0 ? 1.0 / (tau + sqrt(1.0 + tau * tau)) : -1.0 / (-tau + sqrt(1.0 + tau * tau));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
-                }
-                s_c[lane] = c;
-                s_s[lane] = s;
-                s_pq[lane] = p | (q << 8);
+        for (uint32_t step = 0; step < COL_F - 1; ++step) {
+            // players: 0 fixed, the others rotated by the step; pair i = (players[i], players[15 - i])
+            auto player = [&](uint32_t j) -> uint32_t {
+                const uint32_t k = j + step;  // 1 + (j - 1 + step) % 15
+                return j == 0 ? 0u : (k >= (uint32_t)COL_F ? k - (COL_F - 1) : k);
+            };
+            const uint32_t i0 = player(bi), i1 = player(COL_F - 1 - bi), j0 = player(bj), j1 = player(COL_F - 1 - bj);
+            const uint32_t pi = min(i0, i1), qi = max(i0, i1), pj = min(j0, j1), qj = max(j0, j1);
+            const double ipp = A[pi][pi], iqq = A[qi][qi], ipq = A[pi][qi];
+            const double jpp = A[pj][pj], jqq = A[qj][qj], jpq = A[pj][qj];
+            const double a00 = A[pi][pj], a01 = A[pi][qj], a10 = A[qi][pj], a11 = A[qi][qj];
+            double v[2][2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                v[u][0] = V[2 * bi + u][pj];
+                v[u][1] = V[2 * bi + u][qj];
             }
-            wsync();
-            // rows: (J^T A)[p][:] = c A[p][:] - s A[q][:], (J^T A)[q][:] = s A[p][:] + c A[q][:]
-            {
-                const uint32_t pr = lane / 8, j0 = (lane % 8) * 2;
-                const uint32_t p = s_pq[pr] & 255u, q = s_pq[pr] >> 8;
-                const double c = s_c[pr], s = s_s[pr];
-                double ap[2], aq[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    ap[u] = A[p][j0 + u];
-                    aq[u] = A[q][j0 + u];
-                }
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    A[p][j0 + u] = c * ap[u] - s * aq[u];
-                    A[q][j0 + u] = s * ap[u] + c * aq[u];
-                }
+            double ci, si, cj, sj;
+            jacobi_rotation(ipp, iqq, ipq, ci, si);
+            jacobi_rotation(jpp, jqq, jpq, cj, sj);
+            // (the padding's pair, and a zero entry, are left alone)
+            if (ipq == 0.0 || qi == (uint32_t)COL_AC) {
+                ci = 1.0;
+                si = 0.0;
             }
-            wsync();
-            // columns of A and of V: (X J)[:][p] = c X[:][p] - s X[:][q], (X J)[:][q] = s X[:][p] + c X[:][q]
-            {
-                const uint32_t pr = lane / 8, i0 = (lane % 8) * 2;
-                const uint32_t p = s_pq[pr] & 255u, q = s_pq[pr] >> 8;
-                const double c = s_c[pr], s = s_s[pr];
-                double xp[4], xq[4];
+            if (jpq == 0.0 || qj == (uint32_t)COL_AC) {
+                cj = 1.0;
+                sj = 0.0;
+            }
+            wsync();  // (every lane has read before any writes)
+            // rows: [p] = c [p] - s [q], [q] = s [p] + c [q]; then the columns likewise
+            const double r00 = ci * a00 - si * a10, r01 = ci * a01 - si * a11;
+            const double r10 = si * a00 + ci * a10, r11 = si * a01 + ci * a11;
+            A[pi][pj] = cj * r00 - sj * r01;
+            A[pi][qj] = sj * r00 + cj * r01;
+            A[qi][pj] = cj * r10 - sj * r11;
+            A[qi][qj] = sj * r10 + cj * r11;
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    xp[u] = A[i0 + u][p];
-                    xq[u] = A[i0 + u][q];
-                    xp[2 + u] = V[i0 + u][p];
-                    xq[2 + u] = V[i0 + u][q];
-                }
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    A[i0 + u][p] = c * xp[u] - s * xq[u];
-                    A[i0 + u][q] = s * xp[u] + c * xq[u];
-                    V[i0 + u][p] = c * xp[2 + u] - s * xq[2 + u];
-                    V[i0 + u][q] = s * xp[2 + u] + c * xq[2 + u];
-                }
+            for (int u = 0; u < 2; ++u) {
+                V[2 * bi + u][pj] = cj * v[u][0] - sj * v[u][1];
+                V[2 * bi + u][qj] = sj * v[u][0] + cj * v[u][1];
             }
             wsync();
         }
@@ -241,9 +243,7 @@ __device__ inline void jacobi16(double (*A)[COL_F], double (*V)[COL_F], double *
 __global__ __launch_bounds__(COL_BASIS_THREADS) void k_color_basis(ColorArgs a)
 {
     __shared__ double s_g[COL_ENT];
-    __shared__ double s_A[3][COL_F][COL_F], s_V[3][COL_F][COL_F];
-    __shared__ double s_c[3][8], s_s[3][8];
-    __shared__ uint32_t s_pq[3][8];
+    __shared__ double s_A[3][COL_F][COL_P], s_V[3][COL_F][COL_P];
     const uint32_t t = threadIdx.x;
     const GAS double *fold = gp(a.part) + (size_t)a.blocks * COL_ENT;  // k_color_fold's groups
     if (t < (uint32_t)COL_ENT) {
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(COL_BASIS_THREADS) void k_color_basis(ColorArgs a)
         s_A[c][i][j] = v;
     }
     wsync();
-    jacobi16(s_A[c], s_V[c], s_c[c], s_s[c], s_pq[c]);
+    jacobi16(s_A[c], s_V[c]);
     // lane j < 15: eigenpair j's rank (decreasing eigenvalue, index order on ties) and sign
     if (lane < (uint32_t)COL_AC) {
         const uint32_t j = lane;
