@@ -305,6 +305,32 @@ gsc_status gsc_ste_backward(int64_t n, int32_t J, int32_t C, const float *d_grad
                             size_t ws_bytes, int32_t *d_info, void *stream);
 
 /* ------------------------------------------------------------------------------------------
+ * The rate-distortion loss of the differentiable layer, for float rows [rows][C]:
+ *   dist = sum (ahat - aref)^2 / (count C), rate = lambda sum log2(1 + |yhat| / step[c]),
+ *   loss = dist + rate; count is *d_nv (one device int64) when d_nv is given, else rows.
+ * gsc_rd_loss_workspace_size: device scratch bytes of the forward.
+ * gsc_rd_loss_forward: the scalars (device floats) *d_loss, *d_dist, *d_rate, *d_count; d_diff
+ *   (optional) = ahat - aref, which the backward takes with *d_count. Sums are FP64 in a fixed order.
+ * gsc_rd_loss_backward: d_grad_yhat and d_grad_ahat [rows][C] from the scalars dL/dloss, dL/ddist
+ *   and dL/drate (device floats, each may be NULL: zero); sgn(0) = 0 in the rate term.
+ * gsc_ste_pad: after gsc_ste_forward with the same d_info on outputs of n rows: rows Nv..n-1 of
+ *   yhat, ahat and aref cleared (every row after a device-detected error) and *d_nv = Nv (0 then).
+ * ---------------------------------------------------------------------------------------- */
+gsc_status gsc_rd_loss_workspace_size(size_t *bytes);
+gsc_status gsc_rd_loss_forward(const float *d_yhat, const float *d_ahat, const float *d_aref,
+                               const float *d_step, int64_t rows, int32_t C, double lambda,
+                               const int64_t *d_nv, float *d_diff, float *d_loss, float *d_dist,
+                               float *d_rate, float *d_count, void *d_ws, size_t ws_bytes,
+                               void *stream);
+gsc_status gsc_rd_loss_backward(const float *d_yhat, const float *d_diff, const float *d_step,
+                                int64_t rows, int32_t C, double lambda, const float *d_count,
+                                const float *d_grad_loss, const float *d_grad_dist,
+                                const float *d_grad_rate, float *d_grad_yhat, float *d_grad_ahat,
+                                void *stream);
+gsc_status gsc_ste_pad(const int32_t *d_info, int64_t n, int32_t C, float *d_yhat, float *d_ahat,
+                       float *d_aref, int64_t *d_nv, void *stream);
+
+/* ------------------------------------------------------------------------------------------
  * Block-parallel entropy coding of quantized coefficients (Sec. 3.4 "Quantization and Entropy
  * Coding": run-length / adaptive Golomb-Rice coding of independent blocks of consecutive
  * coefficients of one channel, coded in parallel).

@@ -867,6 +867,101 @@ gsc_status gsc_raht_adjoint(const uint64_t *d_codes, int64_t nv, int32_t J, int3
     return raht_f32(d_codes, nv, J, C, d_in, d_out, d_ws, ws_bytes, d_info, stream, true);
 }
 
+// ------------------------------------------------------------- loss of the differentiable layer
+gsc_status gsc_rd_loss_workspace_size(size_t *bytes)
+{
+    if (!bytes) return GSC_ERR_INVALID_ARG;
+    *bytes = rd_loss_workspace_bytes();
+    return GSC_OK;
+}
+
+static gsc_status rd_shape(int64_t rows, int32_t C)
+{
+    if (C < 1 || C > GSC_MAX_CHANNELS) return GSC_ERR_DEPTH;
+    return rows < 1 || rows > N_LIMIT ? GSC_ERR_INVALID_ARG : GSC_OK;
+}
+
+gsc_status gsc_rd_loss_forward(const float *d_yhat, const float *d_ahat, const float *d_aref,
+                               const float *d_step, int64_t rows, int32_t C, double lambda,
+                               const int64_t *d_nv, float *d_diff, float *d_loss, float *d_dist,
+                               float *d_rate, float *d_count, void *d_ws, size_t ws_bytes,
+                               void *stream)
+{
+    gsc_status st = rd_shape(rows, C);
+    if (st != GSC_OK) return st;
+    if (!d_yhat || !d_ahat || !d_aref || !d_step || !d_loss || !d_dist || !d_rate || !d_count || !d_ws)
+        return GSC_ERR_INVALID_ARG;
+    const size_t need = rd_loss_workspace_bytes();
+    if (ws_bytes < need) return GSC_ERR_WORKSPACE;
+    {
+        const uint64_t m = (uint64_t)rows * C * 4;
+        Spans sp;
+        sp.rd(d_yhat, m);
+        sp.rd(d_ahat, m);
+        sp.rd(d_aref, m);
+        sp.rd(d_step, (uint64_t)C * 4);
+        sp.rd(d_nv, 8);
+        sp.wr(d_diff, m);
+        for (float *p : {d_loss, d_dist, d_rate, d_count}) sp.wr(p, 4);
+        sp.wr(d_ws, need);
+        if (!sp.disjoint()) return GSC_ERR_INVALID_ARG;
+    }
+    float *const out[4] = {d_loss, d_dist, d_rate, d_count};
+    GSC_LAUNCH(launch_rd_loss_forward(d_yhat, d_ahat, d_aref, d_step, (uint64_t)rows, (uint32_t)C, lambda, d_nv, d_diff, out,
+                                      static_cast<double *>(d_ws), static_cast<hipStream_t>(stream)));
+    return GSC_OK;
+}
+
+gsc_status gsc_rd_loss_backward(const float *d_yhat, const float *d_diff, const float *d_step,
+                                int64_t rows, int32_t C, double lambda, const float *d_count,
+                                const float *d_grad_loss, const float *d_grad_dist,
+                                const float *d_grad_rate, float *d_grad_yhat, float *d_grad_ahat,
+                                void *stream)
+{
+    gsc_status st = rd_shape(rows, C);
+    if (st != GSC_OK) return st;
+    if (!d_yhat || !d_diff || !d_step || !d_count || !d_grad_yhat || !d_grad_ahat) return GSC_ERR_INVALID_ARG;
+    {
+        const uint64_t m = (uint64_t)rows * C * 4;
+        Spans sp;
+        sp.rd(d_yhat, m);
+        sp.rd(d_diff, m);
+        sp.rd(d_step, (uint64_t)C * 4);
+        sp.rd(d_count, 4);
+        sp.rd(d_grad_loss, 4);
+        sp.rd(d_grad_dist, 4);
+        sp.rd(d_grad_rate, 4);
+        sp.wr(d_grad_yhat, m);
+        sp.wr(d_grad_ahat, m);
+        if (!sp.disjoint()) return GSC_ERR_INVALID_ARG;
+    }
+    GSC_LAUNCH(launch_rd_loss_backward(d_yhat, d_diff, d_step, (uint64_t)rows, (uint32_t)C, lambda, d_count, d_grad_loss,
+                                       d_grad_dist, d_grad_rate, d_grad_yhat, d_grad_ahat,
+                                       static_cast<hipStream_t>(stream)));
+    return GSC_OK;
+}
+
+gsc_status gsc_ste_pad(const int32_t *d_info, int64_t n, int32_t C, float *d_yhat, float *d_ahat,
+                       float *d_aref, int64_t *d_nv, void *stream)
+{
+    if (C < 1 || C > GSC_MAX_CHANNELS) return GSC_ERR_DEPTH;
+    if (n < 0 || n > N_LIMIT) return GSC_ERR_INVALID_ARG;
+    if (!d_info || !d_nv || (n > 0 && (!d_yhat || !d_ahat || !d_aref))) return GSC_ERR_INVALID_ARG;
+    {
+        const uint64_t m = (uint64_t)n * C * 4;
+        Spans sp;
+        sp.rd(d_info, GSC_INFO_WORDS * 4);
+        sp.wr(d_yhat, m);
+        sp.wr(d_ahat, m);
+        sp.wr(d_aref, m);
+        sp.wr(d_nv, 8);
+        if (!sp.disjoint()) return GSC_ERR_INVALID_ARG;
+    }
+    GSC_LAUNCH(launch_ste_pad(d_info, (uint64_t)n, (uint32_t)C, d_yhat, d_ahat, d_aref, d_nv,
+                              static_cast<hipStream_t>(stream)));
+    return GSC_OK;
+}
+
 }  // extern "C"
 
 // ---------------------------------------------------------------- block entropy coder

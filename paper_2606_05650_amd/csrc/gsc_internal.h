@@ -397,6 +397,16 @@ hipError_t launch_raht_inv(const TileMap &m, bool finish, const RahtCfg &cfg, hi
 hipError_t launch_raht_inv_up(const TileMap &m, int kmax, uint32_t items_max, bool prelude, const RahtCfg &cfg,
                               hipStream_t s);
 hipError_t launch_finish(const TileMap &m, hipStream_t s);
+// the differentiable layer's loss and padding (k_loss.hip)
+size_t rd_loss_workspace_bytes();
+hipError_t launch_rd_loss_forward(const float *yhat, const float *ahat, const float *aref, const float *step, uint64_t rows,
+                                  uint32_t C, double lam, const int64_t *nv, float *diff, float *const out[4], double *ws,
+                                  hipStream_t s);
+hipError_t launch_rd_loss_backward(const float *yhat, const float *diff, const float *step, uint64_t rows, uint32_t C,
+                                   double lam, const float *count, const float *g_loss, const float *g_dist,
+                                   const float *g_rate, float *g_yhat, float *g_ahat, hipStream_t s);
+hipError_t launch_ste_pad(const int32_t *info, uint64_t rows, uint32_t C, float *m0, float *m1, float *m2, int64_t *nv,
+                          hipStream_t s);
 // Block entropy coder (k_rlgr.hip); ws: 8 (ceil(nv / B) + 1) bytes.
 // occupancy-byte rANS coder (k_rans.hip)
 uint64_t rans_chunks(uint64_t n, uint32_t K);

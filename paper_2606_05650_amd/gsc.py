@@ -108,6 +108,16 @@ def lib():
                                       vp, vp, vp, vp]
         L.gsc_ste_backward.restype = i32
         L.gsc_ste_backward.argtypes = [i64, i32, i32, vp, vp, vp, vp, sz, vp, vp]
+        dbl = ctypes.c_double
+        L.gsc_rd_loss_workspace_size.restype = i32
+        L.gsc_rd_loss_workspace_size.argtypes = [ctypes.POINTER(sz)]
+        L.gsc_rd_loss_forward.restype = i32
+        L.gsc_rd_loss_forward.argtypes = [vp, vp, vp, vp, i64, i32, dbl, vp, vp, vp, vp, vp, vp, vp, sz,
+                                           vp]
+        L.gsc_rd_loss_backward.restype = i32
+        L.gsc_rd_loss_backward.argtypes = [vp, vp, vp, i64, i32, dbl, vp, vp, vp, vp, vp, vp, vp]
+        L.gsc_ste_pad.restype = i32
+        L.gsc_ste_pad.argtypes = [vp, i64, i32, vp, vp, vp, vp, vp]
         L.gsc_raht_forward.restype = i32
         L.gsc_raht_forward.argtypes = [vp, i64, i32, i32, vp, vp, vp, sz, vp, vp]
         L.gsc_raht_adjoint.restype = i32
@@ -628,6 +638,59 @@ def ste_backward(fwd, grad_yhat, grad_ahat, *, out=None, info=None, stream=None)
                                 _ptr(e.ws.buf), e.ws.bytes, _ptr(info), _stream(stream))
     _check(rc, "gsc_ste_backward")
     return out, info
+
+
+def ste_pad(fwd, *, nv=None, stream=None):
+    """Clears rows Nv..n-1 of a ste_forward's outputs (every row after a device-detected error)
+    and returns Nv (0 then) as a one-element int64 device tensor, without waiting for the device."""
+    torch = _torch()
+    e = fwd.encoded
+    if nv is None:
+        nv = torch.empty(1, dtype=torch.int64, device=e.info.device)
+    _check_tensor(nv, "nv", torch.int64, numel=1)
+    for name, t in (("yhat", fwd.yhat), ("ahat", fwd.ahat), ("aref", fwd.aref)):
+        _check_tensor(t, name, torch.float32, fwd.n, e.C)
+    _check(lib().gsc_ste_pad(_ptr(e.info), fwd.n, e.C, _ptr(fwd.yhat), _ptr(fwd.ahat), _ptr(fwd.aref), _ptr(nv),
+                             _stream(stream)), "gsc_ste_pad")
+    return nv
+
+
+def rd_loss_forward(yhat, ahat, aref, steps, lam, *, nv=None, want_diff=True, stream=None):
+    """(loss, distortion, rate, count, diff): float32 scalars on the device and ahat - aref (or None)."""
+    torch = _torch()
+    rows, C = int(yhat.shape[0]), int(yhat.shape[1])
+    for name, t in (("yhat", yhat), ("ahat", ahat), ("aref", aref)):
+        _check_tensor(t, name, torch.float32, rows, C)
+    _check_tensor(steps, "steps", torch.float32, numel=C)
+    _check_tensor(nv, "nv", torch.int64, numel=1)
+    dev = yhat.device
+    need = ctypes.c_size_t()
+    _check(lib().gsc_rd_loss_workspace_size(ctypes.byref(need)), "rd_loss_workspace_size")
+    ws = _dev_u8(need.value, dev)
+    out = [torch.empty((), dtype=torch.float32, device=dev) for _ in range(4)]
+    diff = torch.empty_like(ahat) if want_diff else None
+    _check(lib().gsc_rd_loss_forward(_ptr(yhat), _ptr(ahat), _ptr(aref), _ptr(steps), rows, C, float(lam), _ptr(nv),
+                                     _ptr(diff), *(_ptr(t) for t in out), _ptr(ws), ws.numel(), _stream(stream)),
+           "gsc_rd_loss_forward")
+    return (*out, diff)
+
+
+def rd_loss_backward(yhat, diff, steps, lam, count, g_loss, g_dist, g_rate, *, stream=None):
+    """(dL/dyhat, dL/dahat) from rd_loss_forward's diff and count and the scalar gradients of loss,
+    distortion and rate (each may be None)."""
+    torch = _torch()
+    rows, C = int(yhat.shape[0]), int(yhat.shape[1])
+    for name, t in (("yhat", yhat), ("diff", diff)):
+        _check_tensor(t, name, torch.float32, rows, C)
+    _check_tensor(steps, "steps", torch.float32, numel=C)
+    _check_tensor(count, "count", torch.float32, numel=1)
+    for name, t in (("g_loss", g_loss), ("g_dist", g_dist), ("g_rate", g_rate)):
+        _check_tensor(t, name, torch.float32, numel=1)
+    gy, ga = torch.empty_like(yhat), torch.empty_like(diff)
+    _check(lib().gsc_rd_loss_backward(_ptr(yhat), _ptr(diff), _ptr(steps), rows, C, float(lam), _ptr(count), _ptr(g_loss),
+                                      _ptr(g_dist), _ptr(g_rate), _ptr(gy), _ptr(ga), _stream(stream)),
+           "gsc_rd_loss_backward")
+    return gy, ga
 
 
 # ----------------------------------------------------------------- block entropy coder

@@ -9,16 +9,18 @@ by the voxel's member count. Nv is only known once the encoder has run, so this 
 the device to cut the outputs to Nv rows.
 
 SteCoderPadded.apply(attr, pos, params) is the same layer without that wait, for training loops
-that must not stall on the device: it returns n rows (its outputs start zeroed and the kernels
-write rows below Nv only, so rows past Nv are zero) and Nv as a one-element device tensor.
-Nothing in its forward or backward synchronizes the host. A device-detected error (corrupt
-input, capacity) leaves Nv = 0, which makes rd_loss's distortion NaN.
+that must not stall on the device: it returns n rows (rows past Nv zero) and Nv as a one-element
+device tensor. Nothing in its forward or backward synchronizes the host. A device-detected error
+(corrupt input, capacity) leaves Nv = 0 and every row zero, which makes rd_loss's distortion NaN.
 
 rd_loss is the rate-distortion objective of the differentiable workload: the mean squared error
 of the decoded attributes against the voxel means plus lambda times the rate proxy
-sum log2(1 + |yhat| / step).
+sum log2(1 + |yhat| / step). On plain contiguous float32 device rows it runs as one HIP launch pair
+(_RdLoss); every other call is the same formula in torch operators.
 """
 from __future__ import annotations
+
+import math
 
 import torch
 
@@ -63,13 +65,13 @@ class SteCoderPadded(torch.autograd.Function):
         if not attr.is_cuda:
             raise ValueError("SteCoderPadded runs on the GPU only")
         n = int(pos.shape[0])
-        rows = (max(n, 1), int(params.C))
-        # zeroed outputs: the kernels write rows below Nv only
-        z = [torch.zeros(rows, dtype=torch.float32, device=attr.device) for _ in range(3)]
-        fwd = gsc.ste_forward(pos.contiguous(), attr.detach().contiguous(), params, yhat=z[0], ahat=z[1], aref=z[2])
-        info = fwd.encoded.info
-        # Nv on the device (0 after a device-detected error)
-        nv = torch.where(info[0:1] == 0, info[1:2], torch.zeros_like(info[1:2])).to(torch.int64)
+        # the kernels write rows below Nv; the rest is cleared once Nv is known on the device
+        fwd = gsc.ste_forward(pos.contiguous(), attr.detach().contiguous(), params)
+        nv = gsc.ste_pad(fwd)
+        z = (fwd.yhat, fwd.ahat, fwd.aref)
+        if n == 0:
+            for t in z:  # (one row is allocated)
+                t.zero_()
         ctx.fwd = fwd
         out = [t[:n] for t in z]
         ctx.mark_non_differentiable(out[2], nv)
@@ -80,11 +82,71 @@ class SteCoderPadded(torch.autograd.Function):
         return _backward(ctx, g_yhat, g_ahat), None, None
 
 
+class _RdLoss(torch.autograd.Function):
+    """rd_loss on plain rows. The difference ahat - aref is kept for the backward as an output of its
+    own, so that neither ahat nor aref has to stay unchanged until then, and so that gradients of
+    the gradient flow through it."""
+
+    @staticmethod
+    def forward(ctx, yhat, ahat, aref, steps, lam, nv):
+        ctx.set_materialize_grads(False)
+        loss, dist, rate, ctx.count, diff = gsc.rd_loss_forward(yhat, ahat, aref, steps, lam, nv=nv)
+        ctx.lam = lam
+        ctx.save_for_backward(yhat, diff, steps)
+        return loss, dist, rate, diff
+
+    @staticmethod
+    def backward(ctx, g_loss, g_dist, g_rate, g_diff):
+        yhat, diff, steps = ctx.saved_tensors
+        gs = (g_loss, g_dist, g_rate)
+        if not torch.is_grad_enabled() and g_diff is None and any(g is not None for g in gs):
+            gy, ga = gsc.rd_loss_backward(yhat, diff, steps, ctx.lam, ctx.count, *gs)
+            return gy, ga, None, None, None, None
+        # differentiable (create_graph), or a gradient of the difference: torch operators
+        zero = torch.zeros((), dtype=yhat.dtype, device=yhat.device)
+        gl, gd, gr = (zero if g is None else g for g in gs)
+        ga = (gl + gd) * 2.0 * diff / (ctx.count * diff.shape[1])
+        gy = (gl + gr) * (ctx.lam / math.log(2.0)) * yhat.sgn() / (steps + yhat.abs())
+        if g_diff is not None:
+            ga = ga + g_diff
+        return gy, ga, None, None, None, None
+
+
+def _plain_rows(yhat, ahat, aref, steps, lam, nv):
+    """Whether rd_loss may run as _RdLoss: ordinary float32 rows on the current device, gradients
+    wanted of yhat and ahat only, and no mode or transform active that has to see the operators."""
+    ts = (yhat, ahat, aref, steps) + (() if nv is None else (nv,))
+    if not all(type(t) in (torch.Tensor, torch.nn.Parameter) for t in ts) or type(lam) not in (int, float):
+        return False
+    if not yhat.is_cuda or yhat.device.index != torch.cuda.current_device():
+        return False
+    if yhat.dim() != 2 or yhat.shape[0] < 1 or not 1 <= yhat.shape[1] <= gsc.MAX_CHANNELS:
+        return False
+    for t in ts:
+        if t.device != yhat.device or t.layout != torch.strided or not t.is_contiguous() or t.is_neg():
+            return False
+    if any(t.dtype != torch.float32 for t in ts[:4]) or any(t.shape != yhat.shape for t in ts[1:3]):
+        return False
+    if steps.shape != yhat.shape[1:] or aref.requires_grad or steps.requires_grad:
+        return False
+    if nv is not None and (nv.dtype != torch.int64 or nv.numel() != 1):
+        return False
+    if torch.compiler.is_compiling() or torch.jit.is_tracing() or torch._C._are_functorch_transforms_active():
+        return False
+    if torch.autograd.forward_ad._current_level >= 0:
+        return False
+    return torch._C._len_torch_dispatch_stack() == 0 and torch._C._len_torch_function_stack() == 0
+
+
 def rd_loss(yhat, ahat, aref, steps, lam, nv=None):
     """(loss, distortion, rate): mean((ahat - aref)^2) + lam * sum(log2(1 + |yhat| / steps)).
 
     With nv (SteCoderPadded's device count) the rows are the padded ones: the mean is taken over
     the nv voxel rows (the zero rows past them add nothing to either term), with no host wait."""
+    if _plain_rows(yhat, ahat, aref, steps, lam, nv):
+        if torch.is_grad_enabled() and (yhat.requires_grad or ahat.requires_grad):
+            return _RdLoss.apply(yhat, ahat, aref, steps, lam, nv)[:3]
+        return gsc.rd_loss_forward(yhat, ahat, aref, steps, lam, nv=nv, want_diff=False)[:3]
     sq = (ahat - aref) ** 2
     r = torch.log2(1.0 + yhat.abs() / steps)
     if nv is None:

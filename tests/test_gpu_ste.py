@@ -223,3 +223,94 @@ def test_padded_layer_matches_without_host_synchronization():
     step()
     torch.cuda.synchronize()
     assert torch.equal(tb.grad, first_grad)
+
+
+def _torch_rd_loss(yhat, ahat, aref, steps, lam, nv=None):
+    """rd_loss's formula in torch operators (any precision)."""
+    sq = (ahat - aref) ** 2
+    rate = lam * torch.log2(1.0 + yhat.abs() / steps).sum()
+    dist = sq.mean() if nv is None else sq.sum() / (nv.to(sq.dtype) * sq.shape[1]).reshape(())
+    return dist + rate, dist, rate
+
+
+@pytest.mark.parametrize("rows,C", [(1, 1), (3, 5), (257, 56), (5000, 64), (70_001, 56)])
+@pytest.mark.parametrize("padded", [False, True])
+def test_rd_loss_matches_the_formula(rows, C, padded):
+    """The fused loss against its formula in FP64: values, gradients (each of the three results
+    weighted differently), gradients of a gradient, and the forward without gradients. A sum of FP32
+    terms accumulated in FP64 and rounded once is within 1e-6; a gradient entry takes a handful
+    of FP32 roundings (1e-6 relative)."""
+    from paper_2606_05650_amd.ste import rd_loss
+    dev = _dev()
+    print(f"case rows={rows} C={C} padded={padded}", flush=True)
+    g = torch.Generator(device=dev).manual_seed(rows + C)
+    steps = 2.0 ** -torch.randint(3, 8, (C,), generator=g, device=dev).float()
+    y = (torch.randn(rows, C, generator=g, device=dev) / steps).round() * steps * 0.5
+    y[0, 0] = 0.0
+    h, r = (torch.randn(rows, C, generator=g, device=dev) for _ in range(2))
+    nv = None
+    if padded:
+        nv = torch.tensor([max(rows - 2, 1)], device=dev)
+        for t in (y, h, r):
+            t[int(nv):] = 0.0
+    lam = 0.01
+    w = (0.5, 2.0, 3.0)
+
+    def run(fn, dtype):
+        a, b = (t.to(dtype).detach().requires_grad_(True) for t in (y, h))
+        out = fn(a, b, r.to(dtype), steps.to(dtype), lam, nv=nv)
+        total = sum(k * o for k, o in zip(w, out))
+        ga, gb = torch.autograd.grad(total, (a, b), create_graph=True)
+        hb = torch.autograd.grad((ga * ga).sum() + (gb * gb).sum(), (a, b))
+        a2, b2 = (t.to(dtype).detach().requires_grad_(True) for t in (y, h))
+        sum(k * o for k, o in zip(w, fn(a2, b2, r.to(dtype), steps.to(dtype), lam, nv=nv))).backward()
+        return list(out) + [ga, gb, *hb, a2.grad, b2.grad]
+
+    got, want = run(rd_loss, torch.float32), run(_torch_rd_loss, torch.float64)
+    for i, (x, z) in enumerate(zip(got, want)):
+        assert x.dtype == torch.float32 and x.shape == z.shape
+        scale = z.abs().max().item()
+        assert (x.double() - z).abs().max().item() <= (4e-6 if i >= 5 else 1e-6) * scale, i
+    with torch.no_grad():
+        for x, z in zip(rd_loss(y, h, r, steps, lam, nv=nv), got):
+            assert torch.equal(x, z)
+
+
+def test_rd_loss_keeps_torch_semantics():
+    """What the fused loss's autograd function must not lose: ahat may change in place before the
+    backward, results may be changed in place, saved-tensor hooks see its tensors, and inputs it is
+    not made for (other types, layouts, transforms, CPU rows, steps with a gradient) still work."""
+    from paper_2606_05650_amd.ste import rd_loss
+    dev = _dev()
+    g = torch.Generator(device=dev).manual_seed(1)
+    y, h, r = (torch.randn(33, 8, generator=g, device=dev) for _ in range(3))
+    steps = torch.full((8,), 0.25, device=dev)
+    yl, hl = y.clone().requires_grad_(True), h.clone().requires_grad_(True)
+    want = torch.autograd.grad(_torch_rd_loss(yl, hl, r, steps, 0.01)[0], (yl, hl))
+    h2 = hl * 1.0
+    loss, _, _ = rd_loss(yl, h2, r, steps, 0.01)
+    h2.mul_(3.0)
+    loss += 1.0
+    got = torch.autograd.grad(loss, (yl, hl))
+    for a, b in zip(got, want):
+        torch.testing.assert_close(a, b, rtol=2e-6, atol=1e-9)
+    seen = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: seen.append(t.shape) or t, lambda t: t):
+        rd_loss(yl, hl, r, steps, 0.01)[0].backward()
+    assert y.shape in seen
+    ref = [t.double().cpu() for t in (y, h, r, steps)]
+    for args in ((y.double(), h.double(), r.double(), steps.double()), (y.cpu(), h.cpu(), r.cpu(), steps.cpu()),
+                 (y.t().contiguous().t(), h, r, steps), (y, h, r, steps[:1]), (y[:0], h[:0], r[:0], steps)):
+        out = rd_loss(*args, 0.01)
+        if args[0].shape[0]:
+            torch.testing.assert_close(out[0].double().cpu(), _torch_rd_loss(*ref, 0.01)[0], rtol=1e-6, atol=0)
+        else:
+            assert out[1].isnan()
+    s2 = steps.clone().requires_grad_(True)
+    rd_loss(y, h, r, s2, 0.01)[0].backward()
+    assert s2.grad is not None
+    per_row = torch.func.vmap(lambda a, b, c: rd_loss(a, b, c, steps, 0.01)[0])(y[:, None], h[:, None], r[:, None])
+    assert per_row.shape == (33,)
+    _, tangent = torch.func.jvp(lambda a: rd_loss(a, h, r, steps, 0.01)[0], (y,), (torch.ones_like(y),))
+    # (torch's own forward-mode formulas return this tangent in FP64)
+    torch.testing.assert_close(tangent.float(), want[0].sum(), rtol=1e-5, atol=1e-6)
