@@ -12,10 +12,19 @@
 //   * a decoder accepts a chunk only if its first state is at least 2^23 (an encoder's always
 //     is) and it ends in the state 2^23 with all its bytes consumed; an accepted chunk therefore
 //     holds at most 2 K + 4 bytes.
-// Encode: the byte counts (LDS histograms added to device-wide counters), the table (one wave),
-// then one thread per chunk codes its chunk into a scratch area, the chunks' offsets come from a
-// decoupled look-back over waves of 64 chunks, and each thread copies its bytes to their place.
-// Decode: one thread per chunk.
+// Encode: the byte counts (LDS histograms added to device-wide counters; the last workgroup to end
+// makes the table), then one thread per chunk codes its chunk, the chunks' offsets come from a
+// decoupled look-back over the waves, and each thread copies its bytes to their place. Decode: one
+// thread per chunk.
+//
+// A chunk is a serial chain of K steps and a frame has few chunks (13.7 K of 256 bytes for the 3.5 MB
+// of a 1M frame: less than one wave per SIMD), so a step's latency bounds both directions. Chunks
+// of at most RANS_STAGE_K bytes are coded wholly from LDS, where the step is about 14 instructions:
+// the bytes that may follow are read (decode) or written (encode) two at a time at the byte
+// position, whether or not the step takes them, in parallel with the table lookup, and the state
+// is renormalised by one shift. 3.5 MB, chunks of 256: encoding 39 -> 26 us, decoding 59 -> 31 us (byte
+// buffers of 64 bits in registers, a store per word and a table built with a scan per 64 slots before);
+// both directions with their launches 119 -> 71 us.
 #include "gsc_device.h"
 
 #include <cstring>
@@ -40,7 +49,9 @@ struct RansArgs {
     uint32_t hblocks;    // encode: histogram workgroups
     uint8_t *tmp;        // per-chunk scratch, chunk c at c * tmp_stride
     uint64_t tmp_stride;
+    uint32_t per;        // encode: chunks per wave
     uint32_t stage;      // LDS bytes of a wave's staged input (encode) or stream (decode); 0: none
+    uint32_t out_stride; // encode, staged: LDS bytes of a chunk's code
     int32_t *info;
 };
 
@@ -75,21 +86,90 @@ __host__ __device__ inline uint64_t rans_tmp_off(uint64_t nc) { return rans_alig
 __device__ inline uint64_t rans_data_off(uint32_t nc) { return sizeof(gsc_rans_header) + 512ull + 4ull * (nc + 1); }
 
 // ---------------------------------------------------------------------------------- encode
-// The info words (d_info[0..3]): the device status, n, and the stream bytes (encode, 0 on an
-// error), after every other kernel of the call.
-__global__ __launch_bounds__(WAVE) void k_rans_info(RansArgs a, int decode)
+// Counts a workgroup of a call's last launch as done (word RANS_DONE); the last one writes the info
+// words: the device status, n, and the stream bytes (encode, 0 on an error). Every wave's reports to
+// the workspace words are device-scope atomics that have completed before it is counted.
+constexpr uint32_t RANS_DONE = 1, RANS_HIST_DONE = 258, RANS_TOTAL = 259;  // workspace words
+__device__ inline void rans_finish(const RansArgs &a, bool decode)
 {
+    __builtin_amdgcn_s_waitcnt(0);
     if (threadIdx.x != 0) return;
-    const uint32_t e = __hip_atomic_load(&a.ws[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__hip_atomic_fetch_add(&a.ws[RANS_DONE], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u != gridDim.x) return;
+    const uint32_t e = ld_relaxed32(&a.ws[0]);
     a.info[0] = (int32_t)e;
     a.info[1] = (int32_t)(uint32_t)a.n;
-    uint64_t bytes = 0;
-    if (!decode && e == 0) {
-        uint32_t *tot = reinterpret_cast<uint32_t *>(a.out + sizeof(gsc_rans_header) + 512) + a.nc;
-        bytes = rans_data_off(a.nc) + __hip_atomic_load(tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    const uint64_t bytes = !decode && e == 0 ? rans_data_off(a.nc) + ld_relaxed32(&a.ws[RANS_TOTAL]) : 0u;
     a.info[2] = (int32_t)(uint32_t)(bytes & 0xFFFFFFFFu);
     a.info[3] = (int32_t)(uint32_t)(bytes >> 32);
+}
+
+// An empty input: the header, a zero table and one offset (encode); the decoder writes no byte.
+__global__ __launch_bounds__(WAVE) void k_rans_empty(RansArgs a, int decode)
+{
+    const uint32_t lane = lane_id();
+    if (!decode) {
+        GAS uint16_t *tab = gp(reinterpret_cast<uint16_t *>(a.out + sizeof(gsc_rans_header)));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) tab[4 * lane + q] = 0;
+    }
+    if (lane != 0) return;
+    if (!decode) {
+        gsc_rans_header *h = reinterpret_cast<gsc_rans_header *>(a.out);
+        h->magic = GSC_RANS_MAGIC;
+        h->version = GSC_VERSION;
+        h->n = 0;
+        h->K = a.K;
+        h->nchunks = 0;
+        h->total = 0;
+        h->reserved = 0;
+        *reinterpret_cast<uint32_t *>(a.out + sizeof(gsc_rans_header) + 512) = 0;
+    }
+    a.info[0] = GSC_OK;
+    a.info[1] = 0;
+    a.info[2] = decode ? 0 : (int32_t)(uint32_t)rans_data_off(0);
+    a.info[3] = 0;
+}
+
+// The table from the byte counts, written to the stream (the header comes with the last chunk), by
+// one wave.
+__device__ inline void rans_table(const RansArgs &a)
+{
+    const uint32_t lane = lane_id();
+    GAS uint16_t *tab = gp(reinterpret_cast<uint16_t *>(a.out + sizeof(gsc_rans_header)));
+    uint32_t c[4], f[4];
+    uint32_t present = 0, sum = 0;
+    uint32_t best = 0, best_s = 0;  // count and byte of this lane's most frequent byte
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t s = lane * 4 + q;
+        c[q] = __hip_atomic_load(&a.ws[2 + s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        present += c[q] ? 1u : 0u;
+        if (c[q] > best) {
+            best = c[q];
+            best_s = s;
+        }
+    }
+    uint32_t P = present;
+    for (int o = 32; o > 0; o >>= 1) P += __shfl_xor(P, o, WAVE);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f[q] = c[q] ? 1u + (uint32_t)((uint64_t)c[q] * (RANS_M - P) / a.n) : 0u;
+        sum += f[q];
+    }
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, WAVE);
+    // the most frequent byte, the smallest on a tie (lanes hold increasing bytes)
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t bc = __shfl_xor(best, o, WAVE), bs = __shfl_xor(best_s, o, WAVE);
+        if (bc > best || (bc == best && bs < best_s)) {
+            best = bc;
+            best_s = bs;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t s = lane * 4 + q;
+        tab[s] = (uint16_t)(f[q] + (s == best_s ? RANS_M - sum : 0u));
+    }
 }
 
 __global__ __launch_bounds__(RANS_HIST_THREADS) void k_rans_hist(RansArgs a)
@@ -137,6 +217,13 @@ __global__ __launch_bounds__(RANS_HIST_THREADS) void k_rans_hist(RansArgs a)
         for (int q = 0; q < RANS_HCOPIES; ++q) c += s_h[q][s];
         if (c) atomicAdd(&a.ws[2 + s], c);
     }
+    // the last workgroup whose counts are in makes the table
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_h[0][0] = __hip_atomic_fetch_add(&a.ws[RANS_HIST_DONE], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x;
+    __syncthreads();
+    if (s_h[0][0] && threadIdx.x < WAVE) rans_table(a);
 }
 
 // Clears the error and count words and the look-back words (encode) or the error word (decode).
@@ -145,74 +232,17 @@ __global__ __launch_bounds__(256) void k_rans_zero(uint32_t *ws, uint32_t nwords
     for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < nwords; i += gridDim.x * 256) ws[i] = 0;
 }
 
-// One wave: the table from the byte counts, written to the stream (the header comes with the
-// last chunk). An empty input gets its whole stream here.
-__global__ __launch_bounds__(WAVE) void k_rans_table(RansArgs a)
-{
-    const uint32_t lane = lane_id();
-    GAS uint16_t *tab = gp(reinterpret_cast<uint16_t *>(a.out + sizeof(gsc_rans_header)));
-    if (a.nc == 0) {
-        if (lane == 0) {  // an empty input: the header, a zero table and one offset
-            gsc_rans_header *h = reinterpret_cast<gsc_rans_header *>(a.out);
-            h->magic = GSC_RANS_MAGIC;
-            h->version = GSC_VERSION;
-            h->n = 0;
-            h->K = a.K;
-            h->nchunks = 0;
-            h->total = 0;
-            h->reserved = 0;
-            *reinterpret_cast<uint32_t *>(a.out + sizeof(gsc_rans_header) + 512) = 0;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) tab[4 * lane + q] = 0;
-        return;
-    }
-    uint32_t c[4], f[4];
-    uint32_t present = 0, sum = 0;
-    uint32_t best = 0, best_s = 0;  // count and byte of this lane's most frequent byte
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t s = lane * 4 + q;
-        c[q] = __hip_atomic_load(&a.ws[2 + s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        present += c[q] ? 1u : 0u;
-        if (c[q] > best) {
-            best = c[q];
-            best_s = s;
-        }
-    }
-    uint32_t P = present;
-    for (int o = 32; o > 0; o >>= 1) P += __shfl_xor(P, o, WAVE);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        f[q] = c[q] ? 1u + (uint32_t)((uint64_t)c[q] * (RANS_M - P) / a.n) : 0u;
-        sum += f[q];
-    }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, WAVE);
-    // the most frequent byte, the smallest on a tie (lanes hold increasing bytes)
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t bc = __shfl_xor(best, o, WAVE), bs = __shfl_xor(best_s, o, WAVE);
-        if (bc > best || (bc == best && bs < best_s)) {
-            best = bc;
-            best_s = bs;
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t s = lane * 4 + q;
-        tab[s] = (uint16_t)(f[q] + (s == best_s ? RANS_M - sum : 0u));
-    }
-}
-
 // The encoder's table in LDS, one entry per byte value s (f its frequency, st its start):
 //   x = f 2^19, the renormalisation bound;
-//   y = ceil(2^(31 + l) / f) with l = ceil(log2 f): for every state x < 2^31, which is where the
-//       coder divides, floor(x / f) = (x y) >> (31 + l), the multiply-high division by an
-//       invariant integer of Granlund and Montgomery (1994), exact here because y < 2^32 and
-//       y f - 2^(31 + l) < 2^l;
-//   z = (M - f) | (31 + l) << 24: with q = floor(x / f), the coded state (q << 12) + x - q f + st
-//       is x + q (M - f) + st, a 24-bit multiply-add (q < 2^19 and M - f < 2^12), whose operand
-//       bits 24..31 are ignored, and the shift (31 + l) of the division is z >> 24;
-//   w = st, and f itself in bits 16..28 (0 marks a byte absent from the table).
+//   y, z >> 24: the division by f of a state x < 2^31, where the coder divides, as a multiply-high:
+//       floor(x / f) = mulhi(x, y) >> (l - 1) with y = ceil(2^(31 + l) / f), l = ceil(log2 f) (the
+//       division by an invariant integer of Granlund and Montgomery (1994), exact here because
+//       y < 2^32 and y f - 2^(31 + l) < 2^l); for f = 1, y = 2^32 - 1 gives x - 1, which w makes up for;
+//   z = (M - f) | shift << 24: with q = floor(x / f), the coded state (q << 12) + x - q f + st is
+//       x + q (M - f) + st, a 24-bit multiply-add (q < 2^19 and M - f < 2^12) whose operand bits
+//       24..31 are ignored;
+//   w = st (f = 1: st + M - 1, since there q is one less than x), and f itself in bits 16..28 (0 marks
+//       a byte absent from the table).
 // Built by the workgroup's one wave, four bytes a lane.
 __device__ inline void enc_table(const GAS uint16_t *tab, uint4 *s_enc)
 {
@@ -227,12 +257,19 @@ __device__ inline void enc_table(const GAS uint16_t *tab, uint4 *s_enc)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const uint32_t fq = f[q];
-        const uint32_t l = fq > 1 ? 32u - (uint32_t)__clz(fq - 1) : 0u;
-        const uint32_t y = fq ? (uint32_t)(((1ull << (31 + l)) + fq - 1) / fq) : 0u;
-        s_enc[4 * lane + q] = make_uint4(fq << 19, y, ((RANS_M - fq) & 0xFFFFFFu) | ((31u + l) << 24),
-                                         (st & 0xFFFFu) | (fq << 16));
+        const uint32_t l = fq > 1 ? 32u - (uint32_t)__clz(fq - 1) : 1u;
+        const uint32_t y = fq > 1 ? (uint32_t)(((1ull << (31 + l)) + fq - 1) / fq) : fq ? 0xFFFFFFFFu : 0u;
+        s_enc[4 * lane + q] = make_uint4(fq << 19, y, ((RANS_M - fq) & 0xFFFFFFu) | ((l - 1u) << 24),
+                                         ((st + (fq == 1 ? RANS_M - 1u : 0u)) & 0xFFFFu) | (fq << 16));
         st += fq;
     }
+}
+
+// The state after coding a byte of table entry t in the renormalised state x.
+__device__ inline uint32_t enc_code(uint32_t x, const uint4 &t)
+{
+    const uint32_t q = __umulhi(x, t.y) >> (t.z >> 24);
+    return __umul24(q, t.z) + x + (t.w & 0xFFFFu);  // (__umul24 reads bits 0..23 of each operand)
 }
 
 // Reads the aligned 8-byte block at address p of the input [lo, hi). The vector load is issued
@@ -282,8 +319,33 @@ __device__ inline void enc_step(EncState &E, const uint4 &t, GAS uint32_t *tw)
         tw[E.top / 4] = (uint32_t)(E.acc >> (8 * (E.na - 4)));
         E.na -= 4;
     }
-    const uint32_t q = (uint32_t)(((uint64_t)x * t.y) >> (t.z >> 24));
-    E.x = __umul24(q, t.z) + x + (t.w & 0xFFFFu);  // (__umul24 reads bits 0..23 of each operand)
+    E.x = enc_code(x, t);
+}
+
+// The coding state of one staged chunk: its bytes are written downwards from `pos` in LDS.
+#define LAS __attribute__((address_space(3)))
+struct __attribute__((packed)) RansTwo {  // (at any address)
+    uint16_t v;
+};
+struct __attribute__((packed)) RansFour {
+    uint32_t v;
+};
+struct EncLds {
+    uint32_t x;
+    LAS uint8_t *pos;
+    bool bad;
+};
+// Codes one byte: the state's low two bytes are written below `pos` (the first one emitted highest)
+// whether or not they leave the state; those that do not are written over by the next step.
+__device__ inline void enc_step(EncLds &E, const uint4 &t)
+{
+    E.bad |= t.w < (1u << 16);  // (an absent byte: impossible with the stream's own table)
+    const uint32_t x = E.x, x1 = x >> 8;
+    reinterpret_cast<LAS RansTwo *>(E.pos - 2)->v = (uint16_t)__builtin_amdgcn_perm(0u, x, 0x0c0c0001u);
+    // at most two bytes, since x < 2^31 and the bound is f 2^19 >= 2^19
+    const uint32_t k = (x >= t.x ? 1u : 0u) + (x1 >= t.x ? 1u : 0u);
+    E.pos -= k;
+    E.x = enc_code(x >> (8 * k), t);
 }
 
 // Copies the aligned 16-byte blocks that cover the addresses [lo_r, hi_r) of a buffer [lo, hi)
@@ -291,7 +353,7 @@ __device__ inline void enc_step(EncState &E, const uint4 &t, GAS uint32_t *tw)
 // the buffer (only its first and last blocks hold any) are read one by one as zero, after a
 // vector load from `safe` (16 readable bytes, 4-aligned) that keeps every path's load count
 // equal. Returns the copy's first address. Four loads per lane are issued before their stores.
-__device__ inline uint64_t stage_blocks(uint8_t *s, uint64_t lo_r, uint64_t hi_r, uint64_t lo, uint64_t hi,
+__device__ __attribute__((always_inline)) inline uint64_t stage_blocks(uint8_t *s, uint64_t lo_r, uint64_t hi_r, uint64_t lo, uint64_t hi,
                                         uint64_t safe)
 {
     const uint32_t lane = lane_id();
@@ -321,8 +383,36 @@ __device__ inline uint64_t stage_blocks(uint8_t *s, uint64_t lo_r, uint64_t hi_r
     return sb;
 }
 
-// Thread c codes chunk c into its scratch area, the wave's chunks find their offsets by
-// look-back, and each thread copies its bytes to their place.
+// Copies the m bytes at src (an aligned scratch area of 32-bit words, or LDS) to the global address dst:
+// bytes up to the first 4-aligned destination, whole words (each from two aligned source words),
+// then the last bytes. P: pointer to bytes, PW: to words, in the source's address space.
+template <class P, class PW>
+__device__ inline void put_bytes(P src0, uint32_t so, uint64_t dst, uint32_t m)
+{
+    const uint32_t h = min(m, (uint32_t)((4u - (uint32_t)(dst & 3u)) & 3u));
+    for (uint32_t k = 0; k < h; ++k) *reinterpret_cast<GAS uint8_t *>(dst + k) = src0[so + k];
+    const uint32_t nw = (m - h) / 4, s1 = so + h, dl = s1 & 3u;
+    const PW sw = reinterpret_cast<PW>(src0 + (s1 - dl));
+    GAS uint32_t *dw = reinterpret_cast<GAS uint32_t *>(dst + h);
+    constexpr uint32_t CU = 8;  // words per step: the loads of a step are issued together
+    uint32_t i = 0;
+    // a source word past the last whole one is read only when dl > 0, and then it still starts before
+    // the end of the scratch area (which is 4-aligned)
+    for (; i + CU <= nw; i += CU) {
+        uint32_t v[CU + 1];
+#pragma unroll
+        for (uint32_t u = 0; u < CU; ++u) v[u] = sw[i + u];
+        v[CU] = dl ? sw[i + CU] : 0u;
+#pragma unroll
+        for (uint32_t u = 0; u < CU; ++u) dw[i + u] = __builtin_amdgcn_alignbyte(v[u + 1], v[u], dl);
+    }
+    for (; i < nw; ++i) dw[i] = __builtin_amdgcn_alignbyte(dl ? sw[i + 1] : 0u, sw[i], dl);
+    for (uint32_t k = h + 4 * nw; k < m; ++k) *reinterpret_cast<GAS uint8_t *>(dst + k) = src0[so + k];
+}
+
+// Thread t of a wave codes chunk (wave index) per + t (per chunks a wave) into its scratch area, or
+// (STAGED) into LDS; the wave's chunks find their offsets by look-back, and each thread copies its
+// bytes to their place.
 template <bool STAGED>
 __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
 {
@@ -332,34 +422,36 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
     enc_table(tab, s_enc);
     __syncthreads();
     const uint32_t lane = lane_id();
-    const uint32_t c = blockIdx.x * RANS_THREADS + lane;
-    const uint32_t S = (uint32_t)a.tmp_stride;
-    GAS uint8_t *tmp = gp(a.tmp) + (uint64_t)c * S;
-    EncState E;
-    E.x = RANS_L;
-    E.na = 0;
-    E.top = S;
-    E.acc = 0;
-    E.bad = false;
+    const uint32_t c = blockIdx.x * a.per + lane;
+    const bool mine = lane < a.per && c < a.nc;
+    const uint32_t S = STAGED ? a.out_stride : (uint32_t)a.tmp_stride;  // the chunk's area, its bytes at the end
+    GAS uint8_t *tmp = gp(a.tmp) + (uint64_t)c * a.tmp_stride;
     uint32_t m = 0;  // bytes of this chunk
     // staged: the wave's chunks are consecutive, so one copy holds all their bytes (made by every
-    // lane, also those past the last chunk)
+    // lane, also those without a chunk); the chunks' areas follow it
     uint8_t *s_in = reinterpret_cast<uint8_t *>(s_dyn);
+    LAS uint8_t *s_out = (LAS uint8_t *)s_in + a.stage + lane * a.out_stride;
     uint64_t sb = 0;
     if (STAGED) {
         const uint64_t lo = reinterpret_cast<uint64_t>(a.in), hi = lo + a.n;
-        const uint64_t w0 = lo + (uint64_t)blockIdx.x * RANS_THREADS * a.K;
-        sb = stage_blocks(s_in, w0, min(w0 + (uint64_t)RANS_THREADS * a.K, hi), lo, hi, reinterpret_cast<uint64_t>(a.ws));
+        const uint64_t w0 = lo + (uint64_t)blockIdx.x * a.per * a.K;
+        sb = stage_blocks(s_in, w0, min(w0 + (uint64_t)a.per * a.K, hi), lo, hi, reinterpret_cast<uint64_t>(a.ws));
         __syncthreads();
     }
-    if (c < a.nc) {
+    if (mine) {
         GAS uint32_t *tw = reinterpret_cast<GAS uint32_t *>(tmp);
         const uint64_t lo = reinterpret_cast<uint64_t>(a.in), hi = lo + a.n;
         const uint64_t b = lo + (uint64_t)c * a.K, e = min(b + a.K, hi);  // the chunk's addresses
         const uint64_t safe = reinterpret_cast<uint64_t>(a.ws);          // (8-aligned, >= 16 bytes)
+        EncState E = {RANS_L, 0, S, 0, false};
+        EncLds L = {RANS_L, s_out + S, false};
         auto block8 = [&](uint64_t q) -> uint2 {
             if (STAGED) return *reinterpret_cast<const uint2 *>(s_in + (q - sb));
             return in_block8(q, lo, hi, safe);
+        };
+        auto step = [&](const uint4 &t) {
+            if (STAGED) enc_step(L, t);
+            else enc_step(E, t, tw);
         };
         // the chunk's 8-byte blocks from the last down, the next one loaded before this one is coded
         uint64_t p = (e - 1) & ~7ull;
@@ -374,27 +466,33 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
             for (int q = 0; q < 8; ++q) t[q] = s_enc[(w[q / 4] >> (8 * (q % 4))) & 255u];
             if (p >= b && p + 8 <= e) {  // a block inside the chunk (all but its first and last)
 #pragma unroll
-                for (int q = 7; q >= 0; --q) enc_step(E, t[q], tw);
+                for (int q = 7; q >= 0; --q) step(t[q]);
             } else {
 #pragma unroll
                 for (int q = 7; q >= 0; --q)
-                    if (p + q >= b && p + q < e) enc_step(E, t[q], tw);
+                    if (p + q >= b && p + q < e) step(t[q]);
             }
             if (!more) break;
             p -= 8;
             cur = nxt;
         }
         // the final state, low byte emitted first (stored most significant first)
-        E.acc = (E.acc << 32) | __builtin_bswap32(E.x);
-        E.na += 4;
-        m = S - E.top + E.na;
-        if (E.na >= 4) {
-            E.top -= 4;
-            tw[E.top / 4] = (uint32_t)(E.acc >> (8 * (E.na - 4)));
-            E.na -= 4;
+        if (STAGED) {
+            L.pos -= 4;
+            reinterpret_cast<LAS RansFour *>(L.pos)->v = __builtin_bswap32(L.x);
+            m = S - (uint32_t)(L.pos - s_out);
+        } else {
+            E.acc = (E.acc << 32) | __builtin_bswap32(E.x);
+            E.na += 4;
+            m = S - E.top + E.na;
+            if (E.na >= 4) {
+                E.top -= 4;
+                tw[E.top / 4] = (uint32_t)(E.acc >> (8 * (E.na - 4)));
+                E.na -= 4;
+            }
+            if (E.na > 0) tw[E.top / 4 - 1] = (uint32_t)(E.acc << (8 * (4 - E.na)));
         }
-        if (E.na > 0) tw[E.top / 4 - 1] = (uint32_t)(E.acc << (8 * (4 - E.na)));
-        if (E.bad) rans_error(a.ws, GSC_ERR_INTERNAL);  // (impossible with the stream's own table)
+        if (STAGED ? L.bad : E.bad) rans_error(a.ws, GSC_ERR_INTERNAL);  // (impossible with the stream's own table)
     }
     // the chunks' offsets: a scan over the wave, then the look-back over the waves
     uint64_t incl = m;
@@ -409,54 +507,21 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
     const uint64_t d0 = rans_data_off(a.nc);
     const uint64_t room = a.cap > d0 ? a.cap - d0 : 0;
     GAS uint32_t *offs = gp(reinterpret_cast<uint32_t *>(a.out + sizeof(gsc_rans_header) + 512));
-    if (c < a.nc) {
+    if (mine) {
         if (first + m > room || first + m > 0xFFFFFFFFull) {
             rans_error(a.ws, GSC_ERR_CAPACITY);
         } else {
             offs[c] = (uint32_t)first;
-            // copy tmp[S - m, S) to the chunk's place: bytes up to the first 4-aligned destination
-            // address, whole words (each from two aligned source words), then the last bytes
-            const uint64_t src = reinterpret_cast<uint64_t>(a.tmp) + (uint64_t)c * S + (S - m);
             const uint64_t dst = reinterpret_cast<uint64_t>(a.out) + d0 + first;
-            const uint32_t h = min(m, (uint32_t)((4u - (uint32_t)(dst & 3u)) & 3u));
-            for (uint32_t k = 0; k < h; ++k)
-                *reinterpret_cast<GAS uint8_t *>(dst + k) = *reinterpret_cast<const GAS uint8_t *>(src + k);
-            const uint32_t nw = (m - h) / 4;
-            const uint64_t s1 = src + h;
-            const uint32_t dl = (uint32_t)(s1 & 3u);
-            const GAS uint32_t *sw = reinterpret_cast<const GAS uint32_t *>(s1 - dl);
-            GAS uint32_t *dw = reinterpret_cast<GAS uint32_t *>(dst + h);
-            constexpr uint32_t CU = 8;  // words per step: the loads of a step are issued together
-            uint32_t i = 0;
-            if (dl == 0) {
-                for (; i + CU <= nw; i += CU) {
-                    uint32_t v[CU];
-#pragma unroll
-                    for (uint32_t u = 0; u < CU; ++u) v[u] = sw[i + u];
-#pragma unroll
-                    for (uint32_t u = 0; u < CU; ++u) dw[i + u] = v[u];
-                }
-                for (; i < nw; ++i) dw[i] = sw[i];
-            } else {
-                // a source word past the last whole one is read only when dl > 0, and then it still
-                // starts before the end of the scratch area (which is 4-aligned)
-                for (; i + CU <= nw; i += CU) {
-                    uint32_t v[CU + 1];
-#pragma unroll
-                    for (uint32_t u = 0; u <= CU; ++u) v[u] = sw[i + u];
-#pragma unroll
-                    for (uint32_t u = 0; u < CU; ++u) dw[i + u] = __builtin_amdgcn_alignbyte(v[u + 1], v[u], dl);
-                }
-                for (; i < nw; ++i) dw[i] = __builtin_amdgcn_alignbyte(sw[i + 1], sw[i], dl);
-            }
-            for (uint32_t k = h + 4 * nw; k < m; ++k)
-                *reinterpret_cast<GAS uint8_t *>(dst + k) = *reinterpret_cast<const GAS uint8_t *>(src + k);
+            if (STAGED) put_bytes<const LAS uint8_t *, const LAS uint32_t *>(s_out, S - m, dst, m);
+            else put_bytes<const GAS uint8_t *, const GAS uint32_t *>(tmp, S - m, dst, m);
         }
     }
-    if (c == a.nc - 1) {  // the last chunk: the total and the header
+    if (mine && c == a.nc - 1) {  // the last chunk: the total and the header
         const uint64_t total = first + m;
         if (total <= room && total <= 0xFFFFFFFFull) {
             offs[a.nc] = (uint32_t)total;
+            st_relaxed32(&a.ws[RANS_TOTAL], (uint32_t)total);
             gsc_rans_header *hd = reinterpret_cast<gsc_rans_header *>(a.out);
             hd->magic = GSC_RANS_MAGIC;
             hd->version = GSC_VERSION;
@@ -467,48 +532,50 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
             hd->reserved = 0;
         }
     }
+    rans_finish(a, false);
 }
 
 // ---------------------------------------------------------------------------------- decode
 // The decoder's table in LDS, one word per slot of [0, M): byte | (f - 1) << 8 | (slot - start)
-// << 20 of the byte whose range holds the slot. Each present byte marks its first slot; a
-// running maximum over the slots (64 at a time across the wave, carried from one step to the
-// next) then gives every slot its byte. Returns false (uniform) when the frequencies do not sum
-// to M.
-__device__ inline bool dec_table(const GAS uint16_t *tab, uint32_t *s_dec, uint32_t *s_fst)
+// << 20 of the byte whose range holds the slot. The first slots of the present bytes are bits of a
+// mask, and the bytes' words a list in order: a slot's byte is the list entry of its rank among the
+// first slots, so the 64 groups of 64 slots need nothing from one another but the number of first
+// slots before them (one scan). Returns false (uniform) when the frequencies do not sum to M.
+__device__ inline bool dec_table(const GAS uint16_t *tab, uint32_t *s_dec, uint32_t *s_list, unsigned long long *s_mask)
 {
+    static_assert(RANS_M == WAVE * WAVE, "one mask word per lane");
     const uint32_t lane = lane_id();
-    uint32_t f[4], sum = 0;
+    uint32_t f[4], sum = 0, present = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         f[q] = tab[4 * lane + q];
         sum += f[q];
+        present += f[q] ? 1u : 0u;
     }
-    const uint32_t incl = wave_incl_scan(sum);
+    const uint32_t incl = wave_incl_scan(sum), rank0 = wave_incl_scan(present) - present;
     if (__shfl(incl, WAVE - 1, WAVE) != RANS_M) return false;
-    for (uint32_t j = lane; j < RANS_M; j += WAVE) s_dec[j] = 0;
+    s_mask[lane] = 0;
     __syncthreads();
-    uint32_t st = incl - sum;
+    uint32_t st = incl - sum, r = rank0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        if (f[q]) s_dec[st] = 4 * lane + q + 1;
-        s_fst[4 * lane + q] = f[q] | ((st & 0xFFFu) << 13);
+        if (f[q]) {
+            atomicOr(&s_mask[st / WAVE], 1ull << (st % WAVE));
+            s_list[r++] = (4 * lane + q) | ((f[q] - 1u) << 8) | (st << 20);
+        }
         st += f[q];
     }
     __syncthreads();
-    uint32_t carry = 0;
-    for (uint32_t j0 = 0; j0 < RANS_M; j0 += WAVE) {
-        uint32_t v = s_dec[j0 + lane];
-#pragma unroll
-        for (int o = 1; o < WAVE; o <<= 1) {
-            const uint32_t t = __shfl_up(v, o, WAVE);
-            if (lane >= (uint32_t)o) v = max(v, t);
-        }
-        v = max(v, carry);
-        carry = __shfl(v, WAVE - 1, WAVE);
-        const uint32_t s = v - 1, fst = s_fst[s];
-        const uint32_t fs = fst & 0x1FFFu, sts = fst >> 13;
-        s_dec[j0 + lane] = s | ((fs - 1) << 8) | ((j0 + lane - sts) << 20);
+    const unsigned long long mine = s_mask[lane];
+    const uint32_t cnt = (uint32_t)__popcll(mine), before = wave_incl_scan(cnt) - cnt;
+    const unsigned long long upto = (2ull << lane) - 1ull;  // slots 0 .. lane of a group (lane 63: all)
+#pragma unroll 8
+    for (uint32_t g = 0; g < WAVE; ++g) {
+        const unsigned long long m = ((unsigned long long)__builtin_amdgcn_readlane((uint32_t)(mine >> 32), g) << 32) |
+                                     (uint32_t)__builtin_amdgcn_readlane((uint32_t)mine, g);
+        const uint32_t k = __builtin_amdgcn_readlane(before, g) + (uint32_t)__popcll(m & upto) - 1u;
+        const uint32_t e = s_list[k];
+        s_dec[g * WAVE + lane] = (e & 0xFFFFFu) | ((g * WAVE + lane - (e >> 20)) << 20);
     }
     __syncthreads();
     return true;
@@ -577,17 +644,53 @@ __device__ inline uint32_t dec_step(DecState &D, const uint32_t *s_dec, uint32_t
     return t & 255u;
 }
 
-// Decodes chunk c (stream bytes [p0, p1) of the data area) into its output bytes.
-template <bool STAGED>
-__device__ inline void dec_chunk(const RansArgs &a, uint32_t c, uint64_t p0, uint64_t p1, uint64_t d0,
-                                 const uint32_t *s_dec, const uint8_t *s_st, uint64_t sb, uint64_t se)
+// The state of one staged chunk's decoder: the state and the place of the next stream byte in LDS.
+struct DecLds {
+    uint32_t x;
+    const LAS uint8_t *pos;
+};
+// Decodes one byte. The four bytes at `pos` are read beside the table lookup; the state takes the
+// first k of them, k = 0, 1 or 2: a state of at least 2^23 leaves at least 2^11 after the lookup.
+__device__ inline uint32_t dec_step(DecLds &D, const uint32_t *s_dec)
+{
+    const uint32_t w = reinterpret_cast<const LAS RansFour *>(D.pos)->v;
+    const uint32_t t = s_dec[D.x & (RANS_M - 1u)], xh = D.x >> RANS_BITS;
+    const uint32_t x = __umul24((t >> 8) & 0xFFFu, xh) + (xh + (t >> 20));  // ((f - 1) xh + xh + bias: xh < 2^19)
+    // 8 k: 2^23 and more has at most 8 leading zeros (none only in a damaged chunk's first states)
+    const uint32_t k8 = __builtin_elementwise_sub_sat((uint32_t)__clz(x), 1u) & 0x18u;
+    const uint64_t win = ((uint64_t)x << 32) | __builtin_bswap32(w);
+    D.x = (uint32_t)((win << k8) >> 32);
+    D.pos += k8 / 8;
+    return t & 255u;
+}
+
+// The output bytes [b, e) of a chunk at a.out: bytes up to the first 4-aligned address, four to a
+// word, the last bytes.
+template <class Step>
+__device__ inline void dec_output(const RansArgs &a, uint64_t b, uint64_t e, Step step)
+{
+    GAS uint8_t *ob = gp(a.out);
+    const uint64_t oa = reinterpret_cast<uint64_t>(a.out) + b;
+    const uint64_t hb = min(e - b, (uint64_t)((4u - (uint32_t)(oa & 3u)) & 3u));
+    uint64_t i = b;
+    for (; i < b + hb; ++i) ob[i] = (uint8_t)step();
+    GAS uint32_t *ow = reinterpret_cast<GAS uint32_t *>(oa + hb);
+    for (uint32_t j = 0; i + 4 <= e; i += 4, ++j) {
+        uint32_t v = step();
+        v |= step() << 8;
+        v |= step() << 16;
+        v |= step() << 24;
+        ow[j] = v;
+    }
+    for (; i < e; ++i) ob[i] = (uint8_t)step();
+}
+
+// Decodes chunk c (stream bytes [p0, p1) of the data area), its words read from global memory.
+__device__ inline void dec_chunk(const RansArgs &a, uint32_t c, uint64_t p0, uint64_t p1, uint64_t d0, const uint32_t *s_dec)
 {
     const uint64_t lo = reinterpret_cast<uint64_t>(a.src), hi = lo + a.cap;
     const uint64_t safe = lo;
-    auto word = [&](uint64_t q) -> uint32_t {
-        if (STAGED) return q >= sb && q + 4 <= se ? *reinterpret_cast<const uint32_t *>(s_st + (q - sb)) : 0u;
-        return src_word(q, lo, hi, safe);
-    };
+    auto word = [&](uint64_t q) -> uint32_t { return src_word(q, lo, hi, safe); };
     const uint32_t len = (uint32_t)(p1 - p0);
     const uint64_t q0 = lo + d0 + p0;  // the chunk's first byte
     DecState D;
@@ -605,44 +708,39 @@ __device__ inline void dec_chunk(const RansArgs &a, uint32_t c, uint64_t p0, uin
     D.bad = D.x < RANS_L;  // an encoder's first stored state is at least 2^23
     D.nw = word(D.wa);
     D.wa += 4;
-    GAS uint8_t *ob = gp(a.out);
     const uint64_t b = (uint64_t)c * a.K, e = min(b + a.K, a.n);
-    // head: bytes up to the first 4-aligned output address; body: four bytes to a word; tail
-    const uint64_t oa = reinterpret_cast<uint64_t>(a.out) + b;
-    const uint64_t hb = min(e - b, (uint64_t)((4u - (uint32_t)(oa & 3u)) & 3u));
-    uint64_t i = b;
-    for (; i < b + hb; ++i) ob[i] = (uint8_t)dec_step(D, s_dec, len, word);
-    GAS uint32_t *ow = reinterpret_cast<GAS uint32_t *>(oa + hb);
-    for (uint32_t j = 0; i + 4 <= e; i += 4, ++j) {
-        uint32_t v = dec_step(D, s_dec, len, word);
-        v |= dec_step(D, s_dec, len, word) << 8;
-        v |= dec_step(D, s_dec, len, word) << 16;
-        v |= dec_step(D, s_dec, len, word) << 24;
-        ow[j] = v;
-    }
-    for (; i < e; ++i) ob[i] = (uint8_t)dec_step(D, s_dec, len, word);
+    dec_output(a, b, e, [&]() { return dec_step(D, s_dec, len, word); });
     if (D.bad || D.x != RANS_L || D.used != len) rans_error(a.ws, GSC_ERR_CORRUPT_STREAM);
+}
+
+// The same from the LDS copy: the chunk's bytes start at `src`. A chunk takes at most two bytes a step,
+// so a damaged one reads at most 2 K + 4 bytes past its start, within the copy's area (whatever lies
+// there: it has then taken more bytes than it has, and is rejected).
+__device__ inline void dec_chunk_lds(const RansArgs &a, uint32_t c, uint32_t len, const uint32_t *s_dec, const LAS uint8_t *src)
+{
+    const uint32_t x = __builtin_bswap32(reinterpret_cast<const LAS RansFour *>(src)->v);
+    const bool bad = x < RANS_L;  // an encoder's first stored state is at least 2^23
+    DecLds D = {bad ? RANS_L : x, src + 4};
+    const uint64_t b = (uint64_t)c * a.K, e = min(b + a.K, a.n);
+    dec_output(a, b, e, [&]() { return dec_step(D, s_dec); });
+    if (bad || D.x != RANS_L || (uint32_t)(D.pos - src) != len) rans_error(a.ws, GSC_ERR_CORRUPT_STREAM);
 }
 
 // Thread c decodes chunk c. The header and table are checked by every workgroup, the chunk's
 // offsets by its thread. Staged (chunks of at most RANS_STAGE_K bytes), the wave first copies
-// its chunks' stream bytes to LDS and the chunk's words come from there (words outside the copy
-// read as zero: only a chunk that takes more bytes than it has gets there, and it is rejected);
-// a wave whose bytes do not fit the copy holds a chunk longer than an encoder writes (2 K + 4
-// bytes) and is rejected whole. Otherwise the words come from global memory. The decoded bytes
-// are stored four to a word (byte by byte where the chunk starts or ends inside a word).
+// its chunks' stream bytes to LDS; a wave whose bytes do not fit the copy holds a chunk longer than
+// an encoder writes (2 K + 4 bytes) and is rejected whole. Otherwise the words come from global
+// memory. The decoded bytes are stored four to a word (byte by byte where the chunk starts or ends
+// inside a word).
 template <bool STAGED>
-__global__ __launch_bounds__(RANS_THREADS) void k_rans_decode(RansArgs a)
+__device__ __attribute__((always_inline)) inline void dec_wave(const RansArgs &a, gi4 *s_dyn, uint32_t *s_dec, uint32_t *s_list, unsigned long long *s_mask)
 {
-    extern __shared__ gi4 s_dyn[];
-    __shared__ uint32_t s_dec[RANS_M];
-    __shared__ uint32_t s_fst[256];
     const CAS gsc_rans_header *h = cp(reinterpret_cast<const gsc_rans_header *>(a.src));
     const GAS uint16_t *tab = gp(reinterpret_cast<const uint16_t *>(a.src + sizeof(gsc_rans_header)));
     const uint64_t d0 = rans_data_off(a.nc);
     const bool hdr = h->magic == GSC_RANS_MAGIC && h->n == a.n && h->K == a.K && h->nchunks == a.nc &&
                      d0 + (uint64_t)h->total <= a.cap;
-    if (!hdr || !dec_table(tab, s_dec, s_fst)) {  // (uniform)
+    if (!hdr || !dec_table(tab, s_dec, s_list, s_mask)) {  // (uniform)
         if (threadIdx.x == 0) rans_error(a.ws, GSC_ERR_CORRUPT_STREAM);
         return;
     }
@@ -653,30 +751,39 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_decode(RansArgs a)
     const bool mine = c < a.nc;
     const bool ok = p1 >= p0 + 4 && p1 <= h->total;
     if (mine && !ok) rans_error(a.ws, GSC_ERR_CORRUPT_STREAM);
-    const uint64_t lo = reinterpret_cast<uint64_t>(a.src), hi = lo + a.cap;
-    const uint64_t safe = lo;  // (the header: 8-aligned, 32 readable bytes)
-    uint8_t *s_st = reinterpret_cast<uint8_t *>(s_dyn);
-    uint64_t sb = 0, se = 0;
-    if (STAGED) {
-        const uint64_t rlo = mine && ok ? p0 : ~0ull, rhi = mine && ok ? p1 : 0ull;
-        uint64_t wlo = rlo, whi = rhi;
-        for (int o = 32; o > 0; o >>= 1) {
-            wlo = min(wlo, (uint64_t)__shfl_xor(wlo, o, WAVE));
-            whi = max(whi, (uint64_t)__shfl_xor(whi, o, WAVE));
-        }
-        if (whi > wlo && whi - wlo + 32 > a.stage) {  // (uniform)
-            if (threadIdx.x == 0) rans_error(a.ws, GSC_ERR_CORRUPT_STREAM);
-                return;
-        }
-        if (whi > wlo) {
-            sb = stage_blocks(s_st, lo + d0 + wlo, lo + d0 + whi, lo, hi, safe);
-            se = sb + (whi + d0 + lo - sb + 15) / 16 * 16;
-        }
-        __syncthreads();
+    if (!STAGED) {
+        if (mine && ok) dec_chunk(a, c, p0, p1, d0, s_dec);
+        return;
     }
-    if (mine && ok) dec_chunk<STAGED>(a, c, p0, p1, d0, s_dec, s_st, sb, se);
+    const uint64_t lo = reinterpret_cast<uint64_t>(a.src), hi = lo + a.cap;
+    const uint64_t rlo = mine && ok ? p0 : ~0ull, rhi = mine && ok ? p1 : 0ull;
+    uint64_t wlo = rlo, whi = rhi;
+    for (int o = 32; o > 0; o >>= 1) {
+        wlo = min(wlo, (uint64_t)__shfl_xor(wlo, o, WAVE));
+        whi = max(whi, (uint64_t)__shfl_xor(whi, o, WAVE));
+    }
+    if (whi > wlo && whi - wlo + 32 > a.stage) {  // (uniform)
+        if (threadIdx.x == 0) rans_error(a.ws, GSC_ERR_CORRUPT_STREAM);
+        return;
+    }
+    uint8_t *s_st = reinterpret_cast<uint8_t *>(s_dyn);
+    uint64_t sb = 0;
+    if (whi > wlo)  // (safe reads: the header, 8-aligned, 32 readable bytes)
+        sb = stage_blocks(s_st, lo + d0 + wlo, lo + d0 + whi, lo, hi, lo);
+    __syncthreads();
+    if (mine && ok) dec_chunk_lds(a, c, (uint32_t)(p1 - p0), s_dec, (const LAS uint8_t *)s_st + (uint32_t)(lo + d0 + p0 - sb));
 }
 
+template <bool STAGED>
+__global__ __launch_bounds__(RANS_THREADS) void k_rans_decode(RansArgs a)
+{
+    extern __shared__ gi4 s_dyn[];
+    __shared__ uint32_t s_dec[RANS_M];
+    __shared__ uint32_t s_list[256];
+    __shared__ unsigned long long s_mask[WAVE];
+    dec_wave<STAGED>(a, s_dyn, s_dec, s_list, s_mask);
+    rans_finish(a, true);
+}
 
 // ------------------------------------------------------------------------------- launches
 uint64_t rans_chunks(uint64_t n, uint32_t K) { return (n + K - 1) / K; }
@@ -724,21 +831,30 @@ hipError_t launch_rans_encode(const uint8_t *in, uint64_t n, uint32_t K, uint8_t
     a.out = out;
     a.cap = cap;
     a.info = info;
-    const uint32_t zw = (uint32_t)rans_head_words(a.nc);
-    hipLaunchKernelGGL(k_rans_zero, dim3(min((zw + 255) / 256, 1024u)), dim3(256), 0, s, a.ws, zw);
-    if (a.nc > 0) hipLaunchKernelGGL(k_rans_hist, dim3(a.hblocks), dim3(RANS_HIST_THREADS), 0, s, a);
-    hipLaunchKernelGGL(k_rans_table, dim3(1), dim3(WAVE), 0, s, a);
-    if (a.nc > 0) {
-        const dim3 g((a.nc + RANS_THREADS - 1) / RANS_THREADS);
-        const uint32_t stage = (uint32_t)(RANS_THREADS * K + 32);
-        if (K <= RANS_STAGE_K && stage_fits(stage, 256 * sizeof(uint4))) {
-            a.stage = stage;
-            hipLaunchKernelGGL(k_rans_encode<true>, g, dim3(RANS_THREADS), a.stage, s, a);
-        } else {
-            hipLaunchKernelGGL(k_rans_encode<false>, g, dim3(RANS_THREADS), 0, s, a);
-        }
+    if (a.nc == 0) {
+        hipLaunchKernelGGL(k_rans_empty, dim3(1), dim3(WAVE), 0, s, a, 0);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_rans_info, dim3(1), dim3(WAVE), 0, s, a, 0);
+    // Staged, a wave's input (per K bytes) and its chunks' code (2 K + 4 each at most) lie in LDS: 64
+    // chunks up to K = 512 (103 KB), 32 up to 1024. Twice as many waves then take look-back words,
+    // which lie in the chunks' scratch areas (unused by the staged kernel).
+    a.per = K <= RANS_STAGE_K / 2 ? RANS_THREADS : RANS_THREADS / 2;
+    a.out_stride = (2 * K + 4 + 7) / 8 * 8;
+    a.stage = (a.per * K + 32 + 15) / 16 * 16;
+    const size_t lds = a.stage + (size_t)a.per * a.out_stride;
+    const bool staged = K <= RANS_STAGE_K && stage_fits(lds, 256 * sizeof(uint4));
+    uint32_t zw = (uint32_t)rans_head_words(a.nc);
+    if (!staged) {
+        a.per = RANS_THREADS;
+    } else if (a.per < (uint32_t)RANS_THREADS) {
+        a.status = reinterpret_cast<uint64_t *>(a.tmp);
+        zw = (uint32_t)(rans_tmp_off(a.nc) / 4) + 2 * ((a.nc + a.per - 1) / a.per);
+    }
+    const dim3 g((a.nc + a.per - 1) / a.per);
+    hipLaunchKernelGGL(k_rans_zero, dim3(min((zw + 255) / 256, 1024u)), dim3(256), 0, s, a.ws, zw);
+    hipLaunchKernelGGL(k_rans_hist, dim3(a.hblocks), dim3(RANS_HIST_THREADS), 0, s, a);
+    if (staged) hipLaunchKernelGGL(k_rans_encode<true>, g, dim3(RANS_THREADS), lds, s, a);
+    else hipLaunchKernelGGL(k_rans_encode<false>, g, dim3(RANS_THREADS), 0, s, a);
     return hipGetLastError();
 }
 
@@ -750,19 +866,22 @@ hipError_t launch_rans_decode(const uint8_t *in, uint64_t in_bytes, uint64_t n, 
     a.cap = in_bytes;
     a.out = out;
     a.info = info;
-    hipLaunchKernelGGL(k_rans_zero, dim3(1), dim3(256), 0, s, a.ws, 1u);
-    if (a.nc > 0) {
-        const dim3 g((a.nc + RANS_THREADS - 1) / RANS_THREADS);
-        // an encoder's chunk holds at most 2 K + 4 bytes (two per symbol and the state)
-        const uint32_t stage = (uint32_t)(RANS_THREADS * (2 * K + 8) + 32);
-        if (K <= RANS_STAGE_K && stage_fits(stage, (RANS_M + 256) * sizeof(uint32_t))) {
-            a.stage = stage;
-            hipLaunchKernelGGL(k_rans_decode<true>, g, dim3(RANS_THREADS), a.stage, s, a);
-        } else {
-            hipLaunchKernelGGL(k_rans_decode<false>, g, dim3(RANS_THREADS), 0, s, a);
-        }
+    if (a.nc == 0) {
+        hipLaunchKernelGGL(k_rans_empty, dim3(1), dim3(WAVE), 0, s, a, 1);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_rans_info, dim3(1), dim3(WAVE), 0, s, a, 1);
+    hipLaunchKernelGGL(k_rans_zero, dim3(1), dim3(256), 0, s, a.ws, 2u);
+    const dim3 g((a.nc + RANS_THREADS - 1) / RANS_THREADS);
+    // an encoder's chunk holds at most 2 K + 4 bytes (two per symbol and the state); after the copy's
+    // `stage` bytes, room for what a damaged chunk reads past its end
+    const uint32_t stage = (uint32_t)(RANS_THREADS * (2 * K + 8) + 32);
+    const size_t lds = stage + 2 * (size_t)K + 32;
+    if (K <= RANS_STAGE_K && stage_fits(lds, (RANS_M + 256 + 2 * WAVE) * sizeof(uint32_t))) {
+        a.stage = stage;
+        hipLaunchKernelGGL(k_rans_decode<true>, g, dim3(RANS_THREADS), lds, s, a);
+    } else {
+        hipLaunchKernelGGL(k_rans_decode<false>, g, dim3(RANS_THREADS), 0, s, a);
+    }
     return hipGetLastError();
 }
 

@@ -162,3 +162,44 @@ def test_first_state_below_the_bound_is_rejected():
         out, info = gsc.rans_decode(torch.from_numpy(blob.copy()).to(dev), 1, 1)
         torch.cuda.synchronize()
         assert int(info[0].item()) == want
+
+
+@pytest.mark.parametrize("K", [511, 512, 513, 1023, 1024, 1025])
+def test_chunk_lengths_around_the_staged_paths(K):
+    """64 chunks a wave up to 512 bytes, 32 up to 1024 (their look-back words elsewhere), the path
+    without LDS copies above; several waves each, and a frequency-1 byte (its own division)."""
+    rng = np.random.default_rng(K)
+    data = rng.choice(40, size=70_001, p=rng.dirichlet(np.ones(40))).astype(np.uint8)
+    data[12_345] = 255
+    _roundtrip(data, K)
+
+
+def test_damaged_chunks_are_accepted_as_the_oracle_does():
+    """Single damaged bytes anywhere in the coded data, first states of 2^31 and more among them:
+    the GPU accepts and decodes exactly what the oracle does."""
+    dev = _dev()
+    rng = np.random.default_rng(8)
+    data = rng.choice(6, size=700, p=[0.5, 0.2, 0.1, 0.1, 0.06, 0.04]).astype(np.uint8)
+    K = 64
+    f, off, coded = orc.rans_encode(data, K)
+    good = np.frombuffer(_oracle_stream(data, K), dtype=np.uint8)
+    d0 = len(good) - len(coded)
+    print("case damaged chunks", flush=True)
+    seen = set()
+    for i in range(80):
+        at = int(off[i % 11]) if i < 22 else int(rng.integers(len(coded)))
+        bad = coded.copy()
+        bad[at] = 0xFF if i < 11 else int(rng.integers(256))
+        try:
+            want = orc.rans_decode(f, off, bad, len(data), K)
+        except ValueError:
+            want = None
+        blob = good.copy()
+        blob[d0:] = bad
+        out, info = gsc.rans_decode(torch.from_numpy(blob).to(dev), len(data), K)
+        torch.cuda.synchronize()
+        assert int(info[0].item()) == (5 if want is None else 0), i
+        if want is not None:
+            assert np.array_equal(out.cpu().numpy(), want)
+        seen.add(want is None)
+    assert True in seen
