@@ -86,91 +86,85 @@ __device__ inline uint32_t load_error(const Ctrl *c)
 __device__ inline uint32_t lane_id() { return __lane_id(); }
 __device__ inline uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
 
-__device__ inline uint32_t wave_incl_scan(uint32_t v)
+// Wave-wide scans and reductions by data-parallel-primitive moves between lanes (within rows of 16
+// lanes by 1, 2, 4 and 8, then lane 15 of rows 0 and 2 to the row above, then lane 31 to the upper
+// half): six vector instructions, where lane exchanges through the LDS unit (shuffles) cost six
+// round trips of about 100 cycles each. A lane without a source, or outside the rows of a step,
+// takes `old`. Every lane of the wave must be active.
+template <int CTRL, int ROWS>
+__device__ inline uint32_t dpp(uint32_t old, uint32_t v)
 {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-        uint32_t t = __shfl_up(v, o, WAVE);
-        if (lane >= (uint32_t)o) v += t;
-    }
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ inline uint64_t dpp(uint64_t old, uint64_t v)
+{
+    return (uint64_t)dpp<CTRL, ROWS>((uint32_t)old, (uint32_t)v) |
+           ((uint64_t)dpp<CTRL, ROWS>((uint32_t)(old >> 32), (uint32_t)(v >> 32)) << 32);
+}
+// Inclusive scan: op(x of lower lanes, own) in lane order; `id` is op's identity.
+template <class T, class F>
+__device__ inline T wave_scan(T v, T id, F op)
+{
+    v = op(dpp<0x111, 0xf>(id, v), v);  // row_shr:1
+    v = op(dpp<0x112, 0xf>(id, v), v);  // row_shr:2
+    v = op(dpp<0x114, 0xf>(id, v), v);  // row_shr:4
+    v = op(dpp<0x118, 0xf>(id, v), v);  // row_shr:8
+    v = op(dpp<0x142, 0xa>(id, v), v);  // row_bcast:15 into rows 1 and 3
+    v = op(dpp<0x143, 0xc>(id, v), v);  // row_bcast:31 into rows 2 and 3
     return v;
 }
-
-// Wave-wide minimum / maximum, returned to every lane (a workgroup-wide reduction through
-// same-address LDS atomics serializes: measured 14 us for 1536 of them on 6 addresses).
-__device__ inline float wave_min(float v)
+__device__ inline uint32_t read_lane(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
+__device__ inline uint64_t read_lane(uint64_t v, uint32_t lane)
 {
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) v = fminf(v, __shfl_xor(v, o, WAVE));
-    return v;
+    return (uint64_t)read_lane((uint32_t)v, lane) | ((uint64_t)read_lane((uint32_t)(v >> 32), lane) << 32);
 }
-__device__ inline float wave_max(float v)
+// The combination over the whole wave, in every lane.
+template <class T, class F>
+__device__ inline T wave_reduce(T v, T id, F op)
 {
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
-    return v;
+    return read_lane(wave_scan(v, id, op), (uint32_t)(WAVE - 1));
 }
-
+template <class T>
+__device__ inline T wave_incl_scan(T v)
+{
+    return wave_scan(v, (T)0, [](T a, T b) { return a + b; });
+}
+template <class T>
+__device__ inline T wave_sum(T v)
+{
+    return wave_reduce(v, (T)0, [](T a, T b) { return a + b; });
+}
+template <class T>
+__device__ inline T wave_or(T v)
+{
+    return wave_reduce(v, (T)0, [](T a, T b) { return a | b; });
+}
 __device__ inline uint32_t wave_umin(uint32_t v)
 {
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) v = min(v, (uint32_t)__shfl_xor(v, o, WAVE));
-    return v;
+    return wave_reduce(v, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return min(a, b); });
 }
 __device__ inline uint32_t wave_umax(uint32_t v)
 {
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) v = max(v, (uint32_t)__shfl_xor(v, o, WAVE));
-    return v;
+    return wave_reduce(v, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
 }
 
-// Exclusive scan over the NT threads of a block. `tmp` holds NT/64 + 1 words of LDS.
-// Returns the exclusive prefix of v; *total receives the block total. Ends with a barrier.
+// Exclusive scan over the NT threads of a block (at most 64 waves). `tmp` holds NT/64 words of LDS.
+// Returns the exclusive prefix of v; *total receives the block total. Every wave scans the wave
+// totals itself, so one barrier orders them; a second one frees tmp.
 template <int NT>
 __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t *tmp, uint32_t *total)
 {
-    constexpr int NW = NT / WAVE;
+    constexpr uint32_t NW = NT / WAVE;
     const uint32_t inc = wave_incl_scan(v);
-    const uint32_t w = threadIdx.x / WAVE;
-    if (lane_id() == WAVE - 1) tmp[w] = inc;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = lane_id();
+    if (lane == WAVE - 1) tmp[w] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int i = 0; i < NW; ++i) {
-            uint32_t t = tmp[i];
-            tmp[i] = run;
-            run += t;
-        }
-        tmp[NW] = run;
-    }
+    const uint32_t c = lane < NW ? tmp[lane] : 0u;
+    const uint32_t wi = wave_incl_scan(c);
+    if (total) *total = read_lane(wi, NW - 1);
     __syncthreads();
-    const uint32_t r = tmp[w] + inc - v;
-    if (total) *total = tmp[NW];
-    __syncthreads();
-    return r;
-}
-
-// Exclusive scan within groups of GS consecutive threads (GS a multiple of 64) of an NT-thread
-// block. `tmp` holds NT/64 words of LDS. Returns the exclusive prefix of v inside its group;
-// *total receives the group total. Every thread of the block must call it; ends with a barrier.
-template <int NT, int GS>
-__device__ inline uint32_t group_excl_scan(uint32_t v, uint32_t *tmp, uint32_t *total)
-{
-    const uint32_t inc = wave_incl_scan(v);
-    const uint32_t w = threadIdx.x / WAVE;
-    if (lane_id() == WAVE - 1) tmp[w] = inc;
-    __syncthreads();
-    const uint32_t g0 = (threadIdx.x / GS) * (GS / WAVE);
-    uint32_t pre = 0, tot = 0;
-    for (uint32_t i = g0; i < g0 + GS / WAVE; ++i) {
-        const uint32_t t = tmp[i];
-        if (i < w) pre += t;
-        tot += t;
-    }
-    if (total) *total = tot;
-    __syncthreads();
-    return pre + inc - v;
+    return read_lane(wi - c, w) + inc - v;
 }
 
 // ------------------------------------------------------------ decoupled look-back scan
@@ -268,13 +262,8 @@ struct OpSegOr {
 template <class Op>
 __device__ inline uint64_t wave_combine_ordered(uint64_t v, uint32_t cnt)
 {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int k = 1; k < WAVE; k <<= 1) {
-        const uint64_t older = __shfl_down(v, k, WAVE);
-        if (lane + k < cnt) v = Op::combine(older, v);
-    }
-    return __shfl(v, 0, WAVE);
+    return wave_reduce(lane_id() < cnt ? v : Op::identity(), Op::identity(),
+                       [](uint64_t newer, uint64_t older) { return Op::combine(older, newer); });
 }
 
 // The same look-back performed by a whole wave: each step reads the 64 nearest predecessors at

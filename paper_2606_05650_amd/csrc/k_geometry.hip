@@ -540,18 +540,11 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_pass(TileMap m, int pass)
             s_tmp[NW + w] = ic;
         }
         __syncthreads();
-        if (tid < 2) {
-            uint32_t run = 0;
-#pragma unroll
-            for (int i = 0; i < NW; ++i) {
-                const uint32_t c = s_tmp[tid * NW + i];
-                s_tmp[tid * NW + i] = run;
-                run += c;
-            }
-        }
-        __syncthreads();
-        hist_excl = s_tmp[w] + ih - vh;
-        if (dig) s_lstart[d] = s_tmp[NW + w] + ic - tile_cnt;
+        // every wave scans the 2 NW wave totals itself (the second NW less all of the first)
+        const uint32_t c = lane < 2u * NW ? s_tmp[lane] : 0u, wi = wave_incl_scan(c);
+        const uint32_t wu = __builtin_amdgcn_readfirstlane(w);
+        hist_excl = read_lane(wi - c, wu) + ih - vh;
+        if (dig) s_lstart[d] = read_lane(wi - c, NW + wu) - read_lane(wi, NW - 1) + ic - tile_cnt;
     }
     __syncthreads();
     // keys to LDS in tile-local digit order: the keys leave the registers before the look-back,
@@ -728,7 +721,6 @@ __global__ __launch_bounds__(OCC_THREADS) void k_occupancy(TileMap m)
     __shared__ uint32_t s_carry[GSC_MAX_DEPTH];
     __shared__ uint32_t s_cnt[GSC_MAX_DEPTH];
     __shared__ uint64_t s_pref[GSC_MAX_DEPTH];
-    __shared__ uint32_t s_tmp[OCC_THREADS / WAVE + 1];
 
     const uint32_t f = frame_of(m, blockIdx.x);
     const CAS FrameDesc &fd = *cp(m.fd[f]);  // (not written while the kernel runs)
@@ -848,12 +840,7 @@ __global__ __launch_bounds__(OCC_THREADS) void k_occupancy(TileMap m)
         const uint32_t lane = lane_id();
         const uint32_t hd = lane <= J ? cp(ctrl)->hist_D[lane] : 0u;  // (written by the dedup kernel)
         const uint64_t size = lane < J ? (uint64_t)wave_incl_scan(hd) : 0ull;
-        uint64_t incl = size;
-#pragma unroll
-        for (int o = 1; o < WAVE; o <<= 1) {
-            const uint64_t t = __shfl_up(incl, o, WAVE);
-            if (lane >= (uint32_t)o) incl += t;
-        }
+        const uint64_t incl = wave_incl_scan(size);
         const uint64_t off = GSC_HEADER_BYTES + incl - size;
         if (lane <= J) s_off[lane] = off;
         if (lane == J) {
@@ -940,9 +927,7 @@ __device__ inline bool header_ok_wave(FD &fd, const CAS gsc_header *h)
         const float st = h->quant_step[lane];
         bad = bad || !(st > 0.0f) || !isfinite(st);
     }
-    uint64_t occ = a;  // the occupancy bytes: sizes of levels 0..J-1
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) occ += __shfl_xor(occ, o, WAVE);
+    const uint64_t occ = wave_sum(a);  // the occupancy bytes: sizes of levels 0..J-1
     if (__ballot(bad) != 0ull) return false;
     if (h->occ_offset != GSC_HEADER_BYTES || h->occ_bytes != occ) return false;
     const uint64_t co = align_up(GSC_HEADER_BYTES + occ, 256);

@@ -270,9 +270,7 @@ __device__ inline void prelude_tile(const TileMap &m, uint32_t f, int k, uint32_
         rnd[x] = 0;
         lm |= mine[x] ? 1ull << lvl[x] : 0ull;
     }
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) lm |= __shfl_xor(lm, o, WAVE);
-    lm = uniform64(lm);
+    lm = wave_or(lm);
     while (lm) {
         const uint32_t q = (uint32_t)(__ffsll((long long)lm) - 1);
         lm &= ~(1ull << q);
@@ -299,9 +297,7 @@ __device__ inline void prelude_tile(const TileMap &m, uint32_t f, int k, uint32_
     for (int x = 0; x < PRE_EPT; ++x) {
         wrank[x] = 0;
         uint64_t rm = mine[x] ? 1ull << rnd[x] : 0ull;
-#pragma unroll
-        for (int o = 1; o < WAVE; o <<= 1) rm |= __shfl_xor(rm, o, WAVE);
-        rm = uniform64(rm);
+        rm = wave_or(rm);
         while (rm) {
             const uint32_t r = (uint32_t)(__ffsll((long long)rm) - 1);
             rm &= ~(1ull << r);
@@ -333,7 +329,7 @@ __device__ inline void prelude_tile(const TileMap &m, uint32_t f, int k, uint32_
             a[q] = i < (uint32_t)SEG_N ? s_cnt[i] : 0u;
             sum += a[q];
         }
-        uint32_t ex = group_excl_scan<PRE_BLOCK, PRE_THREADS>(sum, s_tmp, nullptr);
+        uint32_t ex = block_excl_scan<PRE_BLOCK>(sum, s_tmp, nullptr);
 #pragma unroll
         for (int q = 0; q < PRE_SEG; ++q) {
             const uint32_t i = PRE_SEG * t + q;
@@ -1017,7 +1013,7 @@ __device__ inline UpItem up_item(const TileMap &m, int kmax, bool desc, uint32_t
             const uint32_t inc = wave_incl_scan(cf);
             const uint64_t b = __ballot(inc > g);
             const uint32_t f = __builtin_amdgcn_readfirstlane((uint32_t)(__ffsll((long long)b) - 1));
-            const uint32_t before = __builtin_amdgcn_readfirstlane((uint32_t)__shfl(inc - cf, (int)f, WAVE));
+            const uint32_t before = read_lane(inc - cf, f);
             const uint32_t local = g - before;
             u.k = k;
             u.f = f;

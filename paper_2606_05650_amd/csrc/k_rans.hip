@@ -149,14 +149,13 @@ __device__ inline void rans_table(const RansArgs &a)
             best_s = s;
         }
     }
-    uint32_t P = present;
-    for (int o = 32; o > 0; o >>= 1) P += __shfl_xor(P, o, WAVE);
+    const uint32_t P = wave_sum(present);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         f[q] = c[q] ? 1u + (uint32_t)((uint64_t)c[q] * (RANS_M - P) / a.n) : 0u;
         sum += f[q];
     }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, WAVE);
+    sum = wave_sum(sum);
     // the most frequent byte, the smallest on a tie (lanes hold increasing bytes)
     for (int o = 32; o > 0; o >>= 1) {
         const uint32_t bc = __shfl_xor(best, o, WAVE), bs = __shfl_xor(best_s, o, WAVE);
@@ -495,13 +494,7 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
         if (STAGED ? L.bad : E.bad) rans_error(a.ws, GSC_ERR_INTERNAL);  // (impossible with the stream's own table)
     }
     // the chunks' offsets: a scan over the wave, then the look-back over the waves
-    uint64_t incl = m;
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-        const uint64_t t = __shfl_up(incl, o, WAVE);
-        if (lane >= (uint32_t)o) incl += t;
-    }
-    const uint64_t wave_total = __shfl(incl, WAVE - 1, WAVE);
+    const uint64_t incl = wave_incl_scan((uint64_t)m), wave_total = read_lane(incl, (uint32_t)(WAVE - 1));
     const uint64_t base = lookback_wave<OpSum>(a.status, 1, blockIdx.x, wave_total, reinterpret_cast<Ctrl *>(a.ws));
     const uint64_t first = base + incl - m;
     const uint64_t d0 = rans_data_off(a.nc);
@@ -553,7 +546,7 @@ __device__ inline bool dec_table(const GAS uint16_t *tab, uint32_t *s_dec, uint3
         present += f[q] ? 1u : 0u;
     }
     const uint32_t incl = wave_incl_scan(sum), rank0 = wave_incl_scan(present) - present;
-    if (__shfl(incl, WAVE - 1, WAVE) != RANS_M) return false;
+    if (read_lane(incl, (uint32_t)(WAVE - 1)) != RANS_M) return false;
     s_mask[lane] = 0;
     __syncthreads();
     uint32_t st = incl - sum, r = rank0;
@@ -757,11 +750,8 @@ __device__ __attribute__((always_inline)) inline void dec_wave(const RansArgs &a
     }
     const uint64_t lo = reinterpret_cast<uint64_t>(a.src), hi = lo + a.cap;
     const uint64_t rlo = mine && ok ? p0 : ~0ull, rhi = mine && ok ? p1 : 0ull;
-    uint64_t wlo = rlo, whi = rhi;
-    for (int o = 32; o > 0; o >>= 1) {
-        wlo = min(wlo, (uint64_t)__shfl_xor(wlo, o, WAVE));
-        whi = max(whi, (uint64_t)__shfl_xor(whi, o, WAVE));
-    }
+    const uint64_t wlo = wave_reduce(rlo, ~(uint64_t)0, [](uint64_t x, uint64_t y) { return min(x, y); });
+    const uint64_t whi = wave_reduce(rhi, (uint64_t)0, [](uint64_t x, uint64_t y) { return max(x, y); });
     if (whi > wlo && whi - wlo + 32 > a.stage) {  // (uniform)
         if (threadIdx.x == 0) rans_error(a.ws, GSC_ERR_CORRUPT_STREAM);
         return;

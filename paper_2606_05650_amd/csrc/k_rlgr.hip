@@ -63,8 +63,8 @@ __device__ inline RlBlock rl_block(uint32_t nv, uint32_t C, uint32_t B, uint32_t
     k.L = on ? min(B, nv - (j0 + dj) * B) : 0u;
     k.ubase = (size_t)j0 * B * C;
     k.off = on ? 4u * (dj * B * C + (tid - dj * C)) : 0u;
-    k.lmax = __builtin_amdgcn_readfirstlane(wave_umax(k.L));
-    k.lmin = __builtin_amdgcn_readfirstlane(wave_umin(on ? k.L : 0xFFFFFFFFu));
+    k.lmax = wave_umax(k.L);
+    k.lmin = wave_umin(on ? k.L : 0xFFFFFFFFu);
     return k;
 }
 
@@ -207,13 +207,7 @@ __global__ __launch_bounds__(RLGR_THREADS) void k_rlgr_count(RlgrArgs a)
     RlgrEnc<false> enc;
     rl_encode_block<false>(a, k, enc);
     const uint64_t words = k.L ? ((uint64_t)enc.nbits + 31) / 32 : 0;
-    uint64_t incl = words;
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-        const uint64_t t = __shfl_up(incl, o, WAVE);
-        if (tid >= (uint32_t)o) incl += t;
-    }
-    const uint64_t row_words = __shfl(incl, WAVE - 1, WAVE);
+    const uint64_t incl = wave_incl_scan(words), row_words = read_lane(incl, (uint32_t)(WAVE - 1));
     const uint64_t base = lookback_wave<OpSum>(a.status, 1, blockIdx.x, row_words, reinterpret_cast<Ctrl *>(a.err));
     const uint64_t first = base + incl - words;
     // the stream's capacity (header, table, words) bounds the total
