@@ -549,6 +549,15 @@ struct TileSched {
     bool final_level;
 };
 
+// A word that workgroups of the running launch may have written (and released): read with a
+// device-coherent load, so that the reader needs no acquire. (An acquire invalidates the XCD's whole
+// L2, under the workgroups still at first-level items, and was paid by every workgroup.)
+template <class T>
+__device__ inline T ld_live(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Loads the schedule of a tile of an upper level (k >= 2) into LDS: segment starts, level masks,
 // open positions, voxel indices of the entries, and the records with (a, b) of every local merge.
 // Returns false if the workgroup has nothing to do.
@@ -571,22 +580,22 @@ __device__ inline bool load_schedule(FD &fd, Ctrl *ctrl, int k, uint32_t tile,
     ts.nk = nk;
     ts.mlen = (int)(ts.e - s);
     ts.final_level = nk <= (uint32_t)RT;
-    const GAS uint16_t *lstart = gp(lv.lstart), *opos = gp(lv.opos);
-    const GAS uint32_t *sidx = gp(lv.s_idx), *recs = gp(lv.rec);
+    const uint16_t *lstart = lv.lstart, *opos = lv.opos;
+    const uint32_t *sidx = lv.s_idx, *recs = lv.rec;
     // Every load is issued at once, at clamped in-bounds slots, and none waits on another (one
     // memory round trip): the counts, the segment starts, the masks, all OPEN_CAP open
     // positions, the voxel indices and all RT record slots; slots past the tile's counts are
     // read but not used.
     static_assert(RAHT_THREADS == RT && LSTART_N <= 2 * RAHT_THREADS && OPEN_CAP <= RAHT_THREADS, "one entry per thread");
-    const uint32_t obase = lv.obase[tile], ocnt = lv.ocnt[tile];
+    const uint32_t obase = ld_live(&lv.obase[tile]), ocnt = ld_live(&lv.ocnt[tile]);
     const size_t lb = (size_t)tile * LSTART_N;
-    const uint16_t ls0 = lstart[lb + tid], ls1 = lstart[lb + min(tid + (uint32_t)RT, (uint32_t)LSTART_N - 1)];
-    const uint16_t op = opos[(size_t)tile * OPEN_CAP + min(tid, (uint32_t)OPEN_CAP - 1)];
-    const unsigned long long lmk = gp(lv.lmask)[(size_t)tile * NCLS + min(tid, (uint32_t)NCLS - 1)];
+    const uint16_t ls0 = ld_live(&lstart[lb + tid]), ls1 = ld_live(&lstart[lb + min(tid + (uint32_t)RT, (uint32_t)LSTART_N - 1)]);
+    const uint16_t op = ld_live(&opos[(size_t)tile * OPEN_CAP + min(tid, (uint32_t)OPEN_CAP - 1)]);
+    const unsigned long long lmk = ld_live(&lv.lmask[(size_t)tile * NCLS + min(tid, (uint32_t)NCLS - 1)]);
     const uint32_t jl = min(tid, (uint32_t)ts.mlen - 1);
-    const uint32_t vi = sidx[s + jl];
-    const uint32_t rec = recs[(size_t)tile * RT + tid];
-    const uint32_t ve = sidx[min(ts.e, nk - 1)], nv = ctrl->n_vox;
+    const uint32_t vi = ld_live(&sidx[s + jl]);
+    const uint32_t rec = ld_live(&recs[(size_t)tile * RT + tid]);
+    const uint32_t ve = ld_live(&sidx[min(ts.e, nk - 1)]), nv = ctrl->n_vox;
     const uint32_t vend = ts.e < nk ? ve : nv;
     ts.obase = obase;
     ts.ocnt = ocnt;
@@ -1600,8 +1609,6 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
         Ctrl *ctrl0 = cp(m.fd[0])->ctrl;
         // the upper levels' schedules and sizes are written (by the first Gp workgroups)
         done_wait(ctr_word(m, PRE_DONE), Gp, ctrl0);
-        if (tid == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        __syncthreads();
         const uint32_t U = up_totals(m, kmax, NP, s_ucnt);
         const UpArrays A{s_rec, s_ab, reinterpret_cast<uint16_t *>(s_lstw), reinterpret_cast<uint16_t *>(s_oposw),
                          s_m0, s_lmask, OpenSet{s_om[0], s_opre}, nullptr};
@@ -1653,8 +1660,6 @@ __global__ __launch_bounds__(RAHT_THREADS) void k_raht_inv_up(TileMap m, int kma
         const uint32_t Gp = min(level_items(m, 2, 1, s_fs), G);
         if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, ctr_word(m, PRE_DONE));
         done_wait(ctr_word(m, PRE_DONE), Gp, ctrl0);
-        if (tid == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        __syncthreads();
     }
     const uint32_t NP = channel_passes(cp(m.fd[0])->C4, 2);  // every frame of a launch has the same C
     const uint32_t U = up_totals(m, kmax, NP, s_ucnt);
