@@ -217,12 +217,13 @@ int max_K(const Frame *fr, int F)
     return K;
 }
 
-// Worst-case tiles of level 2 over the frames (the largest upper level).
-uint32_t upper_tiles(const Frame *fr, int F)
+// Worst-case tiles of level 2 (the largest upper level), or of every upper level, over the frames.
+uint32_t upper_tiles(const Frame *fr, int F, bool every)
 {
-    uint32_t t = 0;
-    for (int f = 0; f < F; ++f) t += fr[f].L.K >= 2 ? fr[f].L.tiles[2] : 0u;
-    return t;
+    uint64_t t = 0;
+    for (int f = 0; f < F; ++f)
+        for (uint32_t k = 2; k <= fr[f].L.K && (k == 2 || every); ++k) t += fr[f].L.tiles[k];
+    return (uint32_t)std::min<uint64_t>(t, 1u << 20);  // (far above any grid)
 }
 
 // The first level's schedule (the upper levels' schedules are built by the transform launches).
@@ -255,7 +256,7 @@ gsc_status run_inverse(const Frame *fr, int F, const RahtCfg &cfg, bool prelude,
     if (K >= 2) {
         StageScope sc(GSC_STAGE_RAHT_INV_TOP, s);
         TileMap m = make_map(fr, F, [](const Frame &) { return 1u; });
-        GSC_LAUNCH(launch_raht_inv_up(m, K, upper_tiles(fr, F) * channel_slices_upper(cfg.C4), prelude, cfg, s));
+        GSC_LAUNCH(launch_raht_inv_up(m, K, upper_tiles(fr, F, prelude) * channel_slices_upper(cfg.C4), prelude, cfg, s));
     }
     TileMap m = make_map(fr, F, [&cfg](const Frame &x) { return raht_blocks(x.L.tiles[1], 1, cfg.C4); });
     if (m.start[F] == 0) return GSC_OK;

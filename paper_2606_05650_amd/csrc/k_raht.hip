@@ -108,22 +108,225 @@ __device__ inline bool fp64_weights(FD &fd)
 // entries are known and whose prefix is resolved after the rest of the tile's work.
 constexpr int PRE_TILES = 1;  // tiles per workgroup
 
+// LDS of one tile's schedule construction by RT / EPT threads.
+template <int EPT>
+struct PreScratch {
+    static constexpr int NWV = RT / EPT / WAVE;
+    uint64_t mask[NLVL][NCHUNK];  // active lists (pre_lists)
+    uint32_t lvl_e;               // binary level of the entry after the tile
+    uint32_t cnt[SEG_N], fill[SEG_N];
+    uint32_t tmp[NWV + 1];
+    uint8_t rdl[RT];  // round of the chunk merge that last wrote an entry
+    LbScratch<NWV> lb;
+};
+// A thread's entries: entry j(x) = t + x THREADS, x < EPT, lies in wave chunk w + x WAVES, and the
+// chunk-wide steps (ballots, rounds) run once per chunk.
+template <int EPT>
+struct PreEntry {
+    static constexpr int THREADS = RT / EPT, WAVES = THREADS / WAVE;
+    int jj[EPT];
+    uint32_t lvl[EPT];  // binary level; 0: no entry
+    bool is_local[EPT], is_open[EPT];
+    int left[EPT], right[EPT];
+    uint32_t cls[EPT];
+    bool mine[EPT];  // a merge of the entry's own chunk
+    uint32_t rnd[EPT], wrank[EPT];
+};
+
+// Active lists of the levels that can hold a merge: an entry merges at a level of at most 3J
+// (the tile's first entry of the sequence, LVL_NONE, is in every list and is never a right
+// sibling). mask[q][c] has bit i set when entry i of chunk c has a level >= q. Levels are
+// below 128, so seven ballots give the bit planes of a chunk's levels; lane q compares every
+// entry's level with q on those planes (most significant bit first: an entry is below q
+// from the first bit where the two differ and q has a one) and stores the list of level q.
+template <int EPT>
+__device__ inline void pre_lists(PreScratch<EPT> &S, const PreEntry<EPT> &E, uint32_t J)
+{
+    const uint32_t t = threadIdx.x, w = t / WAVE, lane = lane_id();
+    for (uint32_t q = t; q < (uint32_t)SEG_N; q += PreEntry<EPT>::THREADS) {
+        S.cnt[q] = 0;
+        S.fill[q] = 0;
+    }
+#pragma unroll
+    for (int x = 0; x < EPT; ++x) S.rdl[E.jj[x]] = 0;
+    static_assert(NLVL <= WAVE && LVL_NONE < 128, "one lane per level; seven bit planes");
+    const uint32_t nlvl = min(3u * J + 1u, (uint32_t)NLVL);
+#pragma unroll
+    for (int x = 0; x < EPT; ++x) {
+        uint64_t plane[7];
+#pragma unroll
+        for (int bit = 0; bit < 7; ++bit) plane[bit] = __ballot((E.lvl[x] >> bit) & 1u);
+        uint64_t below = 0, same = ~0ull;  // entries below lane's q; entries equal so far
+#pragma unroll
+        for (int bit = 6; bit >= 0; --bit) {
+            const uint64_t qm = ((lane >> bit) & 1u) ? ~0ull : 0ull;
+            below |= same & ~plane[bit] & qm;
+            same &= ~(plane[bit] ^ qm);
+        }
+        if (lane >= 1 && lane < nlvl) S.mask[lane][w + x * PreEntry<EPT>::WAVES] = ~below;
+    }
+}
+
+// Each entry's left partner and node end from the lists (after a barrier), whether its merge is
+// local or it is open, and the class of a local merge.
+template <int EPT>
+__device__ inline void pre_partners(const PreScratch<EPT> &S, PreEntry<EPT> &E, int mlen)
+{
+    const uint32_t lane = lane_id(), lvl_e = S.lvl_e;
+#pragma unroll
+    for (int x = 0; x < EPT; ++x) {
+        const uint32_t wc = threadIdx.x / WAVE + x * PreEntry<EPT>::WAVES;  // the entry's chunk
+        const uint32_t lv_ = E.lvl[x];
+        E.is_local[x] = E.is_open[x] = false;
+        E.left[x] = -1;
+        E.right[x] = mlen;
+        E.cls[x] = CROSS;
+        if (E.jj[x] < mlen) {
+            if (lv_ >= 1 && lv_ < (uint32_t)NLVL) {
+                const uint64_t below = lanemask_lt();
+                const uint64_t above = ~below & ~(1ull << lane);
+                uint64_t mm = S.mask[lv_][wc] & below;
+                if (mm) {
+                    E.left[x] = (int)(wc * WAVE) + msb64(mm);
+                } else {
+                    for (int ww = (int)wc - 1; ww >= 0; --ww) {
+                        const uint64_t b = S.mask[lv_][ww];
+                        if (b) {
+                            E.left[x] = ww * WAVE + msb64(b);
+                            break;
+                        }
+                    }
+                }
+                mm = S.mask[lv_][wc] & above;
+                if (mm) {
+                    E.right[x] = (int)(wc * WAVE) + (__ffsll((long long)mm) - 1);
+                } else {
+                    for (int ww = (int)wc + 1; ww < NCHUNK; ++ww) {
+                        const uint64_t b = S.mask[lv_][ww];
+                        if (b) {
+                            E.right[x] = ww * WAVE + (__ffsll((long long)b) - 1);
+                            break;
+                        }
+                    }
+                }
+                E.is_local[x] = E.left[x] >= 0 && (E.right[x] < mlen || lvl_e > lv_);
+                E.is_open[x] = !E.is_local[x];
+                if (E.is_local[x] && E.left[x] / WAVE == (int)wc && (E.right[x] - 1) / WAVE == (int)wc) E.cls[x] = wc;
+            } else {
+                E.is_open[x] = true;  // entry 0 of the sequence never merges as a right sibling
+            }
+        }
+    }
+}
+
+// Rounds and segment counts (before a barrier).
+template <int EPT>
+__device__ inline void pre_rounds(PreScratch<EPT> &S, PreEntry<EPT> &E)
+{
+    const uint32_t w = threadIdx.x / WAVE, lane = lane_id();
+    // ---- rounds: each chunk's own merges by its wave (levels ascending, no workgroup barrier).
+    // A local merge's partner lies in the entry's own chunk, so the wave's chunks (one per entry
+    // slot) touch disjoint entries and walk the union of their levels in one loop.
+    uint64_t lm = 0;
+#pragma unroll
+    for (int x = 0; x < EPT; ++x) {
+        E.mine[x] = E.is_local[x] && E.cls[x] != CROSS;  // (then cls is the entry's own chunk)
+        E.rnd[x] = 0;
+        lm |= E.mine[x] ? 1ull << E.lvl[x] : 0ull;
+    }
+    lm = wave_or(lm);
+    while (lm) {
+        const uint32_t q = (uint32_t)(__ffsll((long long)lm) - 1);
+        lm &= ~(1ull << q);
+        uint32_t prev[EPT];
+#pragma unroll
+        for (int x = 0; x < EPT; ++x)
+            prev[x] = E.mine[x] && E.lvl[x] == q ? max((uint32_t)S.rdl[E.left[x]], (uint32_t)S.rdl[E.jj[x]]) : 0u;
+#pragma unroll
+        for (int x = 0; x < EPT; ++x) {
+            if (E.mine[x] && E.lvl[x] == q) {
+                E.rnd[x] = 1u + prev[x];
+                S.rdl[E.left[x]] = (uint8_t)E.rnd[x];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    // ---- segment counts: a chunk's merges are counted by its own wave with ballots (only one
+    // wave holds a chunk's merges; the rank in the ballot is the record's place in its segment);
+    // crossing merges keep their binary level as their round (a round of their own would cost a
+    // workgroup barrier per level) and are counted with LDS atomics
+#pragma unroll
+    for (int x = 0; x < EPT; ++x) {
+        E.wrank[x] = 0;
+        uint64_t rm = E.mine[x] ? 1ull << E.rnd[x] : 0ull;
+        rm = wave_or(rm);
+        while (rm) {
+            const uint32_t r = (uint32_t)(__ffsll((long long)rm) - 1);
+            rm &= ~(1ull << r);
+            const uint64_t bal = __ballot(E.mine[x] && E.rnd[x] == r);
+            if (E.mine[x] && E.rnd[x] == r) E.wrank[x] = (uint32_t)__popcll(bal & lanemask_lt());
+            if (lane == 0) S.cnt[r * NCLS + w + x * PreEntry<EPT>::WAVES] = (uint32_t)__popcll(bal);
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < EPT; ++x) {
+        if (E.is_local[x] && E.cls[x] == CROSS) {
+            E.rnd[x] = E.lvl[x];
+            atomicAdd(&S.cnt[E.rnd[x] * NCLS + CROSS], 1u);
+        }
+    }
+}
+
+// The round masks of the classes (mask c to put_mask(c, mask), by thread 0) and the segment starts:
+// cnt becomes its own exclusive scan. After a barrier; ends with one.
+template <int EPT, class PutMask>
+__device__ inline void pre_segments(PreScratch<EPT> &S, PutMask put_mask)
+{
+    constexpr int THREADS = PreEntry<EPT>::THREADS, SEG = (SEG_N + THREADS - 1) / THREADS;  // counts per thread
+    const uint32_t t = threadIdx.x;
+    if (t < WAVE) {  // lane q tests round q
+#pragma unroll
+        for (uint32_t c = 0; c < (uint32_t)NCLS; ++c) {
+            const uint64_t b = __ballot(S.cnt[t * NCLS + c] != 0);
+            if (t == 0) put_mask(c, b);
+        }
+    }
+    uint32_t a[SEG], sum = 0;
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) {
+        const uint32_t i = SEG * t + q;
+        a[q] = i < (uint32_t)SEG_N ? S.cnt[i] : 0u;
+        sum += a[q];
+    }
+    uint32_t ex = block_excl_scan<THREADS>(sum, S.tmp, nullptr);
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) {
+        const uint32_t i = SEG * t + q;
+        if (i < (uint32_t)SEG_N) S.cnt[i] = ex;
+        ex += a[q];
+    }
+    __syncthreads();
+}
+
+// The record of entry slot x's local merge and its place among the tile's (below RT).
+template <int EPT>
+__device__ inline uint32_t pre_record(PreScratch<EPT> &S, const PreEntry<EPT> &E, int x, uint32_t &slot)
+{
+    const uint32_t seg = E.rnd[x] * NCLS + E.cls[x];
+    slot = S.cnt[seg] + (E.mine[x] ? E.wrank[x] : atomicAdd(&S.fill[seg], 1u));
+    return (uint32_t)E.jj[x] | ((uint32_t)E.left[x] << 10) | ((uint32_t)E.right[x] << 20);
+}
+
 // lc (first level only, or null): the codes of entries s - 1 .. s + RT of the tile starting at
 // entry s, in LDS (lc[j] = code of entry s - 1 + j); otherwise they are read from the leaf codes.
 template <bool LIVE, int PRE_EPT>
-__device__ inline void prelude_tile(const TileMap &m, uint32_t f, int k, uint32_t tile, const uint64_t *lc = nullptr)
+__device__ inline void prelude_tile(const TileMap &m, uint32_t f, int k, uint32_t tile, PreScratch<PRE_EPT> &S,
+                                    const uint64_t *lc = nullptr)
 {
     static_assert(PRE_TILES == 1, "one tile per workgroup");
     constexpr int PRE_THREADS = RT / PRE_EPT, PRE_BLOCK = PRE_THREADS;
-    constexpr int PRE_WAVES = PRE_THREADS / WAVE;
-    constexpr int PRE_SEG = (SEG_N + PRE_THREADS - 1) / PRE_THREADS;  // segment counts per thread
     static_assert(PRE_EPT == 1 || PRE_EPT == 2, "one or two entries per thread");
-    __shared__ uint32_t s_lvl_e;
-    __shared__ uint64_t s_mask[NLVL][NCHUNK];
-    __shared__ uint32_t s_cnt[SEG_N], s_fill[SEG_N];
-    __shared__ uint32_t s_tmp[PRE_BLOCK / WAVE + 1];
-    __shared__ uint8_t s_rdl[RT];  // round of the chunk merge that last wrote an entry
-    __shared__ LbScratch<PRE_BLOCK / WAVE> s_lb;
 
     const CAS FrameDesc &fd = *cp(m.fd[f]);  // (not written while the kernel runs)
     Ctrl *ctrl = fd.ctrl;
@@ -139,230 +342,73 @@ __device__ inline void prelude_tile(const TileMap &m, uint32_t f, int k, uint32_
     const GAS uint64_t *codes = gp((fd.mode == MODE_FWD_F32 || fd.mode == MODE_ADJ_F32) ? fd.codes_in : fd.leaf);
     const GAS uint8_t *slvl = gp(lv.s_lvl);
 
-    // thread t holds entries j(x) = t + x PRE_THREADS, x < PRE_EPT: entry j(x) lies in wave
-    // chunk w + x PRE_WAVES, and the chunk-wide steps (ballots, rounds) run once per chunk
-    const uint32_t t = threadIdx.x, w = t / WAVE, lane = lane_id();
-    int jj[PRE_EPT];
-    uint32_t lvl[PRE_EPT];  // 0: no entry
+    const uint32_t t = threadIdx.x;
+    PreEntry<PRE_EPT> E;
 #pragma unroll
-    for (int x = 0; x < PRE_EPT; ++x) jj[x] = (int)(t + x * PRE_THREADS);
+    for (int x = 0; x < PRE_EPT; ++x) E.jj[x] = (int)(t + x * PRE_THREADS);
     // both entries' loads before any use, at clamped positions (a load under a per-entry
     // condition would be waited for where its branch joins)
     if (k == 1) {
         uint64_t c0[PRE_EPT], c1[PRE_EPT];
 #pragma unroll
         for (int x = 0; x < PRE_EPT; ++x) {
-            const uint32_t i = s + (uint32_t)min(jj[x], mlen - 1);
+            const uint32_t i = s + (uint32_t)min(E.jj[x], mlen - 1);
             c0[x] = lc ? lc[i - s] : codes[i > 0 ? i - 1 : 0];
             c1[x] = lc ? lc[i - s + 1] : codes[i];
         }
 #pragma unroll
         for (int x = 0; x < PRE_EPT; ++x)
-            lvl[x] = jj[x] < mlen ? (s + jj[x] == 0 ? LVL_NONE : merge_level(c0[x], c1[x])) : 0u;
+            E.lvl[x] = E.jj[x] < mlen ? (s + E.jj[x] == 0 ? LVL_NONE : merge_level(c0[x], c1[x])) : 0u;
     } else {
         uint32_t l[PRE_EPT];
 #pragma unroll
-        for (int x = 0; x < PRE_EPT; ++x) l[x] = slvl[s + (uint32_t)min(jj[x], mlen - 1)];
+        for (int x = 0; x < PRE_EPT; ++x) l[x] = slvl[s + (uint32_t)min(E.jj[x], mlen - 1)];
 #pragma unroll
-        for (int x = 0; x < PRE_EPT; ++x) lvl[x] = jj[x] < mlen ? l[x] : 0u;
+        for (int x = 0; x < PRE_EPT; ++x) E.lvl[x] = E.jj[x] < mlen ? l[x] : 0u;
     }
-    for (uint32_t q = t; q < (uint32_t)SEG_N; q += PRE_THREADS) {
-        s_cnt[q] = 0;
-        s_fill[q] = 0;
-    }
-#pragma unroll
-    for (int x = 0; x < PRE_EPT; ++x) s_rdl[jj[x]] = 0;
     if (t == 0)
-        s_lvl_e = e < nk ? (k == 1 ? (lc ? merge_level(lc[RT], lc[RT + 1]) : merge_level(codes[e - 1], codes[e])) : slvl[e])
+        S.lvl_e = e < nk ? (k == 1 ? (lc ? merge_level(lc[RT], lc[RT + 1]) : merge_level(codes[e - 1], codes[e])) : slvl[e])
                          : LVL_NONE;
-    // active lists of the levels that can hold a merge: an entry merges at a level of at most 3J
-    // (the tile's first entry of the sequence, LVL_NONE, is in every list and is never a right
-    // sibling). s_mask[q][c] has bit i set when entry i of chunk c has a level >= q. Levels are
-    // below 128, so seven ballots give the bit planes of a chunk's levels; lane q compares every
-    // entry's level with q on those planes (most significant bit first: an entry is below q
-    // from the first bit where the two differ and q has a one) and stores the list of level q.
-    static_assert(NLVL <= WAVE && LVL_NONE < 128, "one lane per level; seven bit planes");
-    const uint32_t nlvl = min(3u * fd.J + 1u, (uint32_t)NLVL);
-#pragma unroll
-    for (int x = 0; x < PRE_EPT; ++x) {
-        uint64_t plane[7];
-#pragma unroll
-        for (int bit = 0; bit < 7; ++bit) plane[bit] = __ballot((lvl[x] >> bit) & 1u);
-        uint64_t below = 0, same = ~0ull;  // entries below lane's q; entries equal so far
-#pragma unroll
-        for (int bit = 6; bit >= 0; --bit) {
-            const uint64_t qm = ((lane >> bit) & 1u) ? ~0ull : 0ull;
-            below |= same & ~plane[bit] & qm;
-            same &= ~(plane[bit] ^ qm);
-        }
-        if (lane >= 1 && lane < nlvl) s_mask[lane][w + x * PRE_WAVES] = ~below;
-    }
+    pre_lists(S, E, fd.J);
     __syncthreads();
-
-    const uint32_t lvl_e = s_lvl_e;
-    bool is_local[PRE_EPT], is_open[PRE_EPT];
-    int left[PRE_EPT], right[PRE_EPT];
-    uint32_t cls[PRE_EPT];
-#pragma unroll
-    for (int x = 0; x < PRE_EPT; ++x) {
-        const uint32_t wc = w + x * PRE_WAVES;  // the entry's chunk
-        const uint32_t lv_ = lvl[x];
-        is_local[x] = is_open[x] = false;
-        left[x] = -1;
-        right[x] = mlen;
-        cls[x] = CROSS;
-        if (jj[x] < mlen) {
-            if (lv_ >= 1 && lv_ < (uint32_t)NLVL) {
-                const uint64_t below = lanemask_lt();
-                const uint64_t above = ~below & ~(1ull << lane);
-                uint64_t mm = s_mask[lv_][wc] & below;
-                if (mm) {
-                    left[x] = (int)(wc * WAVE) + msb64(mm);
-                } else {
-                    for (int ww = (int)wc - 1; ww >= 0; --ww) {
-                        const uint64_t b = s_mask[lv_][ww];
-                        if (b) {
-                            left[x] = ww * WAVE + msb64(b);
-                            break;
-                        }
-                    }
-                }
-                mm = s_mask[lv_][wc] & above;
-                if (mm) {
-                    right[x] = (int)(wc * WAVE) + (__ffsll((long long)mm) - 1);
-                } else {
-                    for (int ww = (int)wc + 1; ww < NCHUNK; ++ww) {
-                        const uint64_t b = s_mask[lv_][ww];
-                        if (b) {
-                            right[x] = ww * WAVE + (__ffsll((long long)b) - 1);
-                            break;
-                        }
-                    }
-                }
-                is_local[x] = left[x] >= 0 && (right[x] < mlen || lvl_e > lv_);
-                is_open[x] = !is_local[x];
-                if (is_local[x] && left[x] / WAVE == (int)wc && (right[x] - 1) / WAVE == (int)wc) cls[x] = wc;
-            } else {
-                is_open[x] = true;  // entry 0 of the sequence never merges as a right sibling
-            }
-        }
-    }
+    pre_partners(S, E, mlen);
     // ---- open entries in order: ranks in the tile (the entries j(0) of all threads come before
     // the entries j(1): one scan of the two flags packed in one word), the tile's count published
     // at once (its prefix is resolved at the end, after the rest of the work)
     static_assert(PRE_THREADS < 65536, "two 16-bit counts per scanned word");
     uint32_t ptot;
-    const uint32_t pex = block_excl_scan<PRE_BLOCK>((is_open[0] ? 1u : 0u) | ((PRE_EPT > 1 && is_open[PRE_EPT - 1] ? 1u : 0u) << 16), s_tmp, &ptot);
+    const uint32_t pex = block_excl_scan<PRE_BLOCK>((E.is_open[0] ? 1u : 0u) | ((PRE_EPT > 1 && E.is_open[PRE_EPT - 1] ? 1u : 0u) << 16), S.tmp, &ptot);
     const uint32_t total = (ptot & 0xFFFFu) + (ptot >> 16);
     uint32_t rank[PRE_EPT];
     rank[0] = pex & 0xFFFFu;
     if (PRE_EPT > 1) rank[PRE_EPT - 1] = (ptot & 0xFFFFu) + (pex >> 16);
     lookback_block_publish<OpSum>(lv.status, 1, tile, total);
-    // ---- rounds: each chunk's own merges by its wave (levels ascending, no workgroup barrier).
-    // A local merge's partner lies in the entry's own chunk, so the wave's chunks (one per entry
-    // slot) touch disjoint entries and walk the union of their levels in one loop.
-    bool mine[PRE_EPT];
-    uint32_t rnd[PRE_EPT];
-    uint64_t lm = 0;
-#pragma unroll
-    for (int x = 0; x < PRE_EPT; ++x) {
-        mine[x] = is_local[x] && cls[x] != CROSS;  // (then cls is the entry's own chunk)
-        rnd[x] = 0;
-        lm |= mine[x] ? 1ull << lvl[x] : 0ull;
-    }
-    lm = wave_or(lm);
-    while (lm) {
-        const uint32_t q = (uint32_t)(__ffsll((long long)lm) - 1);
-        lm &= ~(1ull << q);
-        uint32_t prev[PRE_EPT];
-#pragma unroll
-        for (int x = 0; x < PRE_EPT; ++x)
-            prev[x] = mine[x] && lvl[x] == q ? max((uint32_t)s_rdl[left[x]], (uint32_t)s_rdl[jj[x]]) : 0u;
-#pragma unroll
-        for (int x = 0; x < PRE_EPT; ++x) {
-            if (mine[x] && lvl[x] == q) {
-                rnd[x] = 1u + prev[x];
-                s_rdl[left[x]] = (uint8_t)rnd[x];
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
-    // ---- segment counts: a chunk's merges are counted by its own wave with ballots (only one
-    // wave holds a chunk's merges; the rank in the ballot is the record's place in its segment);
-    // crossing merges keep their binary level as their round (a round of their own would cost a
-    // workgroup barrier per level) and are counted with LDS atomics
-    uint32_t wrank[PRE_EPT];
-#pragma unroll
-    for (int x = 0; x < PRE_EPT; ++x) {
-        wrank[x] = 0;
-        uint64_t rm = mine[x] ? 1ull << rnd[x] : 0ull;
-        rm = wave_or(rm);
-        while (rm) {
-            const uint32_t r = (uint32_t)(__ffsll((long long)rm) - 1);
-            rm &= ~(1ull << r);
-            const uint64_t bal = __ballot(mine[x] && rnd[x] == r);
-            if (mine[x] && rnd[x] == r) wrank[x] = (uint32_t)__popcll(bal & lanemask_lt());
-            if (lane == 0) s_cnt[r * NCLS + w + x * PRE_WAVES] = (uint32_t)__popcll(bal);
-        }
-    }
-#pragma unroll
-    for (int x = 0; x < PRE_EPT; ++x) {
-        if (is_local[x] && cls[x] == CROSS) {
-            rnd[x] = lvl[x];
-            atomicAdd(&s_cnt[rnd[x] * NCLS + CROSS], 1u);
-        }
-    }
+    pre_rounds(S, E);
     __syncthreads();
-    if (t < WAVE) {  // round masks of the classes: lane q tests round q
-#pragma unroll
-        for (uint32_t c = 0; c < (uint32_t)NCLS; ++c) {
-            const uint64_t b = __ballot(s_cnt[t * NCLS + c] != 0);
-            if (t == 0) gp(lv.lmask)[(size_t)tile * NCLS + c] = b;
-        }
-    }
-    {   // segment starts: exclusive scan of the SEG_N counts (PRE_SEG per thread)
-        uint32_t a[PRE_SEG], sum = 0;
-#pragma unroll
-        for (int q = 0; q < PRE_SEG; ++q) {
-            const uint32_t i = PRE_SEG * t + q;
-            a[q] = i < (uint32_t)SEG_N ? s_cnt[i] : 0u;
-            sum += a[q];
-        }
-        uint32_t ex = block_excl_scan<PRE_BLOCK>(sum, s_tmp, nullptr);
-#pragma unroll
-        for (int q = 0; q < PRE_SEG; ++q) {
-            const uint32_t i = PRE_SEG * t + q;
-            if (i < (uint32_t)SEG_N) s_cnt[i] = ex;
-            ex += a[q];
-        }
-    }
-    __syncthreads();
+    pre_segments(S, [&](uint32_t c, uint64_t b) { gp(lv.lmask)[(size_t)tile * NCLS + c] = b; });
 #pragma unroll
     for (int x = 0; x < PRE_EPT; ++x) {
-        if (is_local[x]) {
-            const uint32_t seg = rnd[x] * NCLS + cls[x];
-            const uint32_t slot = s_cnt[seg] + (mine[x] ? wrank[x] : atomicAdd(&s_fill[seg], 1u));
-            if (slot < (uint32_t)RT)
-                gp(lv.rec)[(size_t)tile * RT + slot] =
-                    (uint32_t)jj[x] | ((uint32_t)left[x] << 10) | ((uint32_t)right[x] << 20);
+        if (E.is_local[x]) {
+            uint32_t slot;
+            const uint32_t rec = pre_record(S, E, x, slot);
+            if (slot < (uint32_t)RT) gp(lv.rec)[(size_t)tile * RT + slot] = rec;
         }
     }
     for (uint32_t q = t; q < (uint32_t)LSTART_N; q += PRE_THREADS)
-        gp(lv.lstart)[(size_t)tile * LSTART_N + q] = q < (uint32_t)SEG_N ? (uint16_t)s_cnt[q] : 0;
+        gp(lv.lstart)[(size_t)tile * LSTART_N + q] = q < (uint32_t)SEG_N ? (uint16_t)S.cnt[q] : 0;
 
     // ---- the open entries' places in S_{k+1}
-    const uint32_t base = (uint32_t)lookback_block_resolve<OpSum, PRE_BLOCK>(lv.status, 1, tile, total, ctrl, s_lb);
+    const uint32_t base = (uint32_t)lookback_block_resolve<OpSum, PRE_BLOCK>(lv.status, 1, tile, total, ctrl, S.lb);
 #pragma unroll
     for (int x = 0; x < PRE_EPT; ++x) {
-        if (is_open[x]) {
-            if (rank[x] < (uint32_t)OPEN_CAP) gp(lv.opos)[(size_t)tile * OPEN_CAP + rank[x]] = (uint16_t)jj[x];
+        if (E.is_open[x]) {
+            if (rank[x] < (uint32_t)OPEN_CAP) gp(lv.opos)[(size_t)tile * OPEN_CAP + rank[x]] = (uint16_t)E.jj[x];
             if ((uint32_t)k < fd.K) {
                 auto &nx = fd.lv[k + 1];
                 const uint32_t o = base + rank[x];
                 if (o < nx.cap) {
-                    gp(nx.s_idx)[o] = k == 1 ? s + jj[x] : gp(lv.s_idx)[s + jj[x]];
-                    gp(nx.s_lvl)[o] = (uint8_t)lvl[x];
+                    gp(nx.s_idx)[o] = k == 1 ? s + E.jj[x] : gp(lv.s_idx)[s + E.jj[x]];
+                    gp(nx.s_lvl)[o] = (uint8_t)E.lvl[x];
                 }
             }
         }
@@ -379,8 +425,9 @@ __device__ inline void prelude_tile(const TileMap &m, uint32_t f, int k, uint32_
 constexpr int PRE_BLOCK1 = RT / PRE_EPT1;
 __global__ __launch_bounds__(PRE_BLOCK1) void k_prelude(TileMap m, int k)
 {
+    __shared__ PreScratch<PRE_EPT1> S;
     const uint32_t f = frame_of(m, blockIdx.x);
-    prelude_tile<false, PRE_EPT1>(m, f, k, tile_index(m, f));
+    prelude_tile<false, PRE_EPT1>(m, f, k, tile_index(m, f), S);
 }
 
 // The decoder's leaves and first-level schedule in one launch. A workgroup takes the RT leaves
@@ -395,6 +442,7 @@ __global__ __launch_bounds__(PRE_BLOCK1) void k_dec_prelude(TileMap m)
 {
     static_assert(PRE_EPT1 == 2, "two leaves per thread");
     __shared__ uint64_t s_code[RT + 2];
+    __shared__ PreScratch<PRE_EPT1> S;
     const uint32_t f = frame_of(m, blockIdx.x);
     const uint32_t tile = tile_index(m, f);
     const CAS FrameDesc &fd = *cp(m.fd[f]);  // (not written while the kernel runs)
@@ -445,7 +493,7 @@ __global__ __launch_bounds__(PRE_BLOCK1) void k_dec_prelude(TileMap m)
     if (t == 0) s_code[0] = code[2];
     if (t == 1) s_code[RT + 1] = code[2];
     __syncthreads();
-    prelude_tile<false, PRE_EPT1>(m, f, 1, tile, s_code);
+    prelude_tile<false, PRE_EPT1>(m, f, 1, tile, S, s_code);
 }
 
 hipError_t launch_dec_prelude(const TileMap &m, hipStream_t s)
@@ -507,7 +555,8 @@ static_assert(GSC_MAX_BATCH <= WAVE, "one wave counts the frames' items");
 // (phase flags) before they count its tiles; a workgroup without a tile at a level leaves the
 // group (the later levels are no larger). A workgroup that leaves releases its writes and adds
 // itself to the group's counter, which reaches Gp once every level's schedule is written.
-__device__ inline void up_prelude_group(const TileMap &m, int kmax, uint32_t Gp, uint32_t *s_fs, GAS uint32_t *pre_done)
+__device__ inline void up_prelude_group(const TileMap &m, int kmax, uint32_t Gp, uint32_t *s_fs, PreScratch<PRE_EPT_UP> &S,
+                                        GAS uint32_t *pre_done)
 {
     const CAS FrameDesc &fd0 = *cp(m.fd[0]);
     uint32_t *flags = fd0.lvl_flags;
@@ -517,7 +566,7 @@ __device__ inline void up_prelude_group(const TileMap &m, int kmax, uint32_t Gp,
         if (blockIdx.x >= items) break;
         for (uint32_t i = blockIdx.x; i < items; i += Gp) {
             const uint32_t f = item_frame(m, s_fs, i);
-            prelude_tile<true, PRE_EPT_UP>(m, f, k, i - s_fs[f]);
+            prelude_tile<true, PRE_EPT_UP>(m, f, k, i - s_fs[f], S);
             __syncthreads();
         }
         if (k == kmax) break;
@@ -1118,6 +1167,92 @@ __device__ inline bool up_schedule(const TileMap &m, uint32_t f, int k, uint32_t
     return load_schedule(fd, ctrl, k, tile, pass_chunks(fd.C4, k), ts, A.rec, A.ab, A.lst, A.opos, A.idx, A.lmask);
 }
 
+// The schedule of tile `tile` of S_k (k >= 2) built straight into this workgroup's LDS, for an item that
+// it then transforms itself: nothing of it is written to memory, released and read back. The open
+// entries come first: as soon as they are known, the workgroup of the tile's first channel slice
+// (p = 0) writes their places in S_{k+1} with device-coherent stores and counts the tile in *tiles_done,
+// so that S_{k+1}'s workgroups start while this one builds the rest (the other slices' workgroups
+// build the same schedule and publish nothing). Returns false if there is nothing to transform;
+// the tile is counted all the same.
+__device__ inline bool up_schedule_own(const TileMap &m, uint32_t f, int k, uint32_t tile, uint32_t p, PreScratch<1> &S,
+                                       const UpArrays &A, TileSched &ts, GAS uint32_t *tiles_done)
+{
+    const CAS FrameDesc &fd = *cp(m.fd[f]);  // (not written while the kernel runs)
+    Ctrl *ctrl = fd.ctrl;
+    const uint32_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / WAVE), lane = lane_id();
+    const uint32_t nk = seq_size<true>(fd, ctrl, k), s = tile * RT;
+    if (__builtin_amdgcn_readfirstlane(load_error(ctrl)) || !seq_active(nk, k) || s >= nk) {
+        if (p == 0) done_add(tiles_done, 1);
+        return false;
+    }
+    auto &lv = fd.lv[k];
+    const uint32_t e = min(nk, s + RT), mlen = e - s, cap = fd.n, CH4 = pass_chunks(fd.C4, k);
+    const uint32_t jl = s + min(t, mlen - 1), je = min(e, nk - 1);
+    const uint32_t l0 = ld_live(&lv.s_lvl[jl]), vi = ld_live(&lv.s_idx[jl]);
+    const uint32_t le = ld_live(&lv.s_lvl[je]), ve = ld_live(&lv.s_idx[je]), nv = cp(ctrl)->n_vox;
+    PreEntry<1> E;
+    E.jj[0] = (int)t;
+    E.lvl[0] = t < mlen ? l0 : 0u;
+    // voxel indices, clamped to the frame's capacity like every row index read from the workspace
+    if (t < mlen) A.idx[t] = min(vi, cap ? cap - 1 : 0u);
+    if (t == 0) {
+        A.idx[mlen] = min(e < nk ? ve : nv, cap);
+        S.lvl_e = e < nk ? le : LVL_NONE;
+    }
+    pre_lists(S, E, fd.J);
+    __syncthreads();
+    pre_partners(S, E, (int)mlen);
+    // ---- the open entries: the tile's set, its count published, their places in S_{k+1}
+    const uint64_t bal = __ballot(E.is_open[0]);
+    if (lane == 0) A.os.om[w] = bal;
+    __syncthreads();
+    const uint32_t c = lane < (uint32_t)NCHUNK ? (uint32_t)__popcll(A.os.om[lane]) : 0u, inc = wave_incl_scan(c);
+    const uint32_t total = read_lane(inc, NCHUNK - 1), rank = read_lane(inc - c, w) + (uint32_t)__popcll(bal & lanemask_lt());
+    if (p == 0) lookback_block_publish<OpSum>(lv.status, 1, tile, total);
+    const uint32_t base = (uint32_t)lookback_block_resolve<OpSum, RT>(lv.status, 1, tile, total, ctrl, S.lb);
+    if (E.is_open[0] && rank < (uint32_t)OPEN_CAP) A.opos[rank] = (uint16_t)t;
+    if (p == 0) {
+        if (E.is_open[0] && (uint32_t)k < fd.K) {
+            auto &nx = fd.lv[k + 1];
+            const uint32_t o = base + rank;
+            if (o < nx.cap) {
+                __hip_atomic_store(&nx.s_idx[o], A.idx[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&nx.s_lvl[o], (uint8_t)E.lvl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (t == 0) {
+            if (total > open_max((int)fd.J)) set_error(ctrl, GSC_ERR_INTERNAL);
+            if (e == nk) st_relaxed32(&ctrl->lvl_n[k + 1], base + total);
+        }
+        done_add(tiles_done, 1);
+    }
+    // ---- the merges
+    pre_rounds(S, E);
+    __syncthreads();
+    pre_segments(S, [&](uint32_t cl, uint64_t b) { A.lmask[cl] = b; });
+    if (E.is_local[0]) {
+        uint32_t slot;
+        const uint32_t rec = pre_record(S, E, 0, slot);
+        if (slot < (uint32_t)RT) {
+            A.rec[slot] = lds_rec(rec, CH4);
+            const uint32_t ij = A.idx[E.jj[0]], il = A.idx[E.left[0]], ir = A.idx[E.right[0]];
+            A.ab[slot] = rotation(ij - il, ir - ij, fp64_weights(fd));
+        }
+    }
+    for (uint32_t q = t; q < (uint32_t)LSTART_N; q += RT) A.lst[q] = q < (uint32_t)SEG_N ? (uint16_t)S.cnt[q] : 0;
+    ts.tile = tile;
+    ts.s = s;
+    ts.e = e;
+    ts.nk = nk;
+    ts.obase = base;
+    ts.ocnt = min(total, (uint32_t)OPEN_CAP);
+    ts.nrec = S.cnt[SEG_N - 1];
+    ts.mlen = (int)mlen;
+    ts.final_level = nk <= (uint32_t)RT;
+    __syncthreads();
+    return true;
+}
+
 // The quantized (or float) coefficient rows at their voxel rows, of the entries j that `skip`
 // lets through. Open entries are skipped by every caller: an open entry's coefficient is written
 // by the level that completes its merge (so that every row is written exactly once in the
@@ -1209,12 +1344,12 @@ __device__ inline void fwd_up_item(const TileMap &m, uint32_t f, int k, uint32_t
 
 // ============================================================== upper levels, inverse
 // One item of S_k, k >= 2: coefficient rows from the entries' voxels; the tile is inverted with
-// its open entries' low-passes taken as zero, then the low-passes S_{k+1} handed down (once all
-// of S_{k+1}'s items are done) add their shares; the entries' synthesized values go to S_{k-1}'s
+// its open entries' low-passes taken as zero, then the low-passes S_{k+1} handed down (once
+// wait_above() has seen all of S_{k+1}'s items done) add their shares; the entries' synthesized values go to S_{k-1}'s
 // open-entry rows.
-template <bool VEC>
+template <bool VEC, class WaitAbove>
 __device__ inline void inv_up_item(const TileMap &m, uint32_t f, int k, uint32_t p0, const TileSched &ts,
-                                   float4 *s_y, const UpArrays &A, const GAS uint32_t *above_done, uint32_t above_items)
+                                   float4 *s_y, const UpArrays &A, WaitAbove wait_above)
 {
     const CAS FrameDesc &fd = *cp(m.fd[f]);  // (not written while the kernel runs)
     const uint32_t C = fd.C, C4 = fd.C4;
@@ -1225,7 +1360,6 @@ __device__ inline void inv_up_item(const TileMap &m, uint32_t f, int k, uint32_t
     const uint32_t c4 = cb + R.c4;
     const bool live = R.act && R.c4 < nch;
     const bool opens = !ts.final_level && ts.ocnt > 0;
-    os_set(A.os, A.opos[min(threadIdx.x, (uint32_t)OPEN_CAP - 1)], opens && threadIdx.x < ts.ocnt);
     // ---- coefficients of every entry (the high-pass stored at it)
     if (live) {
         if (fd.mode == MODE_DECODE) {
@@ -1259,7 +1393,7 @@ __device__ inline void inv_up_item(const TileMap &m, uint32_t f, int k, uint32_t
     __syncthreads();
     // ---- the open entries' low-passes, handed down by S_{k+1}
     if (opens) {
-        done_wait(above_done, above_items, fd.ctrl);
+        wait_above();
         const GAS float *src = gp(fd.lv[k].vbuf);
         const bool fp64 = fp64_weights(fd);
         for (uint32_t ob = 0; ob < ts.ocnt; ob += LCAP) {
@@ -1444,6 +1578,7 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     __shared__ uint32_t s_ucnt[MAXK + 2];
     __shared__ uint32_t s_fs[GSC_MAX_BATCH + 1];
     __shared__ uint32_t s_tk[1];
+    __shared__ PreScratch<PRE_EPT_UP> s_pre;
     const uint16_t *s_lst = reinterpret_cast<const uint16_t *>(s_lstw);
     const uint16_t *s_opos = reinterpret_cast<const uint16_t *>(s_oposw);
 
@@ -1452,7 +1587,7 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     uint32_t Gp = 0;
     if (kmax >= 2) {
         Gp = min(level_items(m, 2, 1, s_fs), gridDim.x);
-        if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, ctr_word(m, PRE_DONE));
+        if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, s_pre, ctr_word(m, PRE_DONE));
     }
     Frame1 fc;
     fc.f = ~0u;
@@ -1633,11 +1768,17 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
 
 // ============================================================ upper levels, inverse (launch)
 // The inverse of the upper levels kmax .. 2 in one persistent launch (all workgroups resident),
-// before the first level's: with `prelude`, the first Gp workgroups first build the upper
-// levels' schedules. The items run in descending level order (workgroup b takes items b, b + G,
-// ...); every item inverts its tile with the open entries' low-passes taken as zero and only
-// then waits for the level above, so the tiles of all levels are inverted side by side and only
-// the shares of the low-passes (add_open_share) follow the levels' order.
+// before the first level's. Every item inverts its tile with the open entries' low-passes taken
+// as zero and only then waits for the level above, so the tiles of all levels are inverted side by
+// side and only the shares of the low-passes (add_open_share) follow the levels' order.
+// With `prelude` (a decoder or the transform alone: no schedule exists yet) each item has a workgroup
+// of its own that also builds the tile's schedule (up_schedule_own): what is exposed is then, per
+// level, the time from its entries to its open entries, and the shares on the way back. Where the
+// items could outnumber the workgroups, the first Gp workgroups build all schedules first and the
+// items run in descending level order (workgroup b takes items b, b + G, ...), as they do without
+// `prelude`, on the encoder's schedules.
+// A chain of dependent latencies bounds the launch: 1M voxels (41, 2 and 1 tiles of three levels) took
+// 80 us with all schedules first (released, and read back by every item), the decode 269 us; 252 us so.
 template <bool VEC>
 __global__ __launch_bounds__(RAHT_THREADS) void k_raht_inv_up(TileMap m, int kmax, int prelude)
 {
@@ -1653,23 +1794,57 @@ __global__ __launch_bounds__(RAHT_THREADS) void k_raht_inv_up(TileMap m, int kma
     __shared__ float4 s_L[LCAP * CH4_MAX];
     __shared__ uint32_t s_ucnt[MAXK + 2];
     __shared__ uint32_t s_fs[GSC_MAX_BATCH + 1];
+    __shared__ PreScratch<PRE_EPT_UP> s_pre;
     const uint32_t tid = threadIdx.x, G = gridDim.x;
     Ctrl *ctrl0 = cp(m.fd[0])->ctrl;
-    if (tid < NCHUNK) s_om[tid] = 0;
+    const uint32_t NP = channel_passes(cp(m.fd[0])->C4, 2);  // every frame of a launch has the same C
+    const UpArrays A{s_rec, s_ab, s_lst, s_opos, s_idx, s_lmask, OpenSet{s_om, s_opre}, s_L};
     if (prelude) {
-        const uint32_t Gp = min(level_items(m, 2, 1, s_fs), G);
-        if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, ctr_word(m, PRE_DONE));
+        // ---- one item per workgroup, with its schedule in LDS, when even the most items that the levels
+        // above S_2 can have (each of a frame's tiles leaves at most open_max entries open) fit the
+        // grid beside S_2's: frames of up to about 5M voxels, or batches of as many
+        const uint32_t om = open_max((int)cp(m.fd[0])->J);
+        uint32_t items = level_items(m, 2, NP, s_fs), need = items;
+        for (uint32_t k = 3, tiles = items / NP; k <= (uint32_t)kmax; ++k) {
+            tiles = (uint32_t)((uint64_t)tiles * om / RT) + m.F;
+            need += tiles * NP;
+        }
+        if (need <= G) {
+            GAS uint32_t *tiles_done = gp(cp(m.fd[0])->lvl_flags);  // [k]: tiles of S_k whose open entries are known
+            uint32_t g = blockIdx.x;
+            int k = 2;
+            while (g >= items) {  // level k's workgroups come after those of the levels below
+                g -= items;
+                if (k == kmax || items == 0) return;
+                done_wait(&tiles_done[k], items / NP, ctrl0);
+                items = level_items(m, ++k, NP, s_fs);
+            }
+            const uint32_t f = item_frame(m, s_fs, g), local = g - s_fs[f], tile = local / NP, p = local % NP;
+            TileSched ts;
+            if (up_schedule_own(m, f, k, tile, p, s_pre, A, ts, &tiles_done[k]))
+                inv_up_item<VEC>(m, f, k, p, ts, s_y, A, [&]() {
+                    done_wait(&tiles_done[k], items / NP, ctrl0);
+                    const uint32_t above = level_items(m, k + 1, NP, s_fs);
+                    done_wait(done_ctr(m, DONE_INV, k + 1), above, ctrl0);
+                });
+            done_add(done_ctr(m, DONE_INV, k), 1);
+            return;
+        }
+        const uint32_t Gp = min(items / NP, G);
+        if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, s_pre, ctr_word(m, PRE_DONE));
         done_wait(ctr_word(m, PRE_DONE), Gp, ctrl0);
     }
-    const uint32_t NP = channel_passes(cp(m.fd[0])->C4, 2);  // every frame of a launch has the same C
     const uint32_t U = up_totals(m, kmax, NP, s_ucnt);
-    const UpArrays A{s_rec, s_ab, s_lst, s_opos, s_idx, s_lmask, OpenSet{s_om, s_opre}, s_L};
+    if (tid < NCHUNK) s_om[tid] = 0;
     for (uint32_t g = blockIdx.x; g < U; g += G) {
         const UpItem u = up_item(m, kmax, true, NP, s_ucnt, g);
         __syncthreads();  // the previous item's LDS is no longer read
         TileSched ts;
-        const bool ok = up_schedule(m, u.f, u.k, u.tile, ts, A);
-        if (ok) inv_up_item<VEC>(m, u.f, u.k, u.p, ts, s_y, A, done_ctr(m, DONE_INV, u.k + 1), s_ucnt[u.k + 1]);
+        if (up_schedule(m, u.f, u.k, u.tile, ts, A)) {
+            os_set(A.os, A.opos[min(tid, (uint32_t)OPEN_CAP - 1)], !ts.final_level && tid < ts.ocnt);
+            inv_up_item<VEC>(m, u.f, u.k, u.p, ts, s_y, A,
+                             [&]() { done_wait(done_ctr(m, DONE_INV, u.k + 1), s_ucnt[u.k + 1], ctrl0); });
+        }
         done_add(done_ctr(m, DONE_INV, u.k), 1);
         if (tid < NCHUNK) s_om[tid] = 0;
     }
