@@ -470,8 +470,8 @@ typedef enum gsc_stage {
     GSC_STAGE_PRELUDE = 4,     /* the first-level RAHT schedule launch (encoder, transforms) */
     GSC_STAGE_RAHT_FWD1 = 5,   /* the forward RAHT launch: merge, every level, quantize      */
     GSC_STAGE_RAHT_FWD_TOP = 6,/* (unused: the upper levels run in the forward launch)       */
-    GSC_STAGE_RAHT_INV1 = 7,   /* first-level inverse RAHT (dequantize + transform + rows)   */
-    GSC_STAGE_RAHT_INV_TOP = 8,/* inverse RAHT of the upper tiling levels                    */
+    GSC_STAGE_RAHT_INV1 = 7,   /* the inverse RAHT launch: every level, dequantize, rows     */
+    GSC_STAGE_RAHT_INV_TOP = 8,/* (empty: the upper levels run in the inverse launch)        */
     GSC_STAGE_OCTREE_DEC = 9,  /* octree expansion, Morton decode, centres, level-1 schedule */
     GSC_STAGE_COUNT = 10
 } gsc_stage;

@@ -217,15 +217,6 @@ int max_K(const Frame *fr, int F)
     return K;
 }
 
-// Worst-case tiles of level 2 (the largest upper level), or of every upper level, over the frames.
-uint32_t upper_tiles(const Frame *fr, int F, bool every)
-{
-    uint64_t t = 0;
-    for (int f = 0; f < F; ++f)
-        for (uint32_t k = 2; k <= fr[f].L.K && (k == 2 || every); ++k) t += fr[f].L.tiles[k];
-    return (uint32_t)std::min<uint64_t>(t, 1u << 20);  // (far above any grid)
-}
-
 // The first level's schedule (the upper levels' schedules are built by the transform launches).
 gsc_status run_prelude(const Frame *fr, int F, hipStream_t s)
 {
@@ -253,15 +244,12 @@ gsc_status run_forward(const Frame *fr, int F, const RahtCfg &cfg, bool last, bo
 gsc_status run_inverse(const Frame *fr, int F, const RahtCfg &cfg, bool prelude, bool *ended, hipStream_t s)
 {
     const int K = max_K(fr, F);
-    if (K >= 2) {
-        StageScope sc(GSC_STAGE_RAHT_INV_TOP, s);
-        TileMap m = make_map(fr, F, [](const Frame &) { return 1u; });
-        GSC_LAUNCH(launch_raht_inv_up(m, K, upper_tiles(fr, F, prelude) * channel_slices_upper(cfg.C4), prelude, cfg, s));
-    }
+    if (K >= 2) StageScope top(GSC_STAGE_RAHT_INV_TOP, s);  // (an empty stage: the levels run in the launch below)
     TileMap m = make_map(fr, F, [&cfg](const Frame &x) { return raht_blocks(x.L.tiles[1], 1, cfg.C4); });
     if (m.start[F] == 0) return GSC_OK;
     StageScope sc(GSC_STAGE_RAHT_INV1, s);
-    GSC_LAUNCH(launch_raht_inv(m, true, cfg, s));  // (always a call's last launch)
+    // (always a call's last launch)
+    GSC_LAUNCH(launch_raht_inv(m, K, K < 2 ? UP_NONE : prelude ? UP_SCHEDULES : UP_STORED, true, cfg, s));
     *ended = true;
     return GSC_OK;
 }

@@ -384,18 +384,16 @@ struct RahtCfg {
     bool vec, pow2;
 };
 uint32_t raht_blocks(uint32_t tiles, int k, int C4);  // first-level items of a frame
-uint32_t channel_slices_upper(int C4);                // channel slices of an upper-level tile
 // The forward transform of all tiling levels, with the upper levels' schedules, in one persistent
-// launch; the first-level inverse (after launch_raht_inv_up). m maps the first-level items to
-// frames; kmax is the largest tiling level over the frames.
+// launch; the inverse of all tiling levels likewise. m maps the first-level items to frames; kmax is
+// the largest tiling level over the frames.
 // finish: the launch is the call's last and ends it (its last workgroup runs finish_frame)
 hipError_t launch_raht_fwd(const TileMap &m, int kmax, bool finish, const RahtCfg &cfg, hipStream_t s);
-hipError_t launch_raht_inv(const TileMap &m, bool finish, const RahtCfg &cfg, hipStream_t s);
-// The upper levels' inverse (2 .. kmax; only m.F and m.fd are used) in one persistent launch,
-// before launch_raht_inv; with `prelude`, the launch first builds the upper levels' schedules.
-// items_max: the worst-case items of the largest upper level over the launch's frames.
-hipError_t launch_raht_inv_up(const TileMap &m, int kmax, uint32_t items_max, bool prelude, const RahtCfg &cfg,
-                              hipStream_t s);
+// up: what the inverse launch does about the upper levels before the first one
+constexpr int UP_NONE = 0;       // nothing (every frame is one tile)
+constexpr int UP_SCHEDULES = 1;  // builds their schedules and inverts them
+constexpr int UP_STORED = 2;     // inverts them on the schedules a forward launch has stored
+hipError_t launch_raht_inv(const TileMap &m, int kmax, int up, bool finish, const RahtCfg &cfg, hipStream_t s);
 hipError_t launch_finish(const TileMap &m, hipStream_t s);
 // the differentiable layer's loss and padding (k_loss.hip)
 size_t rd_loss_workspace_bytes();

@@ -915,31 +915,38 @@ uint32_t raht_blocks(uint32_t tiles, int k, int C4)
 {
     return (tiles + 7) / 8 * 8 * channel_passes((uint32_t)C4, k);
 }
-uint32_t channel_slices_upper(int C4) { return channel_passes((uint32_t)C4, 2); }
 
 // ================================================= hand-over between tiling levels
 // Every tiling level of a direction runs in one persistent launch, so the open entries' rows
 // pass from one level to the next between workgroups of the same launch, possibly on different
-// XCDs. They are written and read with device-coherent 64-bit accesses, which bypass the XCDs'
+// XCDs. They are written and read with device-coherent accesses (the sc1 bit of a 16-byte buffer
+// access, as an agent-scope atomic of 4 or 8 bytes has it), which bypass the XCDs'
 // non-coherent L2 caches, so neither side needs a cache write-back or invalidation. A producer
 // waits until its stores have completed before it adds its items to its level's completion
-// counter; a consumer reads the rows only after it has seen the count it needs.
-__device__ inline void st_coh4(GAS float *p, const float4 &v)
-{
-    GAS uint64_t *q = reinterpret_cast<GAS uint64_t *>(p);
-    __hip_atomic_store(q, ((uint64_t)__float_as_uint(v.y) << 32) | __float_as_uint(v.x), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(q + 1, ((uint64_t)__float_as_uint(v.w) << 32) | __float_as_uint(v.z), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline float4 ld_coh4(const GAS float *p)
-{
-    const GAS uint64_t *q = reinterpret_cast<const GAS uint64_t *>(p);
-    const uint64_t a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return make_float4(__uint_as_float((uint32_t)a), __uint_as_float((uint32_t)(a >> 32)),
-                       __uint_as_float((uint32_t)b), __uint_as_float((uint32_t)(b >> 32)));
-}
+// counter; a consumer reads the rows only after it has seen the count it needs. (Two 8-byte atomics in
+// place of each access were twice the requests at the memory side: 1M decode 257 against 255 us, a batch
+// of eight frames 3178 against 3149.)
+typedef uint32_t coh_u4 __attribute__((ext_vector_type(4)));
+constexpr int COH_SC1 = 16;  // cache policy of a buffer access: the sc1 bit
+// Rows [r0, r0 + rows) of a hand-over buffer of C4 16-byte chunks a row (uniform).
+struct CohRows {
+    __amdgpu_buffer_rsrc_t r;
+    uint32_t C4;
+    __device__ CohRows(float *buf, size_t r0, uint32_t rows, uint32_t C4_)
+        : r(__builtin_amdgcn_make_buffer_rsrc(buf + r0 * C4_ * 4, 0, (int)(rows * C4_ * 16), 0x00027000)), C4(C4_)
+    {
+    }
+    __device__ void st(uint32_t row, uint32_t c4, const float4 &v) const
+    {
+        const coh_u4 u = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
+        __builtin_amdgcn_raw_buffer_store_b128(u, r, (int)((row * C4 + c4) * 16), 0, COH_SC1);
+    }
+    __device__ float4 ld(uint32_t row, uint32_t c4) const
+    {
+        const coh_u4 u = __builtin_amdgcn_raw_buffer_load_b128(r, (int)((row * C4 + c4) * 16), 0, COH_SC1);
+        return make_float4(__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w));
+    }
+};
 
 // Counter word w of a transform launch (DONE_FWD + k, TK_UPF, ...), in the workspace of the
 // launch's first frame; the completion counters count a level's finished items over all frames.
@@ -959,6 +966,27 @@ __device__ inline void done_add(GAS uint32_t *c, uint32_t v)
     __syncthreads();
     if (threadIdx.x == 0 && v) __hip_atomic_fetch_add(c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// The flag, in UP_FLAG_COPIES copies on lines of their own (after the words that the schedules use), that
+// S_2's inverse items are all done: the first-level workgroups wait on it rather than on the counter,
+// whose line the last items' additions would otherwise share with the loads of hundreds of waiters.
+constexpr uint32_t UP_FLAG_COPIES = 8, UP_FLAG_WORD = 512, UP_FLAG_STRIDE = 64;
+static_assert(UP_FLAG_WORD + UP_FLAG_COPIES * UP_FLAG_STRIDE <= UP_GRID_MAX, "inside the flag words");
+__device__ inline GAS uint32_t *up_flag(const TileMap &m, uint32_t copy)
+{
+    return gp(cp(m.fd[0])->lvl_flags) + UP_FLAG_WORD + copy * UP_FLAG_STRIDE;
+}
+// done_add of one of level k's inverse items; S_2's last of n2 sets the flag.
+__device__ inline void inv_item_done(const TileMap &m, int k, uint32_t n2)
+{
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t before = __hip_atomic_fetch_add(ctr_word(m, DONE_INV + (uint32_t)k), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (k == 2 && before + 1u == n2)
+            for (uint32_t c = 0; c < UP_FLAG_COPIES; ++c)
+                __hip_atomic_store(up_flag(m, c), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
 __device__ inline bool done_reached(const GAS uint32_t *c, uint32_t target)
 {
     return __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target;
@@ -967,6 +995,9 @@ __device__ inline bool done_reached(const GAS uint32_t *c, uint32_t target)
 // depends on comes earlier in the launch's order, each workgroup takes its items in order and
 // all workgroups are resident, so the earliest unfinished item can always proceed; a spin limit
 // turns a stall into GSC_ERR_INTERNAL.
+// SLEEP: 64-cycle units between two looks (many workgroups waiting for long look less often, so that
+// their loads do not crowd the counters' line).
+template <int SLEEP = 1>
 __device__ inline void done_wait(const GAS uint32_t *c, uint32_t target, Ctrl *ctrl)
 {
     if (threadIdx.x == 0) {
@@ -976,7 +1007,7 @@ __device__ inline void done_wait(const GAS uint32_t *c, uint32_t target, Ctrl *c
                 set_error(ctrl, GSC_ERR_INTERNAL);
                 break;
             }
-            __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_s_sleep(SLEEP);
         }
     }
     __syncthreads();
@@ -1321,8 +1352,8 @@ __device__ inline void fwd_up_item(const TileMap &m, uint32_t f, int k, uint32_t
     os_set(A.os, A.opos[min(threadIdx.x, (uint32_t)OPEN_CAP - 1)], threadIdx.x < ts.ocnt);
     // ---- the entries' values of this channel slice
     if (live) {
-        const GAS float *vsrc = gp(fd.lv[k - 1].vbuf);
-        load_slice(s_y, R, CH4, mlen, [&](uint32_t j) { return ld_coh4(vsrc + ((size_t)(ts.s + j) * C4 + c4) * 4); });
+        const CohRows vsrc(fd.lv[k - 1].vbuf, ts.s, mlen, C4);
+        load_slice(s_y, R, CH4, mlen, [&](uint32_t j) { return vsrc.ld(j, c4); });
     }
     __syncthreads();
     // ---- all local merges: within wave chunks, then across chunks (levels ascending)
@@ -1336,9 +1367,8 @@ __device__ inline void fwd_up_item(const TileMap &m, uint32_t f, int k, uint32_t
                            [&](uint32_t j) -> uint64_t { return A.idx[j]; },
                            [&](uint32_t j) { return s_y[j * CH4 + R.c4]; });
     if (!ts.final_level) {
-        GAS float *dst = gp(fd.lv[k].vbuf);
-        for (uint32_t o = R.row0; o < ts.ocnt; o += R.RPB)
-            st_coh4(dst + ((size_t)(ts.obase + o) * C4 + c4) * 4, s_y[A.opos[o] * CH4 + R.c4]);
+        const CohRows dst(fd.lv[k].vbuf, ts.obase, ts.ocnt, C4);
+        for (uint32_t o = R.row0; o < ts.ocnt; o += R.RPB) dst.st(o, c4, s_y[A.opos[o] * CH4 + R.c4]);
     }
 }
 
@@ -1394,13 +1424,13 @@ __device__ inline void inv_up_item(const TileMap &m, uint32_t f, int k, uint32_t
     // ---- the open entries' low-passes, handed down by S_{k+1}
     if (opens) {
         wait_above();
-        const GAS float *src = gp(fd.lv[k].vbuf);
+        const CohRows src(fd.lv[k].vbuf, ts.obase, ts.ocnt, C4);
         const bool fp64 = fp64_weights(fd);
         for (uint32_t ob = 0; ob < ts.ocnt; ob += LCAP) {
             const uint32_t nb = min(LCAP, ts.ocnt - ob);
             for (uint32_t q = threadIdx.x; q < nb * nch; q += RAHT_THREADS) {
                 const uint32_t o = q / nch, c = q - o * nch;
-                A.L[o * CH4 + c] = ld_coh4(src + ((size_t)(ts.obase + ob + o) * C4 + cb + c) * 4);
+                A.L[o * CH4 + c] = src.ld(ob + o, cb + c);
             }
             __syncthreads();
             add_open_share(s_y, R, CH4, live, mlen, A.os, A.opos, ts.ocnt, A.L, ob, nb, fp64,
@@ -1409,8 +1439,8 @@ __device__ inline void inv_up_item(const TileMap &m, uint32_t f, int k, uint32_t
         }
     }
     if (!live) return;
-    GAS float *dst = gp(fd.lv[k - 1].vbuf);
-    for (uint32_t j = R.row0; j < mlen; j += R.RPB) st_coh4(dst + ((size_t)(ts.s + j) * C4 + c4) * 4, s_y[j * CH4 + R.c4]);
+    const CohRows dst(fd.lv[k - 1].vbuf, ts.s, mlen, C4);
+    for (uint32_t j = R.row0; j < mlen; j += R.RPB) dst.st(j, c4, s_y[j * CH4 + R.c4]);
 }
 
 // ============================================================ first level, persistent forward
@@ -1578,7 +1608,6 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     __shared__ uint32_t s_ucnt[MAXK + 2];
     __shared__ uint32_t s_fs[GSC_MAX_BATCH + 1];
     __shared__ uint32_t s_tk[1];
-    __shared__ PreScratch<PRE_EPT_UP> s_pre;
     const uint16_t *s_lst = reinterpret_cast<const uint16_t *>(s_lstw);
     const uint16_t *s_opos = reinterpret_cast<const uint16_t *>(s_oposw);
 
@@ -1587,7 +1616,7 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     uint32_t Gp = 0;
     if (kmax >= 2) {
         Gp = min(level_items(m, 2, 1, s_fs), gridDim.x);
-        if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, s_pre, ctr_word(m, PRE_DONE));
+        if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, *reinterpret_cast<PreScratch<PRE_EPT_UP> *>(s_y), ctr_word(m, PRE_DONE));
     }
     Frame1 fc;
     fc.f = ~0u;
@@ -1726,10 +1755,8 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
                                        [&](uint32_t j) -> uint64_t { return s + j; },
                                        [&](uint32_t j) { return s_y[j * CH4 + R.c4]; });
                 if (!it0.final_level) {
-                    GAS float *dst = gp(d->lv[1].vbuf);
-                    const uint32_t C4 = d->C4;
-                    for (uint32_t o = R.row0; o < ocnt; o += R.RPB)
-                        st_coh4(dst + ((size_t)(obase + o) * C4 + c4) * 4, s_y[s_opos[o] * CH4 + R.c4]);
+                    const CohRows dst(d->lv[1].vbuf, obase, ocnt, d->C4);
+                    for (uint32_t o = R.row0; o < ocnt; o += R.RPB) dst.st(o, c4, s_y[s_opos[o] * CH4 + R.c4]);
                 }
             }
         }
@@ -1766,76 +1793,81 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     if (finish) finish_if_last(m, FIN_FWD, s_y);
 }
 
-// ============================================================ upper levels, inverse (launch)
-// The inverse of the upper levels kmax .. 2 in one persistent launch (all workgroups resident),
-// before the first level's. Every item inverts its tile with the open entries' low-passes taken
+// ================================================================ upper levels, inverse (phase)
+// The inverse of the upper levels kmax .. 2, by the workgroups of the inverse launch (all resident)
+// before their first-level items. Every item inverts its tile with the open entries' low-passes taken
 // as zero and only then waits for the level above, so the tiles of all levels are inverted side by
 // side and only the shares of the low-passes (add_open_share) follow the levels' order.
-// With `prelude` (a decoder or the transform alone: no schedule exists yet) each item has a workgroup
+// With UP_SCHEDULES (a decoder or the transform alone: no schedule exists yet) each item has a workgroup
 // of its own that also builds the tile's schedule (up_schedule_own): what is exposed is then, per
 // level, the time from its entries to its open entries, and the shares on the way back. Where the
 // items could outnumber the workgroups, the first Gp workgroups build all schedules first and the
-// items run in descending level order (workgroup b takes items b, b + G, ...), as they do without
-// `prelude`, on the encoder's schedules.
-// A chain of dependent latencies bounds the launch: 1M voxels (41, 2 and 1 tiles of three levels) took
-// 80 us with all schedules first (released, and read back by every item), the decode 269 us; 252 us so.
+// items run in descending level order (workgroup b takes items b, b + G, ...), as they do with
+// UP_STORED, on the encoder's schedules.
+// Returns the workgroups that could have had an upper item (first-level items are dealt from the next
+// one on). S: scratch that may lie in s_y.
+// A chain of dependent latencies bounds the phase: for 1M voxels (41, 2 and 1 tiles of three levels) a
+// launch of its own took 80 us with all schedules first (released, and read back by every item), 1M
+// decode 269 us, and 252 us with each item's own; as a phase of the inverse launch 249 (100K: 96 against
+// 91 us, the 500K training step 829 against 810).
 template <bool VEC>
-__global__ __launch_bounds__(RAHT_THREADS) void k_raht_inv_up(TileMap m, int kmax, int prelude)
+__device__ inline uint32_t inv_upper(const TileMap &m, int kmax, bool build, float4 *s_y, const UpArrays &A,
+                                     PreScratch<PRE_EPT_UP> &S, uint32_t *s_ucnt, uint32_t *s_fs, uint32_t n2)
 {
-    extern __shared__ float4 s_y[];
-    __shared__ uint32_t s_rec[RT];
-    __shared__ float2 s_ab[RT];
-    __shared__ uint16_t s_lst[LSTART_N];
-    __shared__ uint16_t s_opos[OPEN_CAP];
-    __shared__ uint32_t s_idx[RT + 1];
-    __shared__ unsigned long long s_lmask[NCLS];
-    __shared__ unsigned long long s_om[NCHUNK];
-    __shared__ uint32_t s_opre[NCHUNK + 1];
-    __shared__ float4 s_L[LCAP * CH4_MAX];
-    __shared__ uint32_t s_ucnt[MAXK + 2];
-    __shared__ uint32_t s_fs[GSC_MAX_BATCH + 1];
-    __shared__ PreScratch<PRE_EPT_UP> s_pre;
     const uint32_t tid = threadIdx.x, G = gridDim.x;
     Ctrl *ctrl0 = cp(m.fd[0])->ctrl;
     const uint32_t NP = channel_passes(cp(m.fd[0])->C4, 2);  // every frame of a launch has the same C
-    const UpArrays A{s_rec, s_ab, s_lst, s_opos, s_idx, s_lmask, OpenSet{s_om, s_opre}, s_L};
-    if (prelude) {
-        // ---- one item per workgroup, with its schedule in LDS, when even the most items that the levels
-        // above S_2 can have (each of a frame's tiles leaves at most open_max entries open) fit the
-        // grid beside S_2's: frames of up to about 5M voxels, or batches of as many
+    if (build) {
+        // a workgroup per item, or per tile (its channel slices one after the other), when even the most
+        // tiles that the levels above S_2 can have (each of a frame's tiles leaves at most open_max
+        // entries open) fit the grid beside S_2's: an item each up to about 5M voxels, a tile each up
+        // to about 10M, over the frames of the launch
         const uint32_t om = open_max((int)cp(m.fd[0])->J);
-        uint32_t items = level_items(m, 2, NP, s_fs), need = items;
-        for (uint32_t k = 3, tiles = items / NP; k <= (uint32_t)kmax; ++k) {
+        uint32_t need = n2 / NP;  // tiles
+        for (uint32_t k = 3, tiles = need; k <= (uint32_t)kmax; ++k) {
             tiles = (uint32_t)((uint64_t)tiles * om / RT) + m.F;
-            need += tiles * NP;
+            need += tiles;
         }
+        const uint32_t wpt = need * NP <= G ? NP : 1u;  // workgroups per tile
+        need *= wpt;
         if (need <= G) {
-            GAS uint32_t *tiles_done = gp(cp(m.fd[0])->lvl_flags);  // [k]: tiles of S_k whose open entries are known
+            if (blockIdx.x >= need) return need;
+            // [k]: tiles of S_k whose open entries are known; [UP_SLICE_WORD + 4 k + p]: tiles of S_k whose
+            // slice p is inverted (a tile waits for its own slice above only)
+            constexpr uint32_t UP_SLICE_WORD = 32;
+            static_assert(UP_SLICE_WORD > MAXK && UP_SLICE_WORD + 4 * (MAXK + 1) <= UP_FLAG_WORD, "below the flag copies");
+            static_assert((GSC_MAX_CHANNELS / 4 + CH4_MAX - 1) / CH4_MAX <= 4, "four counters a level");
+            GAS uint32_t *tiles_done = gp(cp(m.fd[0])->lvl_flags);
             uint32_t g = blockIdx.x;
             int k = 2;
-            while (g >= items) {  // level k's workgroups come after those of the levels below
-                g -= items;
-                if (k == kmax || items == 0) return;
-                done_wait(&tiles_done[k], items / NP, ctrl0);
-                items = level_items(m, ++k, NP, s_fs);
+            uint32_t wgs = level_items(m, 2, wpt, s_fs);
+            while (g >= wgs) {  // level k's workgroups come after those of the levels below
+                g -= wgs;
+                if (k == kmax || wgs == 0) return need;
+                done_wait(&tiles_done[k], wgs / wpt, ctrl0);
+                wgs = level_items(m, ++k, wpt, s_fs);
             }
-            const uint32_t f = item_frame(m, s_fs, g), local = g - s_fs[f], tile = local / NP, p = local % NP;
+            const uint32_t f = item_frame(m, s_fs, g), local = g - s_fs[f], tile = local / wpt, p0 = local % wpt;
             TileSched ts;
-            if (up_schedule_own(m, f, k, tile, p, s_pre, A, ts, &tiles_done[k]))
-                inv_up_item<VEC>(m, f, k, p, ts, s_y, A, [&]() {
-                    done_wait(&tiles_done[k], items / NP, ctrl0);
-                    const uint32_t above = level_items(m, k + 1, NP, s_fs);
-                    done_wait(done_ctr(m, DONE_INV, k + 1), above, ctrl0);
-                });
-            done_add(done_ctr(m, DONE_INV, k), 1);
-            return;
+            const bool ok = up_schedule_own(m, f, k, tile, p0, S, A, ts, &tiles_done[k]);
+            for (uint32_t p = p0; p < NP; p += wpt) {
+                if (ok)
+                    inv_up_item<VEC>(m, f, k, p, ts, s_y, A, [&]() {
+                        done_wait(&tiles_done[k], wgs / wpt, ctrl0);
+                        const uint32_t above = level_items(m, k + 1, 1, s_fs);
+                        done_wait(&tiles_done[UP_SLICE_WORD + 4 * (k + 1) + p], above, ctrl0);
+                    });
+                if (k == 2) inv_item_done(m, 2, n2);  // (a barrier: the slice's LDS is free)
+                else done_add(&tiles_done[UP_SLICE_WORD + 4 * k + p], 1);
+            }
+            return need;
         }
-        const uint32_t Gp = min(items / NP, G);
-        if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, s_pre, ctr_word(m, PRE_DONE));
+        const uint32_t Gp = min(n2 / NP, min(G, UP_FLAG_WORD));
+        if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, S, ctr_word(m, PRE_DONE));
         done_wait(ctr_word(m, PRE_DONE), Gp, ctrl0);
     }
     const uint32_t U = up_totals(m, kmax, NP, s_ucnt);
-    if (tid < NCHUNK) s_om[tid] = 0;
+    if (tid < NCHUNK) A.os.om[tid] = 0;
     for (uint32_t g = blockIdx.x; g < U; g += G) {
         const UpItem u = up_item(m, kmax, true, NP, s_ucnt, g);
         __syncthreads();  // the previous item's LDS is no longer read
@@ -1845,34 +1877,52 @@ __global__ __launch_bounds__(RAHT_THREADS) void k_raht_inv_up(TileMap m, int kma
             inv_up_item<VEC>(m, u.f, u.k, u.p, ts, s_y, A,
                              [&]() { done_wait(done_ctr(m, DONE_INV, u.k + 1), s_ucnt[u.k + 1], ctrl0); });
         }
-        done_add(done_ctr(m, DONE_INV, u.k), 1);
-        if (tid < NCHUNK) s_om[tid] = 0;
+        inv_item_done(m, u.k, n2);
+        if (tid < NCHUNK) A.os.om[tid] = 0;
     }
+    return 0;
 }
 
 // ============================================================ first level, persistent inverse
-// The same persistent, prefetching scheme for the first level of the inverse (after the upper
-// levels' launch): while one item's merges are undone and its rows stored, the next item's
+// The same persistent, prefetching scheme for the first level of the inverse, after the upper levels'
+// phase of the same launch: while one item's merges are undone and its rows stored, the next item's
 // schedule, coefficient rows (read as raw 32-bit words, dequantized when they are committed to
-// LDS) and the low-passes of its open entries (from S_2) are in flight in registers.
+// LDS) and the low-passes of its open entries (from S_2) are in flight in registers. Before its first
+// item's merges a workgroup waits until S_2's items are done; that item's rows and the next one's
+// are loaded meanwhile, so the upper levels' chain hides the start of the first level.
 // open entries per thread: ceil(OPEN_CAP / RPB) for the narrowest rows per step
 constexpr int NO1 = (OPEN_CAP + RT / (int)CH4_MAX1 - 1) / (RT / (int)CH4_MAX1);
 
 template <bool VEC>
-__global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PERSIST_PER_CU * RAHT_THREADS / WAVE / 4))) void k_raht_inv(TileMap m, int finish)
+__global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PERSIST_PER_CU * RAHT_THREADS / WAVE / 4))) void k_raht_inv(TileMap m, int kmax, int up, int finish)
 {
     extern __shared__ float4 s_y[];
     __shared__ uint32_t s_rec[RT];
     __shared__ float2 s_ab[RT];
     __shared__ uint32_t s_lstw[LSTART_N / 2 + 1];   // u16 segment starts, in pairs; + sink
     __shared__ uint32_t s_oposw[OPEN_CAP / 2 + 1];  // u16 open positions, in pairs; + sink
-    __shared__ uint32_t s_m0[RT + 2];               // (written by the shared commit, unused)
+    __shared__ uint32_t s_m0[RT + 2];               // (written by the shared commit, unused; upper items: voxel indices)
     __shared__ float s_st[GSC_MAX_CHANNELS];        // dequantization steps of the frame s_stf
     __shared__ unsigned long long s_lmask[NCLS + 1];  // + sink
+    __shared__ unsigned long long s_om[NCHUNK];
+    __shared__ uint32_t s_opre[NCHUNK + 1];
+    __shared__ float4 s_L[LCAP * CH4_MAX];
+    __shared__ uint32_t s_ucnt[MAXK + 2];
+    __shared__ uint32_t s_fs[GSC_MAX_BATCH + 1];
     const uint16_t *s_lst = reinterpret_cast<const uint16_t *>(s_lstw);
     const uint16_t *s_opos = reinterpret_cast<const uint16_t *>(s_oposw);
 
     const uint32_t tid = threadIdx.x, G = gridDim.x, items = m.start[m.F];
+    // ---- the upper levels
+    uint32_t lead = 0, n2 = 0;
+    if (up != UP_NONE) {
+        const UpArrays A{s_rec, s_ab, reinterpret_cast<uint16_t *>(s_lstw), reinterpret_cast<uint16_t *>(s_oposw),
+                         s_m0, s_lmask, OpenSet{s_om, s_opre}, s_L};
+        n2 = level_items(m, 2, channel_passes(cp(m.fd[0])->C4, 2), s_fs);
+        lead = inv_upper<VEC>(m, kmax, up == UP_SCHEDULES, s_y, A, *reinterpret_cast<PreScratch<PRE_EPT_UP> *>(s_y), s_ucnt,
+                              s_fs, n2) % G;
+        __syncthreads();  // the upper levels' LDS is no longer read
+    }
     Frame1 fc;
     fc.f = ~0u;
     fc.nk = 0;
@@ -1889,33 +1939,39 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
         }
         return gp(d->mode == MODE_ENCODE ? d->coef_f32 : d->attr);
     };
-    auto prefetch = [&](const Item1 &it, Sched1 &S, float4 (&D)[NR1], float4 (&O)[NO1]) {
+    // an item's schedule and coefficient rows; the low-passes of its open entries (o entries from ob)
+    auto prefetch = [&](const Item1 &it, Sched1 &S, float4 (&D)[NR1]) {
         CFrame *d = cp(m.fd[it.f]);
         uint32_t CH4, nch;
         slice(it, CH4, nch);
         const Roles R(CH4);
         load_sched1(d, it, S);
-        if (R.act && R.c4 < nch) {
-            const uint32_t c4 = it.p * CH4 + R.c4;
-            load_rows1<VEC>(coef_rows(d), d->C, R, c4, it.mlen, false, nullptr, it.s, D);
-            if (!it.final_level && S.ocnt > 0) {
-                const GAS float *src = gp(d->lv[1].vbuf);
+        if (R.act && R.c4 < nch)
+            load_rows1<VEC>(coef_rows(d), d->C, R, it.p * CH4 + R.c4, it.mlen, false, nullptr, it.s, D);
+    };
+    auto low_passes = [&](const Item1 &it, uint32_t ob, uint32_t no, float4 (&O)[NO1]) {
+        CFrame *d = cp(m.fd[it.f]);
+        uint32_t CH4, nch;
+        slice(it, CH4, nch);
+        const Roles R(CH4);
+        if (R.act && R.c4 < nch && !it.final_level && no > 0) {
+            const CohRows src(d->lv[1].vbuf, ob, no, d->C4);
 #pragma unroll
-                for (int u = 0; u < NO1; ++u) {
-                    const uint32_t o = min(R.row0 + (uint32_t)u * R.RPB, S.ocnt - 1);
-                    O[u] = gload4(src + ((size_t)(S.obase + o) * d->C4 + c4) * 4);
-                }
-            }
+            for (int u = 0; u < NO1; ++u) O[u] = src.ld(min(R.row0 + (uint32_t)u * R.RPB, no - 1), it.p * CH4 + R.c4);
         }
     };
-    Item1 it0 = item1(m, blockIdx.x, fc);
-    Item1 it1 = item1(m, blockIdx.x + G, fc);
+    // first-level item i goes to workgroup (lead + i) % G: the upper items' workgroups come last in the
+    // round-robin, so they take one item fewer when the items do not fill the last round
+    const uint32_t b1 = blockIdx.x >= lead ? blockIdx.x - lead : blockIdx.x + G - lead;
+    Item1 it0 = item1(m, b1, fc);
+    Item1 it1 = item1(m, b1 + G, fc);
     Sched1 S;
     float4 D[NR1], O[NO1];
     uint32_t stf = ~0u;  // frame whose steps are in s_st
-    if (it0.ok) prefetch(it0, S, D, O);
+    if (it0.ok) prefetch(it0, S, D);
 
-    for (uint32_t i = blockIdx.x; i < items; i += G) {
+    bool first = true;  // (the workgroup's first item: the low-passes are still to be loaded)
+    for (uint32_t i = b1; i < items; i += G, first = false) {
         CFrame *d = cp(m.fd[it0.f]);
         const bool decode = d->mode == MODE_DECODE;
         uint32_t CH4, nch;
@@ -1924,7 +1980,7 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
         const uint32_t c4 = it0.p * CH4 + R.c4;
         const bool live = it0.ok && R.act && R.c4 < nch;
         const uint32_t C = d->C;
-        const uint32_t ocnt = S.ocnt;
+        const uint32_t obase = S.obase, ocnt = S.ocnt;
         const bool has_open = it0.ok && !it0.final_level && ocnt > 0;
         if (decode && it0.f != stf) {  // the frame's dequantization steps (once per frame)
             stf = it0.f;
@@ -1954,8 +2010,9 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
             }
         }
         __syncthreads();
-        // ---- open entries take the low-pass handed down by S_2 (also branch-free)
-        {
+        // ---- open entries take the low-pass handed down by S_2 (also branch-free); the next item's
+        // loads, issued after them, or (first item) before the wait for S_2's items
+        auto open_rows = [&]() {
             const uint32_t sink = RT * CH4;
 #pragma unroll
             for (int u = 0; u < NO1; ++u) {
@@ -1963,9 +2020,17 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
                 const bool w = live && has_open && o < ocnt;
                 s_y[w ? s_opos[min(o, (uint32_t)OPEN_CAP - 1)] * CH4 + R.c4 : sink] = O[u];
             }
+        };
+        if (first) {
+            if (it1.ok) prefetch(it1, S, D);
+            if (n2 > 0) done_wait<8>(up_flag(m, blockIdx.x % UP_FLAG_COPIES), 1, cp(m.fd[0])->ctrl);
+            if (it0.ok) low_passes(it0, obase, ocnt, O);
+            open_rows();
+        } else {
+            open_rows();
+            if (it1.ok) prefetch(it1, S, D);
         }
-        // ---- prefetch the next item (issued first), then the item after it
-        if (it1.ok) prefetch(it1, S, D, O);
+        if (it1.ok) low_passes(it1, S.obase, S.ocnt, O);
         const Item1 it2 = item1(m, i + 2 * G, fc);
         // ---- the current item: all local merges undone, across chunks, then within chunks
         if (it0.ok) {
@@ -2013,7 +2078,8 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
 size_t raht_lds_bytes(int C4)
 {
     const uint32_t a = pass_chunks((uint32_t)C4, 1), b = pass_chunks((uint32_t)C4, 2);
-    return ((size_t)RT * (a > b ? a : b) + 1) * sizeof(float4);
+    const size_t rows = ((size_t)RT * (a > b ? a : b) + 1) * sizeof(float4);
+    return rows > sizeof(PreScratch<PRE_EPT_UP>) ? rows : sizeof(PreScratch<PRE_EPT_UP>);  // (schedules are built in it)
 }
 
 // Launch limits of the current device, queried once per (device, kernel, dynamic LDS) and kept
@@ -2062,22 +2128,11 @@ static uint32_t blocks_per_cu(const void *kern, int threads, size_t lds)
     return (uint32_t)nb;
 }
 
-// Workgroups of a persistent launch whose workgroups wait on one another: every one of them must
-// be resident at once, so at most what the occupancy calculator allows per CU (and `per_cu_max`)
-// times the CUs, a multiple of 8 (the XCDs), and at most `want`. 0 if none fits.
-static uint32_t resident_grid(const void *kern, size_t lds, uint32_t per_cu_max, uint32_t want)
-{
-    uint32_t per_cu = blocks_per_cu(kern, RAHT_THREADS, lds);
-    if (per_cu > per_cu_max) per_cu = per_cu_max;
-    const uint32_t g = per_cu * cu_count() / 8 * 8;
-    return want < g ? (want + 7) / 8 * 8 : g;
-}
-
 // Workgroups of a persistent first-level launch over `items` items: resident at once (as above),
 // a multiple of 8 NP (an item and its partner slice, items i and i + 8 of a group of 8 NP, run
-// at the same time on one XCD), and as few as give every workgroup the same number of items, up
-// to one. 0 if none fits.
-static uint32_t persist_grid(uint32_t items, int C4, const void *kern, size_t lds)
+// at the same time on one XCD), and (`even`) as few as give every workgroup the same number of items,
+// up to one. 0 if none fits.
+static uint32_t persist_grid(uint32_t items, int C4, bool even, const void *kern, size_t lds)
 {
     uint32_t per_cu = blocks_per_cu(kern, RAHT_THREADS, lds);
     if (per_cu > (uint32_t)PERSIST_PER_CU) per_cu = PERSIST_PER_CU;
@@ -2085,6 +2140,7 @@ static uint32_t persist_grid(uint32_t items, int C4, const void *kern, size_t ld
     const uint32_t gmax = per_cu * cu_count() / unit * unit;
     if (gmax == 0) return 0;
     if (items <= gmax) return items;
+    if (!even) return gmax;
     const uint32_t rounds = ceil_div(items, gmax);
     return ceil_div(ceil_div(items, rounds), unit) * unit;
 }
@@ -2096,7 +2152,7 @@ hipError_t launch_raht_fwd(const TileMap &m, int kmax, bool finish, const RahtCf
                                            : reinterpret_cast<const void *>(k_raht_fwd<true, false>))
                                : (cfg.pow2 ? reinterpret_cast<const void *>(k_raht_fwd<false, true>)
                                            : reinterpret_cast<const void *>(k_raht_fwd<false, false>));
-    const uint32_t g = persist_grid(m.start[m.F], cfg.C4, kern, lds);
+    const uint32_t g = persist_grid(m.start[m.F], cfg.C4, true, kern, lds);
     if (g == 0) return hipErrorInvalidConfiguration;
     const dim3 grid(g), block(RAHT_THREADS);
     const int fin = finish ? 1 : 0;
@@ -2107,32 +2163,19 @@ hipError_t launch_raht_fwd(const TileMap &m, int kmax, bool finish, const RahtCf
     return hipGetLastError();
 }
 
-hipError_t launch_raht_inv_up(const TileMap &m, int kmax, uint32_t items_max, bool prelude, const RahtCfg &cfg,
-                              hipStream_t s)
-{
-    const size_t lds = raht_lds_bytes(cfg.C4);
-    const void *kern = cfg.vec ? reinterpret_cast<const void *>(k_raht_inv_up<true>)
-                               : reinterpret_cast<const void *>(k_raht_inv_up<false>);
-    uint32_t g = resident_grid(kern, lds, 4, items_max > 0 ? items_max : 1u);
-    if (g > UP_GRID_MAX) g = UP_GRID_MAX;  // (one phase flag per workgroup)
-    if (g == 0) return hipErrorInvalidConfiguration;
-    const dim3 grid(g), block(RAHT_THREADS);
-    if (cfg.vec) hipLaunchKernelGGL((k_raht_inv_up<true>), grid, block, lds, s, m, kmax, prelude ? 1 : 0);
-    else hipLaunchKernelGGL((k_raht_inv_up<false>), grid, block, lds, s, m, kmax, prelude ? 1 : 0);
-    return hipGetLastError();
-}
-
-hipError_t launch_raht_inv(const TileMap &m, bool finish, const RahtCfg &cfg, hipStream_t s)
+hipError_t launch_raht_inv(const TileMap &m, int kmax, int up, bool finish, const RahtCfg &cfg, hipStream_t s)
 {
     const size_t lds = raht_lds_bytes(cfg.C4);
     const void *kern = cfg.vec ? reinterpret_cast<const void *>(k_raht_inv<true>)
                                : reinterpret_cast<const void *>(k_raht_inv<false>);
-    const uint32_t g = persist_grid(m.start[m.F], cfg.C4, kern, lds);
+    // with upper levels the grid is not evened out: their workgroups (the last in the round-robin) start
+    // their first-level items late and should be among those with one item fewer
+    const uint32_t g = persist_grid(m.start[m.F], cfg.C4, up == UP_NONE, kern, lds);
     if (g == 0) return hipErrorInvalidConfiguration;
     const dim3 grid(g), block(RAHT_THREADS);
     const int fin = finish ? 1 : 0;
-    if (cfg.vec) hipLaunchKernelGGL((k_raht_inv<true>), grid, block, lds, s, m, fin);
-    else hipLaunchKernelGGL((k_raht_inv<false>), grid, block, lds, s, m, fin);
+    if (cfg.vec) hipLaunchKernelGGL((k_raht_inv<true>), grid, block, lds, s, m, kmax, up, fin);
+    else hipLaunchKernelGGL((k_raht_inv<false>), grid, block, lds, s, m, kmax, up, fin);
     return hipGetLastError();
 }
 

@@ -223,3 +223,33 @@ def test_deterministic_bytes():
     b = gsc.encode_frame(tp, ta, p)
     torch.cuda.synchronize()
     assert a.to_bytes() == b.to_bytes()
+
+
+@pytest.mark.parametrize("nv,C", [
+    (500, 4),           # one tile: no upper level
+    (513, 64),          # two tiles, three channel slices above them
+    (400_000, 64),      # an upper item per workgroup
+    (6_200_000, 32),    # an upper tile per workgroup, its two slices one after the other
+    (14_000_000, 4),    # more upper tiles than workgroups: all schedules first
+])
+def test_adjoint_inverts_the_forward_over_the_upper_level_paths(nv, C):
+    """A = T^T (T A) on float rows, one size for each way the inverse launch deals its upper tiles. Each of
+    the at most 3J butterflies a value passes, in each direction, is off by a few FP32 roundings (about
+    1.5e-7): 1e-5 of the largest value bounds their sum."""
+    print(f"case nv={nv} C={C} transform and adjoint", flush=True)
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(nv)
+    J = 12
+    gaps = torch.randint(1, max(2, (1 << (3 * J)) // nv), (nv,), generator=g, device=dev)
+    codes = torch.cumsum(gaps, 0) - 1
+    assert int(codes[-1]) < 1 << (3 * J)
+    A = torch.randn(nv, C, generator=g, device=dev)
+    ws = gsc.Workspace(nv, J, C, dev)
+    Y, info = gsc.raht_forward(codes, A, J, ws=ws)
+    B, info2 = gsc.raht_adjoint(codes, Y, J, ws=ws)
+    torch.cuda.synchronize()
+    assert int(info[0]) == 0 and int(info2[0]) == 0
+    assert (B - A).abs().max().item() <= 1e-5 * A.abs().max().item()
+    # (orthonormal: the energy is kept)
+    e = (Y.double().square().sum() / A.double().square().sum()).item()
+    assert abs(e - 1.0) <= 1e-5
