@@ -344,7 +344,9 @@ gsc_status decode_frames(const Frame *fr, int F, int J, int C, hipStream_t s)
         StageScope sc(GSC_STAGE_OCTREE_DEC, s);
         {
             TileMap m = make_map(fr, F, [](const Frame &x) { return x.L.dec_tiles; });
-            GSC_LAUNCH(launch_dec_expand(m, s));
+            int64_t n = 0;
+            for (int f = 0; f < F; ++f) n += fr[f].a.n;
+            GSC_LAUNCH(launch_dec_expand(m, n <= DEC_WIDE_MAX, s));
         }
         {   // the leaves and the first level's schedule
             TileMap m = make_map(fr, F, [](const Frame &x) { return x.L.K >= 1 ? prelude_blocks(x.L.tiles[1]) : 0u; });

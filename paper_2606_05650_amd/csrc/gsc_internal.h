@@ -52,9 +52,12 @@ constexpr int OCC_THREADS = 1024;        // 16 waves: the per-depth look-backs r
 constexpr int OCC_VPT = 2;              // voxels per thread
 constexpr int OCC_TILE = OCC_THREADS * OCC_VPT;
 
-constexpr int DEC_THREADS = 256;
-constexpr int DEC_PPT = 16;             // occupancy bytes per thread
-constexpr int DEC_TILE = DEC_THREADS * DEC_PPT;
+constexpr int DEC_TILE = 4096;          // decoder: occupancy bytes per tile
+// Threads of a tile. A call's tiles (about 3.5 bytes per voxel) that number at most the compute units are
+// latency: 1024 threads with 4 bytes each (100K voxels: decode 91 -> 84 us); beyond, 256 threads with 16
+// bytes each keep more tiles resident (1M voxels: decode 246 us, with 1024 threads 258).
+constexpr int DEC_WIDE = 1024, DEC_NARROW = 256;
+constexpr int64_t DEC_WIDE_MAX = 1 << 18;  // voxels (the frames' capacities together)
 
 constexpr int RT = 512;                 // RAHT tile: entries (eight 64-entry wave chunks)
 constexpr int RAHT_THREADS = 512;       // one wave per chunk
@@ -373,7 +376,7 @@ hipError_t launch_voxelize(const TileMap &m, hipStream_t s);
 hipError_t launch_sort_pass(const TileMap &m, int pass, int variant, int bits, hipStream_t s);
 hipError_t launch_dedup(const TileMap &m, hipStream_t s);
 hipError_t launch_occupancy(const TileMap &m, hipStream_t s);
-hipError_t launch_dec_expand(const TileMap &m, hipStream_t s);
+hipError_t launch_dec_expand(const TileMap &m, bool wide, hipStream_t s);
 // the decoder's leaves and first-level schedule (one workgroup per first-level tile)
 hipError_t launch_dec_prelude(const TileMap &m, hipStream_t s);
 hipError_t launch_prelude(const TileMap &m, int k, hipStream_t s);

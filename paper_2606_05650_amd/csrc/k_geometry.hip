@@ -936,31 +936,18 @@ __device__ inline bool header_ok_wave(FD &fd, const CAS gsc_header *h)
     return true;
 }
 
-// The level of the q-th occupancy byte and that level's first byte: levels are contiguous, so a
-// scan over the (at most 21) level starts from the previous answer finds it.
-struct LevelCursor {
-    uint32_t d, start, end;  // level, its first byte, one past its last byte
-};
-__device__ inline void level_seek(const CAS gsc_header *h, uint32_t J, uint64_t q, LevelCursor &lc)
-{
-    while (lc.d + 1 < J && q >= lc.end) {
-        ++lc.d;
-        lc.start = lc.end;
-        lc.end += h->level_sizes[lc.d];
-    }
-}
-
 // One pass over all occupancy bytes: tile t holds bytes [t DEC_TILE, (t + 1) DEC_TILE) of the
 // stream's occupancy section, striped (byte s + r DEC_THREADS + tid), and finds each byte's
 // child slots with a decoupled look-back over the tiles' set-bit counts. Checks: no byte is 0,
 // and the first byte of every level is the parent of the first node of the next level (its prefix
 // equals Q(d + 1)), and the bytes hold exactly |L_1| + ... + |L_J| set bits.
-__global__ __launch_bounds__(DEC_THREADS) void k_dec_expand(TileMap m)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_dec_expand(TileMap m)
 {
-    constexpr int NW = DEC_THREADS / WAVE;
-    static_assert(DEC_PPT * NW <= WAVE, "one wave scans the (row, wave) child counts");
+    constexpr int NW = THREADS / WAVE, PPT = DEC_TILE / THREADS;  // occupancy bytes per thread
+    static_assert(PPT * NW <= WAVE, "one wave scans the (row, wave) child counts");
     __shared__ uint32_t s_cnt[WAVE + 1];
-    __shared__ LbScratch<DEC_THREADS / WAVE> s_lb;
+    __shared__ LbScratch<THREADS / WAVE> s_lb;
     const uint32_t f = frame_of(m, blockIdx.x);
     const CAS FrameDesc &fd = *cp(m.fd[f]);  // (not written while the kernel runs)
     Ctrl *ctrl = fd.ctrl;
@@ -972,19 +959,24 @@ __global__ __launch_bounds__(DEC_THREADS) void k_dec_expand(TileMap m)
     // byte that is used); a stream shorter than the header fails the check and loads nothing.
     const uint64_t s = (uint64_t)tile * DEC_TILE;
     const GAS uint8_t *occ = gp(fd.in_stream + GSC_HEADER_BYTES);
-    uint32_t raw[DEC_PPT];
+    uint32_t raw[PPT];
     if (fd.in_bytes > GSC_HEADER_BYTES) {
         const uint64_t qmax = fd.in_bytes - GSC_HEADER_BYTES - 1;
 #pragma unroll
-        for (int r = 0; r < DEC_PPT; ++r) raw[r] = occ[min(s + r * DEC_THREADS + tid, qmax)];
+        for (int r = 0; r < PPT; ++r) raw[r] = occ[min(s + r * THREADS + tid, qmax)];
     } else {
 #pragma unroll
-        for (int r = 0; r < DEC_PPT; ++r) raw[r] = 0u;
+        for (int r = 0; r < PPT; ++r) raw[r] = 0u;
     }
+    // the header's check, the levels' first bytes, and Q(d + 1), the nodes of levels 1..d, by wave 0
     __shared__ int s_ok;
+    __shared__ uint64_t s_start[WAVE], s_next[WAVE];
     if (w == 0) {
         const bool ok = header_ok_wave(fd, h);
         if (lane == 0) s_ok = ok ? 1 : 0;
+        const uint64_t size = ok && lane <= fd.J ? h->level_sizes[lane] : 0ull, incl = wave_incl_scan(size);
+        s_start[lane] = lane < fd.J ? incl - size : ~0ull;  // (past the last level: no byte reaches it)
+        s_next[lane] = incl - (ok ? h->level_sizes[0] : 0u);  // |L_1| + ... + |L_lane|
     }
     __syncthreads();
     if (!s_ok) {
@@ -998,18 +990,18 @@ __global__ __launch_bounds__(DEC_THREADS) void k_dec_expand(TileMap m)
         for (uint32_t d = 0; d <= J; ++d) ctrl->level_sizes[d] = h->level_sizes[d];
     }
     if (s >= B) return;
-    uint64_t total_nodes = 0;  // |L_1| + ... + |L_J|
-    for (uint32_t d = 1; d <= J; ++d) total_nodes += h->level_sizes[d];
-    uint32_t bytes[DEC_PPT], wex[DEC_PPT];
+    const uint64_t start = s_start[lane], next = s_next[lane];  // lane d: of level d
+    const uint64_t total_nodes = read_lane(next, J);            // |L_1| + ... + |L_J|
+    uint32_t bytes[PPT], wex[PPT];
     bool bad = false;
 #pragma unroll
-    for (int r = 0; r < DEC_PPT; ++r) {
-        const uint64_t q = s + r * DEC_THREADS + tid;
+    for (int r = 0; r < PPT; ++r) {
+        const uint64_t q = s + r * THREADS + tid;
         bytes[r] = q < B ? raw[r] : 0u;
     }
 #pragma unroll
-    for (int r = 0; r < DEC_PPT; ++r) {
-        const uint64_t q = s + r * DEC_THREADS + tid;
+    for (int r = 0; r < PPT; ++r) {
+        const uint64_t q = s + r * THREADS + tid;
         if (q < B && bytes[r] == 0) bad = true;
         const uint32_t c = (uint32_t)__popc(bytes[r]);
         const uint32_t inc = wave_incl_scan(c);
@@ -1018,40 +1010,49 @@ __global__ __launch_bounds__(DEC_THREADS) void k_dec_expand(TileMap m)
     }
     __syncthreads();
     if (w == 0) {  // (row, wave) totals in byte order -> exclusive offsets
-        const uint32_t c = lane < (uint32_t)(DEC_PPT * NW) ? s_cnt[lane] : 0u;
+        const uint32_t c = lane < (uint32_t)(PPT * NW) ? s_cnt[lane] : 0u;
         const uint32_t inc = wave_incl_scan(c);
-        if (lane < (uint32_t)(DEC_PPT * NW)) s_cnt[lane] = inc - c;
+        if (lane < (uint32_t)(PPT * NW)) s_cnt[lane] = inc - c;
         if (lane == WAVE - 1) s_cnt[WAVE] = inc;
     }
     __syncthreads();
     const uint32_t total = s_cnt[WAVE];
-    const uint64_t base = lookback_block<OpSum, DEC_THREADS>(fd.dec_status, 1, tile, total, ctrl, s_lb);
+    const uint64_t base = lookback_block<OpSum, THREADS>(fd.dec_status, 1, tile, total, ctrl, s_lb);
+    // each byte's parent index and first child, and the byte checks
+    uint32_t pidx[PPT], cfirst[PPT];  // (cfirst: from the tile's first child)
+#pragma unroll
+    for (int r = 0; r < PPT; ++r) {
+        // the level of the row's first byte (levels are contiguous: the last one that starts at or before
+        // it), by one ballot over the level starts; a row that runs into another level is sorted out
+        // per byte
+        const uint64_t q0 = s + r * THREADS + (uint32_t)__builtin_amdgcn_readfirstlane(w) * WAVE, q = q0 + lane;
+        const uint32_t d0 = max((uint32_t)__popcll(__ballot(start <= q0)), 1u) - 1u;
+        uint32_t d = d0;
+        uint64_t ls = read_lane(start, d0), qn = read_lane(next, d0);
+        if (d0 + 1 < J && read_lane(start, d0 + 1) <= q0 + (WAVE - 1)) {
+            while (d + 1 < J && q >= s_start[d + 1]) ++d;
+            ls = s_start[d];
+            qn = s_next[d];
+        }
+        pidx[r] = (uint32_t)(q - ls);
+        cfirst[r] = s_cnt[r * NW + w] + wex[r];
+        const uint64_t P = base + cfirst[r];  // set bits before byte q
+        if (q < B) {
+            if (q == ls && P != qn) bad = true;  // the level's first child: node Q(d + 1)
+            if (q + 1 == B && P + (uint64_t)__popc(bytes[r]) != total_nodes) bad = true;
+        }
+    }
+    // the bytes' children, set bits only (a wave takes as many steps as its fullest byte has children,
+    // mostly one or two below the top levels, instead of eight)
     GAS uint32_t *par = gp(fd.dec_par);
     GAS uint8_t *cbit = gp(fd.dec_cbit);
-    LevelCursor lc;
-    lc.d = 0;
-    lc.start = 0;
-    lc.end = h->level_sizes[0];
-    uint64_t q_level_next = 0;  // Q(d + 1) of the cursor's level d: nodes of levels 1..d
-    uint32_t qd = 0;
 #pragma unroll
-    for (int r = 0; r < DEC_PPT; ++r) {
-        const uint64_t q = s + r * DEC_THREADS + tid;
-        if (q >= B) break;
-        level_seek(h, J, q, lc);
-        while (qd < lc.d) q_level_next += h->level_sizes[++qd];
-        const uint64_t P = base + s_cnt[r * NW + w] + wex[r];  // set bits before byte q
-        if (q == lc.start && P != q_level_next) bad = true;    // the level's first child
-        if (q + 1 == B && P + (uint64_t)__popc(bytes[r]) != total_nodes) bad = true;
-        const uint32_t p = (uint32_t)(q - lc.start);            // the parent's index in its level
-        // the byte's children, set bits only (a wave takes as many steps as its fullest byte
-        // has children, mostly one or two below the top levels, instead of eight)
-        uint64_t c = P;
+    for (int r = 0; r < PPT; ++r) {
+        uint64_t c = base + cfirst[r];
         for (uint32_t bits = bytes[r]; bits; bits &= bits - 1u) {
-            const uint32_t i = (uint32_t)__ffs(bits) - 1u;
             if (c < total_nodes) {
-                par[c] = p;
-                cbit[c] = (uint8_t)i;
+                par[c] = pidx[r];
+                cbit[c] = (uint8_t)(__ffs(bits) - 1);
             } else {
                 bad = true;
             }
@@ -1061,9 +1062,10 @@ __global__ __launch_bounds__(DEC_THREADS) void k_dec_expand(TileMap m)
     if (bad) set_error(ctrl, GSC_ERR_CORRUPT_STREAM);
 }
 
-hipError_t launch_dec_expand(const TileMap &m, hipStream_t s)
+hipError_t launch_dec_expand(const TileMap &m, bool wide, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dec_expand, dim3(m.start[m.F]), dim3(DEC_THREADS), 0, s, m);
+    if (wide) hipLaunchKernelGGL(k_dec_expand<DEC_WIDE>, dim3(m.start[m.F]), dim3(DEC_WIDE), 0, s, m);
+    else hipLaunchKernelGGL(k_dec_expand<DEC_NARROW>, dim3(m.start[m.F]), dim3(DEC_NARROW), 0, s, m);
     return hipGetLastError();
 }
 
