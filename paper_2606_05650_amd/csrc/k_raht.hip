@@ -669,36 +669,39 @@ __device__ inline bool load_schedule(FD &fd, Ctrl *ctrl, int k, uint32_t tile,
 }
 
 
-// One butterfly on channels [4*c4, 4*c4+4) of merge record `rec` (in the form of lds_rec).
-__device__ inline void butterfly(float4 *s_y, uint32_t C4, uint32_t rec, float2 ab, uint32_t c4,
-                                 bool inverse)
+// One butterfly on channels [4*c4, 4*c4+4) of merge record `rec` (in the form of lds_rec); its results
+// are stored if `on`.
+__device__ inline void butterfly(float4 *s_y, uint32_t rec, float2 ab, uint32_t c4, bool inverse, bool on)
 {
     // rec: the LDS rows of the merge's left and right operands, already times the slice width
     // (see lds_rec)
     const uint32_t yl = rec & 0xFFFFu, yj = rec >> 16;
     const float4 y0 = s_y[yl + c4], y1 = s_y[yj + c4];
+    // (the roundings are spelled out: which product is fused must not hang on the code around)
     float4 lo, hi;
     if (!inverse) {
-        lo.x = ab.x * y0.x + ab.y * y1.x;
-        lo.y = ab.x * y0.y + ab.y * y1.y;
-        lo.z = ab.x * y0.z + ab.y * y1.z;
-        lo.w = ab.x * y0.w + ab.y * y1.w;
-        hi.x = -ab.y * y0.x + ab.x * y1.x;
-        hi.y = -ab.y * y0.y + ab.x * y1.y;
-        hi.z = -ab.y * y0.z + ab.x * y1.z;
-        hi.w = -ab.y * y0.w + ab.x * y1.w;
+        lo.x = fmaf(ab.x, y0.x, ab.y * y1.x);
+        lo.y = fmaf(ab.x, y0.y, ab.y * y1.y);
+        lo.z = fmaf(ab.x, y0.z, ab.y * y1.z);
+        lo.w = fmaf(ab.x, y0.w, ab.y * y1.w);
+        hi.x = fmaf(ab.x, y1.x, -(ab.y * y0.x));
+        hi.y = fmaf(ab.x, y1.y, -(ab.y * y0.y));
+        hi.z = fmaf(ab.x, y1.z, -(ab.y * y0.z));
+        hi.w = fmaf(ab.x, y1.w, -(ab.y * y0.w));
     } else {
-        lo.x = ab.x * y0.x - ab.y * y1.x;
-        lo.y = ab.x * y0.y - ab.y * y1.y;
-        lo.z = ab.x * y0.z - ab.y * y1.z;
-        lo.w = ab.x * y0.w - ab.y * y1.w;
-        hi.x = ab.y * y0.x + ab.x * y1.x;
-        hi.y = ab.y * y0.y + ab.x * y1.y;
-        hi.z = ab.y * y0.z + ab.x * y1.z;
-        hi.w = ab.y * y0.w + ab.x * y1.w;
+        lo.x = fmaf(ab.x, y0.x, -(ab.y * y1.x));
+        lo.y = fmaf(ab.x, y0.y, -(ab.y * y1.y));
+        lo.z = fmaf(ab.x, y0.z, -(ab.y * y1.z));
+        lo.w = fmaf(ab.x, y0.w, -(ab.y * y1.w));
+        hi.x = fmaf(ab.y, y0.x, ab.x * y1.x);
+        hi.y = fmaf(ab.y, y0.y, ab.x * y1.y);
+        hi.z = fmaf(ab.y, y0.z, ab.x * y1.z);
+        hi.w = fmaf(ab.y, y0.w, ab.x * y1.w);
     }
-    s_y[yl + c4] = lo;
-    s_y[yj + c4] = hi;
+    if (on) {
+        s_y[yl + c4] = lo;
+        s_y[yj + c4] = hi;
+    }
 }
 
 // Per-thread roles: in a workgroup step, thread t handles channel chunk t % C4 of row t / C4
@@ -731,10 +734,14 @@ __device__ inline uint32_t next_level(uint64_t mask, bool inverse)
 
 
 // Merges local to this wave's chunk, levels ascending (forward) or descending (inverse). Lane x
-// holds the record range of level x in registers (read out with readlane), and each level's first
-// record of a lane is loaded while the previous level runs, so a level costs one LDS round trip.
+// holds the record range of level x in registers (read out with readlane). A step takes up to MPW
+// merges of one level, and its records are loaded while the step before runs, so a step costs one
+// LDS round trip; a level of more merges is several such steps, not a loop inside the step (whose
+// records would be waited for: a chunk of the first level has about 8 levels and 11 steps). A lane
+// without a merge reads the step's last one and writes nothing: the reads stand outside any branch, so
+// the wait for them covers the records loaded before them and the next step begins without one.
 // The wave's own LDS accesses are performed in program order; the fence keeps the compiler from
-// moving one level's accesses across the next level's. Only channel chunks below nch are live.
+// moving one step's accesses across the next step's. Only channel chunks below nch are live.
 __device__ inline void wave_phase(float4 *s_y, const Roles &R, const uint32_t *s_rec,
                                   const float2 *s_ab, const uint16_t *s_lst, uint64_t mask,
                                   uint32_t nch, bool inverse, uint32_t cls)
@@ -743,32 +750,27 @@ __device__ inline void wave_phase(float4 *s_y, const Roles &R, const uint32_t *s
     const uint32_t lane = lane_id();
     const uint32_t lq0 = s_lst[lane * NCLS + cls], lq1 = s_lst[lane * NCLS + cls + 1];
     mask = uniform64(mask);  // one class per wave: one mask per wave
-    uint32_t x = mask ? next_level(mask, inverse) : 0u;
-    uint32_t q0 = __builtin_amdgcn_readlane(lq0, x), q1 = __builtin_amdgcn_readlane(lq1, x);
-    uint32_t rec = 0;
-    float2 ab = make_float2(0.f, 0.f);
-    if (live && q0 + R.wq < q1) {
-        rec = s_rec[q0 + R.wq];
-        ab = s_ab[q0 + R.wq];
-    }
-    while (mask) {
-        mask &= ~(1ull << x);
-        const uint32_t xn = mask ? next_level(mask, inverse) : 0u;
-        const uint32_t q0n = __builtin_amdgcn_readlane(lq0, xn), q1n = __builtin_amdgcn_readlane(lq1, xn);
-        uint32_t recn = 0;
-        float2 abn = make_float2(0.f, 0.f);
-        if (mask && live && q0n + R.wq < q1n) {
-            recn = s_rec[q0n + R.wq];
-            abn = s_ab[q0n + R.wq];
+    if (!mask) return;
+    uint32_t x = next_level(mask, inverse);
+    uint32_t q0 = read_lane(lq0, x), q1 = read_lane(lq1, x);  // (a level in the mask has a merge)
+    uint32_t at = min(min(q0 + R.wq, q1 - 1u), (uint32_t)RT - 1u);
+    uint32_t rec = s_rec[at];
+    float2 ab = s_ab[at];
+    for (;;) {
+        uint32_t q0n = q0 + R.MPW, q1n = q1;
+        if (q0n >= q1) {
+            mask &= ~(1ull << x);
+            x = mask ? next_level(mask, inverse) : x;
+            q0n = read_lane(lq0, x);
+            q1n = read_lane(lq1, x);
         }
-        if (live && q0 + R.wq < q1) {
-            butterfly(s_y, R.C4, rec, ab, R.wc4, inverse);
-            for (uint32_t q = q0 + R.wq + R.MPW; q < q1; q += R.MPW)
-                butterfly(s_y, R.C4, s_rec[q], s_ab[q], R.wc4, inverse);
-        }
+        at = min(min(q0n + R.wq, q1n - 1u), (uint32_t)RT - 1u);
+        const uint32_t recn = s_rec[at];
+        const float2 abn = s_ab[at];
+        butterfly(s_y, rec, ab, R.wc4, inverse, live && q0 + R.wq < q1);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        x = xn;
+        if (!mask) return;
         q0 = q0n;
         q1 = q1n;
         rec = recn;
