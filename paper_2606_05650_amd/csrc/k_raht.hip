@@ -724,6 +724,39 @@ struct Roles {
         wact = wq < MPW;
         w = tid / WAVE;
     }
+    Roles() = default;
+};
+// The roles of a launch's slices (every frame of a launch has the same C) kept in one register
+// between their uses: the divisions are made once per launch, and the unpacked fields do not live
+// through the merges and stores of every item (the opaque copy keeps them from being hoisted).
+struct RolesKept {
+    uint32_t C4, RPB, MPW, packed;
+    __device__ explicit RolesKept(uint32_t C4_)
+    {
+        const Roles r(C4_);
+        static_assert(RT <= 1024 && WAVE <= 64, "10 + 6 bits; a chunk in 4 bits");
+        C4 = C4_;
+        RPB = r.RPB;
+        MPW = r.MPW;
+        packed = r.row0 | (r.c4 << 12) | (r.wq << 16) | (r.wc4 << 24);
+    }
+    __device__ Roles get() const
+    {
+        uint32_t v = packed;
+        asm volatile("" : "+v"(v));
+        Roles r;
+        r.C4 = C4;
+        r.RPB = RPB;
+        r.MPW = MPW;
+        r.row0 = v & 0xFFFu;
+        r.c4 = (v >> 12) & 0xFu;
+        r.wq = (v >> 16) & 0xFFu;
+        r.wc4 = v >> 24;
+        r.act = r.row0 < RPB;
+        r.wact = r.wq < MPW;
+        r.w = threadIdx.x / WAVE;
+        return r;
+    }
 };
 
 // The next level to visit in a mask of levels: ascending (forward) or descending (inverse).
@@ -1286,39 +1319,63 @@ __device__ inline bool up_schedule_own(const TileMap &m, uint32_t f, int k, uint
     return true;
 }
 
+// Where an encoder's quantized coefficient rows begin in its stream: after the header and the
+// occupancy bytes (level d of the octree holds the heads of depths 0 .. d, so head count k is in
+// J - k levels), on the next 256-byte boundary. Lane k holds head count k, so the loads are one
+// round trip; by every wave that stores rows, once per frame or item. null for other modes.
+__device__ inline GAS int32_t *coef_out(const CAS FrameDesc &fd)
+{
+    if (fd.mode != MODE_ENCODE) return nullptr;
+    static_assert(GSC_MAX_DEPTH <= 32, "lane k: head count k; the halves' sums fit 32 bits");
+    const uint32_t lane = lane_id(), J = fd.J;
+    const uint32_t h = gp(fd.ctrl->hist_D)[min(lane, J - 1)];  // (written by an earlier launch)
+    const uint64_t bytes = lane < J ? (uint64_t)h * (J - lane) : 0ull;
+    const uint64_t lo = wave_sum((uint32_t)bytes & 0xFFFFFFu), hi = wave_sum((uint32_t)(bytes >> 24));
+    const uint64_t off = GSC_HEADER_BYTES + lo + (hi << 24);
+    return gp(reinterpret_cast<int32_t *>(fd.stream + align_up(off, 256)));
+}
+
 // The quantized (or float) coefficient rows at their voxel rows, of the entries j that `skip`
-// lets through. Open entries are skipped by every caller: an open entry's coefficient is written
-// by the level that completes its merge (so that every row is written exactly once in the
-// launch), except at the final level, where the open entry is the sequence's first one and holds
-// the DC.
+// lets through; coef: coef_out(fd). Open entries are skipped by every caller: an open entry's
+// coefficient is written by the level that completes its merge (so that every row is written exactly
+// once in the launch), except at the final level, where the open entry is the sequence's first one and
+// holds the DC. The LDS reads of STORE_BATCH rows are issued together.
+constexpr int STORE_BATCH = 4;
 template <bool VEC, bool POW2, class RowOf, class YAt, class Skip>
-__device__ inline void store_coefs(const CAS FrameDesc &fd, const float *s_st, const float *s_ist, const Roles &R,
-                                   uint32_t c4, uint32_t mlen, Skip skip, RowOf row_of, YAt y_at)
+__device__ inline void store_coefs(const CAS FrameDesc &fd, GAS int32_t *coef, const float *s_st, const float *s_ist,
+                                   const Roles &R, uint32_t c4, uint32_t mlen, Skip skip, RowOf row_of, YAt y_at)
 {
     const uint32_t C = fd.C;
     GAS float *cf = gp(fd.coef_f32);
-    if (fd.mode == MODE_ENCODE) {
-        const CAS Ctrl *ctrl = cp(fd.ctrl);
-        uint64_t off = GSC_HEADER_BYTES, run = 0;
-        for (uint32_t dd = 0; dd < fd.J; ++dd) {
-            run += ctrl->hist_D[dd];
-            off += run;
-        }
-        GAS int32_t *coef = gp(reinterpret_cast<int32_t *>(fd.stream + align_up(off, 256)));
-        const double omt = 1.0 - (double)fd.tau;
-        const float thr = ceil_float(omt);
-        const bool deq = fd.ste == STE_FORWARD;  // float output: q * step instead of y
-        float st[4], ist[4];
+    const bool quant = fd.mode == MODE_ENCODE;  // else MODE_FWD_F32: float coefficient rows
+    const bool deq = fd.ste == STE_FORWARD;     // float output: q * step instead of y
+    const double omt = 1.0 - (double)fd.tau;
+    const float thr = ceil_float(omt);
+    float st[4], ist[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t c = min(4 * c4 + q, C - 1);
-            st[q] = s_st[c];
-            ist[q] = s_ist[c];
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t c = min(4 * c4 + q, C - 1);
+        st[q] = s_st[c];
+        ist[q] = s_ist[c];
+    }
+    for (uint32_t jb = R.row0; jb < mlen; jb += STORE_BATCH * R.RPB) {
+        float4 yb[STORE_BATCH];
+        bool off[STORE_BATCH];
+#pragma unroll
+        for (int u = 0; u < STORE_BATCH; ++u) {
+            const uint32_t j = jb + u * R.RPB, jc = min(j, mlen - 1);
+            yb[u] = y_at(jc);
+            off[u] = j >= mlen || skip(jc);
         }
-        for (uint32_t j = R.row0; j < mlen; j += R.RPB) {
-            if (skip(j)) continue;
-            const float4 y = y_at(j);
-            const uint64_t row = row_of(j);
+#pragma unroll
+        for (int u = 0; u < STORE_BATCH; ++u) {
+            if (off[u]) continue;
+            const float4 y = yb[u];
+            const uint64_t row = row_of(jb + u * R.RPB);
+            if (!quant) {
+                st4<VEC>(cf, row, C, c4, y);
+                continue;
+            }
             const int4 q = make_int4(quant1<POW2>(y.x, st[0], ist[0], omt, thr), quant1<POW2>(y.y, st[1], ist[1], omt, thr),
                                      quant1<POW2>(y.z, st[2], ist[2], omt, thr), quant1<POW2>(y.w, st[3], ist[3], omt, thr));
             stq4<VEC>(coef, row, C, c4, q);
@@ -1326,11 +1383,6 @@ __device__ inline void store_coefs(const CAS FrameDesc &fd, const float *s_st, c
                 st4<VEC>(cf, row, C, c4,
                          deq ? make_float4((float)q.x * st[0], (float)q.y * st[1], (float)q.z * st[2], (float)q.w * st[3])
                              : y);
-        }
-    } else {  // MODE_FWD_F32: float coefficient rows
-        for (uint32_t j = R.row0; j < mlen; j += R.RPB) {
-            if (skip(j)) continue;
-            st4<VEC>(cf, row_of(j), C, c4, y_at(j));
         }
     }
 }
@@ -1352,6 +1404,7 @@ __device__ inline void fwd_up_item(const TileMap &m, uint32_t f, int k, uint32_t
     const uint32_t c4 = cb + R.c4;  // this thread's global channel chunk
     const bool live = R.act && R.c4 < nch;
     os_set(A.os, A.opos[min(threadIdx.x, (uint32_t)OPEN_CAP - 1)], threadIdx.x < ts.ocnt);
+    GAS int32_t *coef = coef_out(fd);
     // ---- the entries' values of this channel slice
     if (live) {
         const CohRows vsrc(fd.lv[k - 1].vbuf, ts.s, mlen, C4);
@@ -1364,7 +1417,7 @@ __device__ inline void fwd_up_item(const TileMap &m, uint32_t f, int k, uint32_t
     __syncthreads();
     cross_phase(s_y, R, A.rec, A.ab, A.lst, xmask, nch, false);
     if (!live) return;
-    store_coefs<VEC, POW2>(fd, s_st, s_ist, R, c4, mlen,
+    store_coefs<VEC, POW2>(fd, coef, s_st, s_ist, R, c4, mlen,
                            [&](uint32_t j) { return !ts.final_level && os_open(A.os, j); },
                            [&](uint32_t j) -> uint64_t { return A.idx[j]; },
                            [&](uint32_t j) { return s_y[j * CH4 + R.c4]; });
@@ -1480,6 +1533,10 @@ typedef const CAS FrameDesc CFrame;
 struct Frame1 {
     uint32_t f;   // frame, ~0u before the first
     uint32_t nk;  // entries of S_1; 0 when the frame has nothing to transform
+    uint32_t C4, CH4, NP;  // (every frame of a launch has the same C)
+    __device__ explicit Frame1(const TileMap &m) : f(~0u), nk(0), C4(cp(m.fd[0])->C4), CH4(pass_chunks(C4, 1)), NP(channel_passes(C4, 1)) {}
+    // the channel chunks of slice p
+    __device__ uint32_t chunks(uint32_t p) const { return min(CH4, C4 - p * CH4); }
 };
 
 __device__ inline Item1 item1(const TileMap &m, uint32_t i, Frame1 &fc)
@@ -1503,7 +1560,7 @@ __device__ inline Item1 item1(const TileMap &m, uint32_t i, Frame1 &fc)
         }
         fc.nk = __builtin_amdgcn_readfirstlane(nk);
     }
-    const SliceSplit hs = slice_split(i - m.start[f], channel_passes(d->C4, 1));
+    const SliceSplit hs = slice_split(i - m.start[f], fc.NP);
     it.f = f;
     it.tile = hs.tile;
     it.p = hs.p0;
@@ -1620,9 +1677,9 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
         Gp = min(level_items(m, 2, 1, s_fs), gridDim.x);
         if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, *reinterpret_cast<PreScratch<PRE_EPT_UP> *>(s_y), ctr_word(m, PRE_DONE));
     }
-    Frame1 fc;
-    fc.f = ~0u;
-    fc.nk = 0;
+    Frame1 fc(m);
+    const uint32_t CH4 = fc.CH4;
+    const RolesKept roles(CH4);
     // the first row of entry tid of an item (clamped where it is stored into s_row, so that
     // nothing waits for the load before then)
     auto first_row = [&](const Item1 &it) -> uint32_t {
@@ -1633,20 +1690,12 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
         const uint32_t n = cp(m.fd[it.f])->n;
         return min(r, n ? n - 1 : 0u);
     };
-    // the channel slice of an item: CH4 chunks per slice, nch of them in this one
-    auto slice = [&](const Item1 &it, uint32_t &CH4, uint32_t &nch) {
-        const uint32_t C4 = cp(m.fd[it.f])->C4;
-        CH4 = pass_chunks(C4, 1);
-        nch = min(CH4, C4 - it.p * CH4);
-    };
     auto prefetch = [&](const Item1 &it, Sched1 &S, float4 (&D)[NR1]) {
         CFrame *d = cp(m.fd[it.f]);
         const bool enc = d->mode == MODE_ENCODE;
-        uint32_t CH4, nch;
-        slice(it, CH4, nch);
-        const Roles R(CH4);
         load_sched1(d, it, S);
-        if (R.act && R.c4 < nch)
+        const Roles R = roles.get();
+        if (R.act && R.c4 < fc.chunks(it.p))
             load_rows1<VEC>(gp(d->attr), d->C, R, it.p * CH4 + R.c4, it.mlen, enc, s_row, it.s, D);
     };
     // first-level item i goes to workgroup (Gp + i) % G: the schedule workgroups come last in the
@@ -1657,7 +1706,8 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     Item1 it1 = item1(m, b1 + G, fc);
     Sched1 S;
     float4 D[NR1];
-    uint32_t F1 = 0;
+    uint32_t F1 = 0, cof = ~0u;  // cof: frame whose coefficient rows coef holds
+    GAS int32_t *coef = nullptr;
     // prologue: the quantizer steps (shared by the frames of a launch) into LDS, the open-entry
     // sets cleared, the first item's rows, schedule and row loads
     if (tid < GSC_MAX_CHANNELS) {
@@ -1674,13 +1724,16 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     for (uint32_t i = b1; i < items; i += G, ++n1, par ^= 1u) {
         CFrame *d = cp(m.fd[it0.f]);
         const bool encode = d->mode == MODE_ENCODE;
-        uint32_t CH4, nch;
-        slice(it0, CH4, nch);
-        const Roles R(CH4);
+        const Roles R = roles.get();
+        const uint32_t nch = fc.chunks(it0.p);
         const uint32_t c4 = it0.p * CH4 + R.c4;  // this thread's global channel chunk
         const bool live = it0.ok && R.act && R.c4 < nch;
         const uint32_t C = d->C, n = d->n;
-        const uint32_t obase = S.obase, ocnt = S.ocnt;
+        const uint32_t obase = __builtin_amdgcn_readfirstlane(S.obase), ocnt = __builtin_amdgcn_readfirstlane(S.ocnt);
+        if (it0.f != cof) {  // the frame's first item
+            cof = it0.f;
+            coef = coef_out(*d);
+        }
         const bool dup = S.m_end - S.m_beg != it0.mlen;  // a voxel of the tile has several Gaussians
         const OpenSet os{s_om[par], s_opre};
         __syncthreads();  // the previous item is no longer read from LDS
@@ -1753,7 +1806,7 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
             cross_phase(s_y, R, s_rec, s_ab, s_lst, xmask, nch, false);
             if (live) {
                 const bool fl = it0.final_level;
-                store_coefs<VEC, POW2>(*d, s_st, s_ist, R, c4, mlen, [&](uint32_t j) { return !fl && os_open(os, j); },
+                store_coefs<VEC, POW2>(*d, coef, s_st, s_ist, R, c4, mlen, [&](uint32_t j) { return !fl && os_open(os, j); },
                                        [&](uint32_t j) -> uint64_t { return s + j; },
                                        [&](uint32_t j) { return s_y[j * CH4 + R.c4]; });
                 if (!it0.final_level) {
@@ -1925,14 +1978,9 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
                               s_fs, n2) % G;
         __syncthreads();  // the upper levels' LDS is no longer read
     }
-    Frame1 fc;
-    fc.f = ~0u;
-    fc.nk = 0;
-    auto slice = [&](const Item1 &it, uint32_t &CH4, uint32_t &nch) {
-        const uint32_t C4 = cp(m.fd[it.f])->C4;
-        CH4 = pass_chunks(C4, 1);
-        nch = min(CH4, C4 - it.p * CH4);
-    };
+    Frame1 fc(m);
+    const uint32_t CH4 = fc.CH4;
+    const RolesKept roles(CH4);
     // the coefficient rows of an item: the stream's quantized rows (decode) or float rows
     auto coef_rows = [&](CFrame *d) -> const GAS float * {
         if (d->mode == MODE_DECODE) {
@@ -1941,22 +1989,24 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
         }
         return gp(d->mode == MODE_ENCODE ? d->coef_f32 : d->attr);
     };
+    uint32_t rof = ~0u;  // frame whose coefficient rows `rows` holds
+    const GAS float *rows = nullptr;
     // an item's schedule and coefficient rows; the low-passes of its open entries (o entries from ob)
     auto prefetch = [&](const Item1 &it, Sched1 &S, float4 (&D)[NR1]) {
         CFrame *d = cp(m.fd[it.f]);
-        uint32_t CH4, nch;
-        slice(it, CH4, nch);
-        const Roles R(CH4);
+        const Roles R = roles.get();
         load_sched1(d, it, S);
-        if (R.act && R.c4 < nch)
-            load_rows1<VEC>(coef_rows(d), d->C, R, it.p * CH4 + R.c4, it.mlen, false, nullptr, it.s, D);
+        if (it.f != rof) {
+            rof = it.f;
+            rows = coef_rows(d);
+        }
+        if (R.act && R.c4 < fc.chunks(it.p))
+            load_rows1<VEC>(rows, d->C, R, it.p * CH4 + R.c4, it.mlen, false, nullptr, it.s, D);
     };
     auto low_passes = [&](const Item1 &it, uint32_t ob, uint32_t no, float4 (&O)[NO1]) {
         CFrame *d = cp(m.fd[it.f]);
-        uint32_t CH4, nch;
-        slice(it, CH4, nch);
-        const Roles R(CH4);
-        if (R.act && R.c4 < nch && !it.final_level && no > 0) {
+        const Roles R = roles.get();
+        if (R.act && R.c4 < fc.chunks(it.p) && !it.final_level && no > 0) {
             const CohRows src(d->lv[1].vbuf, ob, no, d->C4);
 #pragma unroll
             for (int u = 0; u < NO1; ++u) O[u] = src.ld(min(R.row0 + (uint32_t)u * R.RPB, no - 1), it.p * CH4 + R.c4);
@@ -1976,13 +2026,12 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     for (uint32_t i = b1; i < items; i += G, first = false) {
         CFrame *d = cp(m.fd[it0.f]);
         const bool decode = d->mode == MODE_DECODE;
-        uint32_t CH4, nch;
-        slice(it0, CH4, nch);
-        const Roles R(CH4);
+        const Roles R = roles.get();
+        const uint32_t nch = fc.chunks(it0.p);
         const uint32_t c4 = it0.p * CH4 + R.c4;
         const bool live = it0.ok && R.act && R.c4 < nch;
         const uint32_t C = d->C;
-        const uint32_t obase = S.obase, ocnt = S.ocnt;
+        const uint32_t obase = __builtin_amdgcn_readfirstlane(S.obase), ocnt = __builtin_amdgcn_readfirstlane(S.ocnt);
         const bool has_open = it0.ok && !it0.final_level && ocnt > 0;
         if (decode && it0.f != stf) {  // the frame's dequantization steps (once per frame)
             stf = it0.f;
@@ -2064,8 +2113,14 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
                     }
                 } else {
                     GAS float *out = gp(d->mode == MODE_ADJ_F32 ? d->coef_f32 : d->attr_out);
-                    for (uint32_t j = R.row0, yi = y0; j < mlen; j += R.RPB, yi += ystep)
-                        st4<VEC>(out, s + j, C, c4, s_y[yi]);
+                    for (uint32_t jb = R.row0; jb < mlen; jb += STORE_BATCH * R.RPB) {
+                        float4 yb[STORE_BATCH];
+#pragma unroll
+                        for (int u = 0; u < STORE_BATCH; ++u) yb[u] = s_y[min(jb + u * R.RPB, mlen - 1) * CH4 + R.c4];
+#pragma unroll
+                        for (int u = 0; u < STORE_BATCH; ++u)
+                            if (jb + u * R.RPB < mlen) st4<VEC>(out, s + jb + u * R.RPB, C, c4, yb[u]);
+                    }
                 }
             }
         }
