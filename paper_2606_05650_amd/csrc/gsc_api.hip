@@ -184,7 +184,7 @@ gsc_status run_setup(const Frame *fr, int F, const SetupArgs &proto, hipStream_t
         uint32_t zb = ceil_div(zmax / 16 + 1, SETUP_THREADS * 4);
         if (zb < 1) zb = 1;
         if (zb > 1024) zb = 1024;
-        GSC_LAUNCH(launch_setup(a, zb > bmax + 1 ? zb : bmax + 1, s));
+        GSC_LAUNCH(launch_setup(a, fr[f0].L, zb > bmax + 1 ? zb : bmax + 1, s));
     }
     return GSC_OK;
 }

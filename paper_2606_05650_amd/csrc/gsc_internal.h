@@ -239,7 +239,7 @@ struct FrameArgs {
 };
 constexpr int SETUP_MAX = 16;
 constexpr int SETUP_THREADS = BBOX_THREADS;  // the setup blocks also take the bounding-box partials
-struct SetupArgs {
+struct SetupCommon {
     uint32_t count;
     uint32_t J, C, mode, bbox_mode;
     uint32_t ste;
@@ -249,6 +249,8 @@ struct SetupArgs {
     double bbox_min[3];
     double cell;
     float step[GSC_MAX_CHANNELS];
+};
+struct SetupArgs : SetupCommon {
     FrameArgs f[SETUP_MAX];
 };
 
@@ -270,6 +272,14 @@ struct Layout {
         obase[MAXK + 1], ocnt[MAXK + 1], status[MAXK + 1], vbuf[MAXK + 1];
     uint32_t tiles[MAXK + 1], cap[MAXK + 1];
 };
+
+// The setup of one frame takes the host's layout with it (the arguments of a launch are limited to
+// 4 KB, so several frames' layouts are computed by their workgroups).
+struct SetupOne : SetupCommon {
+    FrameArgs f[1];
+    Layout L;
+};
+static_assert(sizeof(SetupOne) <= 4096 && sizeof(SetupArgs) <= 4096, "kernel arguments");
 
 __host__ __device__ inline uint32_t ceil_div(uint64_t a, uint64_t b)
 {
@@ -371,7 +381,7 @@ __host__ __device__ inline bool make_layout(int64_t n, int J, int C, Layout *L)
 }
 
 // Launch helpers (defined next to their kernels). Each returns the launch status.
-hipError_t launch_setup(const SetupArgs &a, uint32_t zero_blocks, hipStream_t s);
+hipError_t launch_setup(const SetupArgs &a, const Layout &first, uint32_t zero_blocks, hipStream_t s);
 hipError_t launch_voxelize(const TileMap &m, hipStream_t s);
 hipError_t launch_sort_pass(const TileMap &m, int pass, int variant, int bits, hipStream_t s);
 hipError_t launch_dedup(const TileMap &m, hipStream_t s);
