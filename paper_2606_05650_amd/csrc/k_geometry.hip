@@ -14,8 +14,9 @@ namespace gsc {
 // blocks 1 .. bbox_blocks(n) also take the frame's bounding-box partials (bbox_partial); block
 // (0, f) builds the frame descriptor and initialises the control block. The zero region and the
 // bounding-box slots come from the host's layout; the rest of it is an argument for one frame (a
-// thread that computes it takes 3 us, the longest part of a small frame's setup: 100K decode 80.8 us with it, 79.6 without, 1M decode 236 and 233) and computed by
-// block 0 for several, whose layouts do not fit the arguments.
+// thread that computes it takes 3 us, the longest part of a small frame's setup: 100K decode 80.8 us
+// with it, 79.6 without, 1M decode 236 and 233) and computed by block 0 for several, whose layouts do
+// not fit the arguments.
 __device__ inline void bbox_partial(const float *pos_, uint32_t n, uint32_t b, uint32_t G, GAS uint32_t *slot);
 
 template <class Args>

@@ -728,7 +728,9 @@ struct Roles {
 };
 // The roles of a launch's slices (every frame of a launch has the same C) kept in one register
 // between their uses: the divisions are made once per launch, and the unpacked fields do not live
-// through the merges and stores of every item (the opaque copy keeps them from being hoisted).
+// through the merges and stores of every item (the opaque copy keeps them from being hoisted: held
+// unpacked they pushed both first-level kernels past their 128 registers, and a 1M encode took 386 us
+// in place of 373). With coef_out and the batched stores: a batch of eight frames 3023 -> 2960 us.
 struct RolesKept {
     uint32_t C4, RPB, MPW, packed;
     __device__ explicit RolesKept(uint32_t C4_)
@@ -770,7 +772,8 @@ __device__ inline uint32_t next_level(uint64_t mask, bool inverse)
 // holds the record range of level x in registers (read out with readlane). A step takes up to MPW
 // merges of one level, and its records are loaded while the step before runs, so a step costs one
 // LDS round trip; a level of more merges is several such steps, not a loop inside the step (whose
-// records would be waited for: a chunk of the first level has about 8 levels and 11 steps). A lane
+// records would be waited for: a chunk of the first level has about 8 levels and 11 steps; the flat
+// sequence took a 1M frame's decode from 246 to 238 us, a 4M one's encode from 1131 to 1119). A lane
 // without a merge reads the step's last one and writes nothing: the reads stand outside any branch, so
 // the wait for them covers the records loaded before them and the next step begins without one.
 // The wave's own LDS accesses are performed in program order; the fence keeps the compiler from
@@ -1508,6 +1511,11 @@ __device__ inline void inv_up_item(const TileMap &m, uint32_t f, int k, uint32_t
 // the next item are in flight in registers. The input row of every voxel's first member comes
 // from the dedup kernel's table and is read two items ahead, so the next item's row addresses
 // are known when its loads are issued.
+// What bounds it is the rate of line requests of the sliced rows: a plain gather of 224-byte rows in two
+// 112-byte slices by as many workgroups takes 605 us at 4M rows and 123 us at 1M, of whole rows 410 and
+// 87 (this level: about 560 and 150, merges and quantizer included). Whole rows of a tile need twice the
+// LDS (one workgroup per CU, nothing to overlap its phases with) or tiles of 256 entries (tried with one
+// wave per chunk: 4M 1165 us against 1113, 1M 410 against 374; too few waves for the merges' latency).
 // rows of a slice per thread: ceil(RT / floor(RT / CH4)), at most this for CH4 <= CH4_MAX1
 __host__ __device__ constexpr int rows_per_thread_max(int ch4max)
 {
