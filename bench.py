@@ -68,8 +68,8 @@ def alg_bytes(stage, n, nv, C):
 KERNEL_SOURCES = ("paper_2606_05650_amd/csrc/k_raht.hip", "paper_2606_05650_amd/csrc/gsc_device.h",
                   "paper_2606_05650_amd/csrc/gsc_internal.h")
 PMC_TRAFFIC = {"workload": "frame1M_J12",
-               "sources_sha256": "00307bf33758a177c2a7abe5d20d24907baecf189062d03fe389f87c9331b589",
-               "raht_fwd1": 591801410, "raht_inv1": 481161103}
+               "sources_sha256": "22fac2a4d02833184e319f62a3b67149132c3164f0380980a1957b33d1ecea90",
+               "raht_fwd1": 591519853, "raht_inv1": 481295317}
 KERNEL_NAMES = {"raht_fwd1": "k_raht_fwd", "raht_inv1": "k_raht_inv"}
 
 
