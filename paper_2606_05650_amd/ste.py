@@ -97,12 +97,15 @@ class _RdLoss(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, g_loss, g_dist, g_rate, g_diff):
-        yhat, diff, steps = ctx.saved_tensors
+        yhat, diff, steps = ctx.saved_tensors  # (as a saved-tensor hook hands them back)
         gs = (g_loss, g_dist, g_rate)
-        if not torch.is_grad_enabled() and g_diff is None and any(g is not None for g in gs):
+        given = [g for g in gs if g is not None]
+        if not torch.is_grad_enabled() and g_diff is None and given and \
+                all(_readable(t, yhat.device) for t in (yhat, diff, steps, *given)):
             gy, ga = gsc.rd_loss_backward(yhat, diff, steps, ctx.lam, ctx.count, *gs)
             return gy, ga, None, None, None, None
-        # differentiable (create_graph), or a gradient of the difference: torch operators
+        # differentiable (create_graph), a gradient of the difference, or tensors that are not plain
+        # memory (batched gradients): torch operators
         zero = torch.zeros((), dtype=yhat.dtype, device=yhat.device)
         gl, gd, gr = (zero if g is None else g for g in gs)
         ga = (gl + gd) * 2.0 * diff / (ctx.count * diff.shape[1])
@@ -112,24 +115,34 @@ class _RdLoss(torch.autograd.Function):
         return gy, ga, None, None, None, None
 
 
+def _readable(t, device, dtype=torch.float32):
+    """Whether a kernel may read t's memory as it stands: an ordinary dense tensor of the type, and not
+    a transform's wrapper (which has no memory of its own) or a view that negates when it is read."""
+    if type(t) not in (torch.Tensor, torch.nn.Parameter) or t.dtype != dtype or t.device != device:
+        return False
+    if t.layout != torch.strided or not t.is_contiguous() or t.is_neg():
+        return False
+    try:
+        return t.data_ptr() != 0
+    except RuntimeError:
+        return False
+
+
 def _plain_rows(yhat, ahat, aref, steps, lam, nv):
     """Whether rd_loss may run as _RdLoss: ordinary float32 rows on the current device, gradients
     wanted of yhat and ahat only, and no mode or transform active that has to see the operators."""
     ts = (yhat, ahat, aref, steps) + (() if nv is None else (nv,))
-    if not all(type(t) in (torch.Tensor, torch.nn.Parameter) for t in ts) or type(lam) not in (int, float):
+    if not all(isinstance(t, torch.Tensor) for t in ts) or type(lam) not in (int, float):
         return False
     if not yhat.is_cuda or yhat.device.index != torch.cuda.current_device():
         return False
     if yhat.dim() != 2 or yhat.shape[0] < 1 or not 1 <= yhat.shape[1] <= gsc.MAX_CHANNELS:
         return False
-    for t in ts:
-        if t.device != yhat.device or t.layout != torch.strided or not t.is_contiguous() or t.is_neg():
-            return False
-    if any(t.dtype != torch.float32 for t in ts[:4]) or any(t.shape != yhat.shape for t in ts[1:3]):
+    if not all(_readable(t, yhat.device) for t in ts[:4]) or any(t.shape != yhat.shape for t in ts[1:3]):
         return False
     if steps.shape != yhat.shape[1:] or aref.requires_grad or steps.requires_grad:
         return False
-    if nv is not None and (nv.dtype != torch.int64 or nv.numel() != 1):
+    if nv is not None and (nv.numel() != 1 or not _readable(nv, yhat.device, torch.int64)):
         return False
     if torch.compiler.is_compiling() or torch.jit.is_tracing() or torch._C._are_functorch_transforms_active():
         return False

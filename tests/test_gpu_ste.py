@@ -314,3 +314,44 @@ def test_rd_loss_keeps_torch_semantics():
     _, tangent = torch.func.jvp(lambda a: rd_loss(a, h, r, steps, 0.01)[0], (y,), (torch.ones_like(y),))
     # (torch's own forward-mode formulas return this tangent in FP64)
     torch.testing.assert_close(tangent.float(), want[0].sum(), rtol=1e-5, atol=1e-6)
+
+
+def _loss_inputs(rows=37, C=6):
+    g = torch.Generator(device=_dev()).manual_seed(rows + C)
+    y, h, r = (torch.randn(rows, C, generator=g, device=_dev()) for _ in range(3))
+    return y, h, r, torch.full((C,), 0.25, device=_dev())
+
+
+def _leaves(fn, dtype, y, h, r, steps):
+    a, b = (t.to(dtype).clone().requires_grad_(True) for t in (y, h))
+    return a, b, fn(a, b, r.to(dtype), steps.to(dtype), 0.01)
+
+
+@pytest.mark.parametrize("kind", ["batched", "negated", "strided", "double"])
+def test_rd_loss_backward_of_tensors_a_kernel_cannot_read(kind):
+    """Scalar gradients that are batched (is_grads_batched) or negate when they are read, and saved
+    tensors that a hook hands back with other strides or in another type. A gradient entry is a
+    handful of FP32 roundings (1e-6 relative)."""
+    from paper_2606_05650_amd.ste import rd_loss
+    y, h, r, steps = _loss_inputs()
+
+    def grads(fn, dtype):
+        if kind in ("strided", "double") and fn is rd_loss:
+            def unpack(t):
+                return t if t.dim() != 2 else t.t().contiguous().t() if kind == "strided" else t.double()
+            with torch.autograd.graph.saved_tensors_hooks(lambda t: t, unpack):
+                a, b, out = _leaves(fn, dtype, y, h, r, steps)
+        else:
+            a, b, out = _leaves(fn, dtype, y, h, r, steps)
+        if kind == "batched":
+            return torch.autograd.grad(torch.stack(out), (a, b), torch.eye(3, dtype=dtype, device=_dev()),
+                                       is_grads_batched=True)
+        g = torch.ones((), dtype=dtype, device=_dev())
+        if kind == "negated":
+            g = torch.complex(torch.zeros_like(g), g).conj().imag
+            assert g.is_neg()
+        return torch.autograd.grad(out[0], (a, b), g)
+
+    for x, z in zip(grads(rd_loss, torch.float32), grads(_torch_rd_loss, torch.float64)):
+        assert x.dtype == torch.float32 and x.shape == z.shape
+        assert (x.double() - z).abs().max().item() <= 1e-6 * z.abs().max().item()
