@@ -100,18 +100,23 @@ class _RdLoss(torch.autograd.Function):
         yhat, diff, steps = ctx.saved_tensors  # (as a saved-tensor hook hands them back)
         gs = (g_loss, g_dist, g_rate)
         given = [g for g in gs if g is not None]
-        if not torch.is_grad_enabled() and g_diff is None and given and \
+        # yhat has a gradient by the rate, ahat by the distortion and the difference: an input that none
+        # of the differentiated results depends on has none (zeros would be NaN where a row is not finite)
+        by_rate = [g for g in (g_loss, g_rate) if g is not None] if ctx.needs_input_grad[0] else []
+        by_dist = [g for g in (g_loss, g_dist) if g is not None] if ctx.needs_input_grad[1] else []
+        if not torch.is_grad_enabled() and g_diff is None and by_rate and by_dist and \
                 all(_readable(t, yhat.device) for t in (yhat, diff, steps, *given)):
             gy, ga = gsc.rd_loss_backward(yhat, diff, steps, ctx.lam, ctx.count, *gs)
             return gy, ga, None, None, None, None
-        # differentiable (create_graph), a gradient of the difference, or tensors that are not plain
-        # memory (batched gradients): torch operators
-        zero = torch.zeros((), dtype=yhat.dtype, device=yhat.device)
-        gl, gd, gr = (zero if g is None else g for g in gs)
-        ga = (gl + gd) * 2.0 * diff / (ctx.count * diff.shape[1])
-        gy = (gl + gr) * (ctx.lam / math.log(2.0)) * yhat.sgn() / (steps + yhat.abs())
-        if g_diff is not None:
-            ga = ga + g_diff
+        # one of the two gradients, differentiable (create_graph), a gradient of the difference, or
+        # tensors that are not plain memory (batched gradients): torch operators
+        gy = ga = None
+        if by_rate:
+            gy = sum(by_rate) * (ctx.lam / math.log(2.0)) * yhat.sgn() / (steps + yhat.abs())
+        if by_dist:
+            ga = sum(by_dist) * 2.0 * diff / (ctx.count * diff.shape[1])
+        if g_diff is not None and ctx.needs_input_grad[1]:
+            ga = g_diff if ga is None else ga + g_diff
         return gy, ga, None, None, None, None
 
 

@@ -355,3 +355,26 @@ def test_rd_loss_backward_of_tensors_a_kernel_cannot_read(kind):
     for x, z in zip(grads(rd_loss, torch.float32), grads(_torch_rd_loss, torch.float64)):
         assert x.dtype == torch.float32 and x.shape == z.shape
         assert (x.double() - z).abs().max().item() <= 1e-6 * z.abs().max().item()
+
+
+@pytest.mark.parametrize("empty", [False, True])
+def test_rd_loss_leaves_independent_inputs_alone(empty):
+    """An input that the differentiated results do not depend on has no gradient (as the formula gives
+    none), also where it or the voxel count would make one of NaN."""
+    from paper_2606_05650_amd.ste import rd_loss
+    y, h, r, steps = _loss_inputs()
+    h[3, 2] = float("inf")
+    nv = torch.tensor([0 if empty else y.shape[0]], device=_dev())
+    for k, used in ((2, 0), (1, 1)):  # the rate depends on yhat, the distortion on ahat
+        for fn in (_torch_rd_loss, rd_loss):
+            a, b = (t.clone().requires_grad_(True) for t in (y, h))
+            got = torch.autograd.grad(fn(a, b, r, steps, 0.01, nv=nv)[k], (a, b), allow_unused=True)
+            assert got[used] is not None and got[1 - used] is None
+            assert used == 1 or not got[0].isnan().any()
+            a, b = (t.clone().requires_grad_(True) for t in (y, h))
+            with pytest.raises(RuntimeError):
+                torch.autograd.grad(fn(a, b, r, steps, 0.01, nv=nv)[k], (a, b)[1 - used])
+    # weights that are all given: both have one
+    a, b = (t.clone().requires_grad_(True) for t in (y, h))
+    loss, dist, rate = rd_loss(a, b, r, steps, 0.01, nv=nv)
+    assert all(g is not None for g in torch.autograd.grad(dist + rate, (a, b)))
