@@ -91,6 +91,10 @@ class _RdLoss(torch.autograd.Function):
     def forward(ctx, yhat, ahat, aref, steps, lam, nv):
         ctx.set_materialize_grads(False)
         loss, dist, rate, ctx.count, diff = gsc.rd_loss_forward(yhat, ahat, aref, steps, lam, nv=nv)
+        if not ctx.needs_input_grad[1]:
+            ctx.mark_non_differentiable(dist, diff)
+        if not ctx.needs_input_grad[0]:
+            ctx.mark_non_differentiable(rate)
         ctx.lam = lam
         ctx.save_for_backward(yhat, diff, steps)
         return loss, dist, rate, diff

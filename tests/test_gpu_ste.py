@@ -378,3 +378,15 @@ def test_rd_loss_leaves_independent_inputs_alone(empty):
     a, b = (t.clone().requires_grad_(True) for t in (y, h))
     loss, dist, rate = rd_loss(a, b, r, steps, 0.01, nv=nv)
     assert all(g is not None for g in torch.autograd.grad(dist + rate, (a, b)))
+
+
+@pytest.mark.parametrize("of_yhat,of_ahat", [(True, False), (False, True), (True, True), (False, False)])
+def test_rd_loss_results_require_a_gradient_as_the_formula_s(of_yhat, of_ahat):
+    from paper_2606_05650_amd.ste import rd_loss
+    y, h, r, steps = _loss_inputs()
+    a, b = y.clone().requires_grad_(of_yhat), h.clone().requires_grad_(of_ahat)
+    got, want = rd_loss(a, b, r, steps, 0.01), _torch_rd_loss(a, b, r, steps, 0.01)
+    assert [t.requires_grad for t in got] == [t.requires_grad for t in want]
+    if of_yhat or of_ahat:
+        got[0].backward()
+        assert (a.grad is not None) == of_yhat and (b.grad is not None) == of_ahat
