@@ -19,6 +19,7 @@ HEADER_PATH = os.path.join(os.path.dirname(_HERE), "include", "gsc.h")
 
 MAX_DEPTH = 21
 MAX_CHANNELS = 64
+MAX_ROWS = (1 << 30) - 1  # rows (or Gaussians) of one call
 MAX_BATCH = 64
 HEADER_BYTES = 1024
 VERSION = 1         # GSC_VERSION

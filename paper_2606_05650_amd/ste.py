@@ -145,7 +145,7 @@ def _plain_rows(yhat, ahat, aref, steps, lam, nv):
         return False
     if not yhat.is_cuda or yhat.device.index != torch.cuda.current_device():
         return False
-    if yhat.dim() != 2 or yhat.shape[0] < 1 or not 1 <= yhat.shape[1] <= gsc.MAX_CHANNELS:
+    if yhat.dim() != 2 or not 1 <= yhat.shape[0] <= gsc.MAX_ROWS or not 1 <= yhat.shape[1] <= gsc.MAX_CHANNELS:
         return False
     if not all(_readable(t, yhat.device) for t in ts[:4]) or any(t.shape != yhat.shape for t in ts[1:3]):
         return False

@@ -390,3 +390,10 @@ def test_rd_loss_results_require_a_gradient_as_the_formula_s(of_yhat, of_ahat):
     if of_yhat or of_ahat:
         got[0].backward()
         assert (a.grad is not None) == of_yhat and (b.grad is not None) == of_ahat
+
+
+def test_rd_loss_of_more_rows_than_a_launch_takes():
+    from paper_2606_05650_amd.ste import rd_loss
+    one = torch.ones(gsc.MAX_ROWS + 1, 1, device=_dev())
+    loss, dist, rate = rd_loss(torch.zeros_like(one), one, torch.zeros_like(one), one[0], 0.01)
+    assert float(loss) == float(dist) == 1.0 and float(rate) == 0.0
