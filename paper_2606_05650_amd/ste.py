@@ -137,6 +137,18 @@ def _readable(t, device, dtype=torch.float32):
         return False
 
 
+def _watched():
+    """Whether a compiler, a trace, a transform, forward mode or a mode is active that has to see the
+    operators. torch has no public name for most of these questions: where one cannot be asked, the
+    answer is yes."""
+    try:
+        return (torch.compiler.is_compiling() or torch.jit.is_tracing() or
+                torch._C._are_functorch_transforms_active() or torch.autograd.forward_ad._current_level >= 0 or
+                torch._C._len_torch_dispatch_stack() > 0 or torch._C._len_torch_function_stack() > 0)
+    except AttributeError:
+        return True
+
+
 def _plain_rows(yhat, ahat, aref, steps, lam, nv):
     """Whether rd_loss may run as _RdLoss: ordinary float32 rows on the current device, gradients
     wanted of yhat and ahat only, and no mode or transform active that has to see the operators."""
@@ -153,11 +165,7 @@ def _plain_rows(yhat, ahat, aref, steps, lam, nv):
         return False
     if nv is not None and (nv.numel() != 1 or not _readable(nv, yhat.device, torch.int64)):
         return False
-    if torch.compiler.is_compiling() or torch.jit.is_tracing() or torch._C._are_functorch_transforms_active():
-        return False
-    if torch.autograd.forward_ad._current_level >= 0:
-        return False
-    return torch._C._len_torch_dispatch_stack() == 0 and torch._C._len_torch_function_stack() == 0
+    return not _watched()
 
 
 def rd_loss(yhat, ahat, aref, steps, lam, nv=None):

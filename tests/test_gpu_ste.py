@@ -397,3 +397,18 @@ def test_rd_loss_of_more_rows_than_a_launch_takes():
     one = torch.ones(gsc.MAX_ROWS + 1, 1, device=_dev())
     loss, dist, rate = rd_loss(torch.zeros_like(one), one, torch.zeros_like(one), one[0], 0.01)
     assert float(loss) == float(dist) == 1.0 and float(rate) == 0.0
+
+
+@pytest.mark.parametrize("where,name", [(torch._C, "_are_functorch_transforms_active"), (torch._C, "_len_torch_dispatch_stack"),
+                                        (torch._C, "_len_torch_function_stack"),
+                                        (torch.autograd.forward_ad, "_current_level")])
+def test_rd_loss_without_a_private_name_of_torch(monkeypatch, where, name):
+    """A torch that lacks one of the names takes the operators. Sums of 222 FP32 terms: 1e-5."""
+    from paper_2606_05650_amd.ste import rd_loss
+    y, h, r, steps = _loss_inputs()
+    want = _torch_rd_loss(*(t.double() for t in (y, h, r, steps)), 0.01)
+    monkeypatch.delattr(where, name)
+    got = rd_loss(y, h, r, steps, 0.01)
+    monkeypatch.undo()
+    for x, z in zip(got, want):
+        assert abs(float(x) - float(z)) <= 1e-5 * abs(float(z))
