@@ -414,8 +414,8 @@ struct RlgrDec {
             const uint32_t k = kp >> RLGR_FRAC;
             if (get(k + 1u) != 1u << k) return false;
         }
-        const uint32_t n = taken();
-        return !bad && (nw ? n > (nw - 1u) * 32u && n <= nw * 32u : n == 0);
+        const uint32_t n = taken();  // (at most 65536 values of 68 bits; nw is what the table claims)
+        return !bad && (n + 31u) / 32u == nw;
     }
 };
 

@@ -139,6 +139,22 @@ def test_corrupt_streams_are_reported():
     assert status(bad) == 5
 
 
+def test_table_claiming_more_words_than_32_bits_of_code_count():
+    """A block of one word whose table claims 2^27 + 1 (2^32 + 32 bits) in a stream that is that long."""
+    dev = _dev()
+    nw = (1 << 27) + 1
+    s = gsc.rlgr_encode(torch.tensor([[5]], dtype=torch.int32, device=dev), 1).check()
+    buf = torch.zeros(32 + 4 * (2 + nw), dtype=torch.uint8, device=dev)
+    buf[:s.nbytes()] = s.buf[:s.nbytes()]
+    words = buf.view(torch.int32)
+    assert int(words[6]) == 1 and int(words[9]) == 1  # the header's total and the table's end
+    for claim, status in ((1, 0), (2, 5), (nw, 5)):
+        words[6] = words[9] = claim
+        _, info = gsc.rlgr_decode(buf, 1, 1, 1)
+        torch.cuda.synchronize()
+        assert int(info[0].item()) == status, claim
+
+
 @pytest.mark.slow
 def test_full_size_frame_coefficients():
     # the 1M-Gaussian frame at depth 12 (the benchmark's workload), blocks of 2048
