@@ -284,11 +284,15 @@ __global__ __launch_bounds__(64) void k_rlgr_empty(RlgrArgs a)
 
 // ------------------------------------------------------------------------------ decoder
 // The words of a thread's block pass through an LDS ring of RLGR_RING words (slot i % RLGR_RING of
-// thread t at word t of row i % RLGR_RING: no bank conflicts), refilled every RLGR_STEP values from
-// RLGR_FETCH words loaded RLGR_STEP values earlier, so that the step that needs a new word pays an LDS
-// read whose result is used one word later. A block that outruns its refills (more than RLGR_FETCH
-// words in RLGR_STEP values: escapes) reads the stream directly. Positions are clamped to the block's
-// words; a block that reads past them is rejected by the number of bits it took.
+// thread t at word t of row i % RLGR_RING: no bank conflicts), refilled after every step of RLGR_STEP
+// values from RLGR_FETCH words loaded before it, so that the value that needs a new word pays an LDS
+// read whose result is used one word later. A wave in which a ring runs low (blocks of more than 16
+// bits a value) takes steps of a half or a quarter of the values until it is full again; a word that
+// is not in the ring yet is read from the stream and waited for, and a block that has also taken all the
+// words fetched meanwhile (escapes) loads the next ones at the refill. 1M x 56 uniform values, blocks of
+// 512, with rings that stayed empty once they had been outrun and with these: 14 bits 492 -> 357 us,
+// 20 bits 829 -> 629, 31 bits (escapes) 763 -> 579. Positions are clamped to the block's words; a block
+// that reads past them is rejected by the number of bits it took.
 constexpr uint32_t RLGR_RING = 16, RLGR_FETCH = 8;
 
 struct RlgrDec {
@@ -325,15 +329,24 @@ struct RlgrDec {
 #pragma unroll
         for (uint32_t i = 0; i < RLGR_FETCH; ++i) x[i] = at(hi + i);
     }
-    __device__ void refill(const uint32_t (&x)[RLGR_FETCH])
+    // The values until the next refill (the same for the whole wave).
+    __device__ uint32_t step() const
     {
-        if (rp > hi) {
-            hi = rp;  // (outran the ring: it starts again at the next word)
-        } else if (hi - rp <= RLGR_RING - RLGR_FETCH) {
-#pragma unroll
-            for (uint32_t i = 0; i < RLGR_FETCH; ++i) ring[((hi + i) % RLGR_RING) * RLGR_THREADS] = x[i];
-            hi += RLGR_FETCH;
+        const int32_t ahead = (int32_t)(hi - rp);
+        if (!__any(ahead <= (int32_t)RLGR_FETCH)) return RLGR_STEP;
+        return __any(ahead <= (int32_t)RLGR_FETCH / 2) ? RLGR_STEP / 4 : RLGR_STEP / 2;
+    }
+    __device__ void refill(uint32_t (&x)[RLGR_FETCH])  // (x: the words from hi on)
+    {
+        const int32_t ahead = (int32_t)(hi - rp);
+        if (ahead > (int32_t)(RLGR_RING - RLGR_FETCH)) return;  // (no room)
+        if (ahead <= -(int32_t)RLGR_FETCH) {                    // (all of them taken already)
+            hi = rp;
+            fetch(x);
         }
+#pragma unroll
+        for (uint32_t i = 0; i < RLGR_FETCH; ++i) ring[((hi + i) % RLGR_RING) * RLGR_THREADS] = x[i];
+        hi += RLGR_FETCH;
     }
     __device__ __attribute__((always_inline)) void take(uint32_t n)  // n <= 32 bits
     {
@@ -457,18 +470,21 @@ __global__ __launch_bounds__(RLGR_THREADS) void k_rlgr_decode(RlgrDecArgs a)
         GAS char *dst = reinterpret_cast<GAS char *>(gp(a.q) + k.ubase);
         const uint32_t pitch = 4u * a.C;
         uint32_t off = k.off;
-        for (uint32_t i = 0; i < k.lmax; i += RLGR_STEP) {
+        for (uint32_t i = 0, n; i < k.lmax; i += n) {
+            n = dec.step();
             uint32_t x[RLGR_FETCH];
             dec.fetch(x);
-            if (k.L && i + RLGR_STEP <= k.lmin) {
-#pragma unroll 4
-                for (int u = 0; u < RLGR_STEP; ++u) {
-                    *reinterpret_cast<GAS int32_t *>(dst + off) = dec.value();
-                    off += pitch;
+            if (k.L && i + n <= k.lmin) {
+                for (uint32_t u0 = 0; u0 < n; u0 += RLGR_STEP / 4) {
+#pragma unroll
+                    for (int u = 0; u < RLGR_STEP / 4; ++u) {
+                        *reinterpret_cast<GAS int32_t *>(dst + off) = dec.value();
+                        off += pitch;
+                    }
                 }
             } else {  // (past the wave's shortest block: the last block row, which is shorter)
 #pragma unroll 1
-                for (uint32_t u = 0; u < (uint32_t)RLGR_STEP; ++u) {
+                for (uint32_t u = 0; u < n; ++u) {
                     if (i + u < k.L) {
                         *reinterpret_cast<GAS int32_t *>(dst + off) = dec.value();
                         off += pitch;

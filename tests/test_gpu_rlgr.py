@@ -139,6 +139,18 @@ def test_corrupt_streams_are_reported():
     assert status(bad) == 5
 
 
+@pytest.mark.parametrize("bits", [14, 17, 20, 25, 32])
+def test_dense_blocks_after_sparse_ones(bits):
+    """Values of about `bits` bits (more code words in a step than a refill brings; 25 and 32: escapes),
+    zeros, and both by turns within a block and between the channels of a wave."""
+    rng = np.random.default_rng(bits)
+    dense = rng.integers(-(1 << (bits - 1)), 1 << (bits - 1), size=(1100, 9))
+    turns = dense * ((np.arange(1100)[:, None] // 40 + np.arange(9)) % 3 > 0)
+    for Q in (dense, turns, np.where(np.arange(9) % 2 > 0, dense, 0)):
+        check(Q.astype(np.int32), 512)
+    check(np.tile(turns, (1, 7)).astype(np.int32), 400)
+
+
 def test_table_claiming_more_words_than_32_bits_of_code_count():
     """A block of one word whose table claims 2^27 + 1 (2^32 + 32 bits) in a stream that is that long."""
     dev = _dev()
