@@ -93,6 +93,30 @@ def test_largest_chunks_and_extreme_tables():
     assert f[255] == 1 and f[0] == 4095
 
 
+@pytest.mark.parametrize("K", [2, 64])
+@pytest.mark.parametrize("waves", [511, 512, 513, 1300])
+def test_waves_around_the_counted_ones(K, waves):
+    """Launches of up to 512 waves count them and end themselves, longer ones end in a launch of their
+    own; a damaged byte is reported by both."""
+    dev = _dev()
+    n = (waves - 1) * 64 * K + 1
+    rng = np.random.default_rng(n)
+    data = np.minimum(rng.geometric(0.05, size=n), 256).astype(np.uint8)
+    blob = np.frombuffer(_roundtrip(data, K), dtype=np.uint8).copy()
+    nc = -(-n // K)
+    blob[32 + 512 + 4 * (nc + 1) + 1] ^= 0x40  # the first chunk's state
+    _, info = gsc.rans_decode(torch.from_numpy(blob).to(dev), n, K)
+    torch.cuda.synchronize()
+    assert int(info[0].item()) == 5
+
+
+@pytest.mark.parametrize("n", [(512 << 14) - 5, (512 << 14) + 1])
+def test_histograms_around_the_counted_ones(n):
+    """16 KB a histogram workgroup: the last of up to 512 makes the table, beyond a launch of its own."""
+    rng = np.random.default_rng(n)
+    _roundtrip(np.minimum(rng.geometric(0.2, size=n), 256).astype(np.uint8), 1 << 14)
+
+
 def test_empty_input():
     _roundtrip(np.zeros(0, dtype=np.uint8), 128)
 
