@@ -429,10 +429,10 @@ __device__ inline void put_bytes(P src0, uint32_t so, uint64_t dst, uint32_t m)
     for (uint32_t k = h + 4 * nw; k < m; ++k) *reinterpret_cast<GAS uint8_t *>(dst + k) = src0[so + k];
 }
 
-// Thread t of a wave codes chunk (wave index) per + t (per chunks a wave) into its scratch area, or
-// (STAGED) into LDS; the wave's chunks find their offsets by look-back, and each thread copies its
-// bytes to their place.
-template <bool STAGED>
+// Thread t of a wave codes chunk (wave index) per + t (per chunks a wave); the wave's chunks find their
+// offsets by look-back, and each thread copies its bytes to their place. IN_LDS: the input comes from
+// a copy in LDS; OUT_LDS: the code is made in LDS too, else in the chunk's scratch area.
+template <bool IN_LDS, bool OUT_LDS>
 __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
 {
     extern __shared__ gi4 s_dyn[];
@@ -443,15 +443,15 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
     const uint32_t lane = lane_id();
     const uint32_t c = blockIdx.x * a.per + lane;
     const bool mine = lane < a.per && c < a.nc;
-    const uint32_t S = STAGED ? a.out_stride : (uint32_t)a.tmp_stride;  // the chunk's area, its bytes at the end
+    const uint32_t S = OUT_LDS ? a.out_stride : (uint32_t)a.tmp_stride;  // the chunk's area, its bytes at the end
     GAS uint8_t *tmp = gp(a.tmp) + (uint64_t)c * a.tmp_stride;
     uint32_t m = 0;  // bytes of this chunk
-    // staged: the wave's chunks are consecutive, so one copy holds all their bytes (made by every
-    // lane, also those without a chunk); the chunks' areas follow it
+    // the wave's chunks are consecutive, so one copy holds all their bytes (made by every
+    // lane, also those without a chunk); the chunks' areas in LDS follow it
     uint8_t *s_in = reinterpret_cast<uint8_t *>(s_dyn);
     LAS uint8_t *s_out = (LAS uint8_t *)s_in + a.stage + lane * a.out_stride;
     uint64_t sb = 0;
-    if (STAGED) {
+    if (IN_LDS) {
         const uint64_t lo = reinterpret_cast<uint64_t>(a.in), hi = lo + a.n;
         const uint64_t w0 = lo + (uint64_t)blockIdx.x * a.per * a.K;
         sb = stage_blocks(s_in, w0, min(w0 + (uint64_t)a.per * a.K, hi), lo, hi, reinterpret_cast<uint64_t>(a.ws));
@@ -465,11 +465,11 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
         EncState E = {RANS_L, 0, S, 0, false};
         EncLds L = {RANS_L, s_out + S, false};
         auto block8 = [&](uint64_t q) -> uint2 {
-            if (STAGED) return *reinterpret_cast<const uint2 *>(s_in + (q - sb));
+            if (IN_LDS) return *reinterpret_cast<const uint2 *>(s_in + (q - sb));
             return in_block8(q, lo, hi, safe);
         };
         auto step = [&](const uint4 &t) {
-            if (STAGED) enc_step(L, t);
+            if (OUT_LDS) enc_step(L, t);
             else enc_step(E, t, tw);
         };
         // the chunk's 8-byte blocks from the last down, the next one loaded before this one is coded
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
             cur = nxt;
         }
         // the final state, low byte emitted first (stored most significant first)
-        if (STAGED) {
+        if (OUT_LDS) {
             L.pos -= 4;
             reinterpret_cast<LAS RansFour *>(L.pos)->v = __builtin_bswap32(L.x);
             m = S - (uint32_t)(L.pos - s_out);
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
             }
             if (E.na > 0) tw[E.top / 4 - 1] = (uint32_t)(E.acc << (8 * (4 - E.na)));
         }
-        if (STAGED ? L.bad : E.bad) rans_error(a.ws, GSC_ERR_INTERNAL);  // (impossible with the stream's own table)
+        if (OUT_LDS ? L.bad : E.bad) rans_error(a.ws, GSC_ERR_INTERNAL);  // (impossible with the stream's own table)
     }
     // the chunks' offsets: a scan over the wave, then the look-back over the waves
     const uint64_t incl = wave_incl_scan((uint64_t)m), wave_total = read_lane(incl, (uint32_t)(WAVE - 1));
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(RANS_THREADS) void k_rans_encode(RansArgs a)
         } else {
             offs[c] = (uint32_t)first;
             const uint64_t dst = reinterpret_cast<uint64_t>(a.out) + d0 + first;
-            if (STAGED) put_bytes<const LAS uint8_t *, const LAS uint32_t *>(s_out, S - m, dst, m);
+            if (OUT_LDS) put_bytes<const LAS uint8_t *, const LAS uint32_t *>(s_out, S - m, dst, m);
             else put_bytes<const GAS uint8_t *, const GAS uint32_t *>(tmp, S - m, dst, m);
         }
     }
@@ -818,6 +818,19 @@ static bool stage_fits(size_t dyn, size_t stat)
     return dyn + stat <= (size_t)lim;
 }
 
+// Workgroups of one wave with that much LDS that fit the device at once, and on one CU of it.
+constexpr size_t LDS_GRANULE = 1280;  // bytes in which a CU's LDS is given out
+static bool waves_resident(size_t lds_bytes, uint64_t *on_device, uint32_t *on_cu)
+{
+    int dev = 0, lds = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess) return false;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
+    *on_cu = (uint32_t)((size_t)lds / ((lds_bytes + LDS_GRANULE - 1) / LDS_GRANULE * LDS_GRANULE));
+    *on_device = (uint64_t)cus * *on_cu;
+    return true;
+}
+
 static RansArgs rans_args(uint64_t n, uint32_t K, uint32_t *ws)
 {
     RansArgs a;
@@ -845,27 +858,41 @@ hipError_t launch_rans_encode(const uint8_t *in, uint64_t n, uint32_t K, uint8_t
         hipLaunchKernelGGL(k_rans_empty, dim3(1), dim3(WAVE), 0, s, a, 0);
         return hipGetLastError();
     }
-    // Staged, a wave's input (per K bytes) and its chunks' code (2 K + 4 each at most) lie in LDS: 64
-    // chunks up to K = 512 (103 KB), 32 up to 1024. Twice as many waves then take look-back words,
-    // which lie in the chunks' scratch areas (unused by the staged kernel).
+    // With the code made in LDS, a wave's input (per K bytes) and its chunks' code (2 K + 4 each at most)
+    // lie there: 64 chunks up to K = 512 (103 KB), 32 up to 1024. Twice as many waves then take look-back
+    // words, which lie in the chunks' scratch areas (unused by that kernel). Its steps are the shorter
+    // ones, but it leaves room for few waves on a CU: it is taken where the launch's waves are all
+    // resident at once, or at least eight on a CU; with fewer a second round of waves costs what the
+    // first did. Encode calls, code in LDS against in scratch areas, us: K = 512 (one wave a CU), 8 MB
+    // (245 waves) 62 and 89, 10 MB (306) 101 and 95, 28 MB 201 and 125; K = 256 (two), 8 MB (489) 54 and 67,
+    // 10 MB (611) 78 and 69, 28 MB 158 and 110; K = 96 (six), 8 MB (1303) 53 and 54, 14 MB (2279) 87 and 78;
+    // K = 64 (nine), 8 MB 53 and 56, 28 MB (6836) 133 and 160.
     a.per = K <= RANS_STAGE_K / 2 ? RANS_THREADS : RANS_THREADS / 2;
     a.out_stride = (2 * K + 4 + 7) / 8 * 8;
     a.stage = (a.per * K + 32 + 15) / 16 * 16;
-    const size_t lds = a.stage + (size_t)a.per * a.out_stride;
-    const bool staged = K <= RANS_STAGE_K && stage_fits(lds, 256 * sizeof(uint4));
+    const size_t table = 256 * sizeof(uint4);
+    size_t lds = a.stage + (size_t)a.per * a.out_stride;
+    uint64_t on_device = 0;
+    uint32_t on_cu = 0;
+    const bool out_lds = K <= RANS_STAGE_K && stage_fits(lds, table) && waves_resident(lds + table, &on_device, &on_cu) &&
+                         (on_cu >= 8 || (a.nc + (uint64_t)a.per - 1) / a.per <= on_device);
     uint32_t zw = (uint32_t)rans_head_words(a.nc);
-    if (!staged) {
+    if (!out_lds) {
         a.per = RANS_THREADS;
+        a.stage = (uint32_t)RANS_THREADS * K + 32;
+        lds = a.stage;
     } else if (a.per < (uint32_t)RANS_THREADS) {
         a.status = reinterpret_cast<uint64_t *>(a.tmp);
         zw = (uint32_t)(rans_tmp_off(a.nc) / 4) + 2 * ((a.nc + a.per - 1) / a.per);
     }
+    const bool in_lds = K <= RANS_STAGE_K && stage_fits(lds, table);
     const dim3 g((a.nc + a.per - 1) / a.per);
     hipLaunchKernelGGL(k_rans_zero, dim3(min((zw + 255) / 256, 1024u)), dim3(256), 0, s, a.ws, zw);
     hipLaunchKernelGGL(k_rans_hist, dim3(a.hblocks), dim3(RANS_HIST_THREADS), 0, s, a);
     if (a.hblocks > RANS_COUNTED) hipLaunchKernelGGL(k_rans_table, dim3(1), dim3(WAVE), 0, s, a);
-    if (staged) hipLaunchKernelGGL(k_rans_encode<true>, g, dim3(RANS_THREADS), lds, s, a);
-    else hipLaunchKernelGGL(k_rans_encode<false>, g, dim3(RANS_THREADS), 0, s, a);
+    if (out_lds) hipLaunchKernelGGL((k_rans_encode<true, true>), g, dim3(RANS_THREADS), lds, s, a);
+    else if (in_lds) hipLaunchKernelGGL((k_rans_encode<true, false>), g, dim3(RANS_THREADS), lds, s, a);
+    else hipLaunchKernelGGL((k_rans_encode<false, false>), g, dim3(RANS_THREADS), 0, s, a);
     if (g.x > RANS_COUNTED) hipLaunchKernelGGL(k_rans_info, dim3(1), dim3(WAVE), 0, s, a, 0);
     return hipGetLastError();
 }

@@ -117,6 +117,16 @@ def test_histograms_around_the_counted_ones(n):
     _roundtrip(np.minimum(rng.geometric(0.2, size=n), 256).astype(np.uint8), 1 << 14)
 
 
+@pytest.mark.parametrize("K,waves,chunks", [(64, 2304, 64), (96, 1536, 64), (512, 256, 64), (600, 512, 32), (1024, 256, 32)])
+@pytest.mark.parametrize("more", [0, 1, 777])
+def test_inputs_around_the_waves_of_one_round(K, waves, chunks, more):
+    """Encoding makes the code in LDS while the waves of a launch fit the chip at once (256 compute
+    units), in scratch areas beyond."""
+    n = waves * chunks * K + more
+    rng = np.random.default_rng(n)
+    _roundtrip(np.minimum(rng.geometric(0.03, size=n), 256).astype(np.uint8), K)
+
+
 def test_empty_input():
     _roundtrip(np.zeros(0, dtype=np.uint8), 128)
 
