@@ -441,8 +441,11 @@ struct RlgrDecArgs {
     uint32_t *err;   // [0] device error, [1] workgroups done
 };
 
-// Decodes a wave's block rows, every thread one block, whole matrix rows stored at each step. The
-// last workgroup to end writes the info words.
+// Decodes a wave's block rows, every thread one block, whole matrix rows stored at each step. The last
+// of at most RLGR_COUNTED workgroups to end writes the info words; of more, a launch of its own does
+// (the additions to one word come 9 ns apart, a launch costs 4.5 us): 1M x 56 in blocks of 16 (62500
+// waves) counted 729 us, not counted 127; of 64 216 and 132, of 512 (1954) 235 and 225.
+constexpr uint32_t RLGR_COUNTED = 512;
 __global__ __launch_bounds__(RLGR_THREADS) void k_rlgr_decode(RlgrDecArgs a)
 {
     __shared__ uint32_t s_ring[RLGR_RING * RLGR_THREADS];
@@ -496,9 +499,18 @@ __global__ __launch_bounds__(RLGR_THREADS) void k_rlgr_decode(RlgrDecArgs a)
         ok = k.L == 0 || dec.ends(nw);
     }
     if (!ok) atomicCAS(a.err, 0u, (uint32_t)GSC_ERR_CORRUPT_STREAM);
+    if (gridDim.x > RLGR_COUNTED) return;
     // the wave's error report has completed before it is counted (device-scope atomics throughout)
     __builtin_amdgcn_s_waitcnt(0);
     if (tid == 0 && __hip_atomic_fetch_add(a.err + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x) {
+        a.info[0] = (int32_t)__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        a.info[1] = (int32_t)a.nv;
+    }
+}
+
+__global__ __launch_bounds__(64) void k_rlgr_dec_info(RlgrDecArgs a)
+{
+    if (threadIdx.x == 0) {
         a.info[0] = (int32_t)__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         a.info[1] = (int32_t)a.nv;
     }
@@ -558,9 +570,10 @@ hipError_t launch_rlgr_decode(const uint8_t *in, uint64_t in_bytes, uint32_t nv,
         hipLaunchKernelGGL(k_rlgr_dec_empty, dim3(1), dim3(64), 0, s, a);
         return hipGetLastError();
     }
-    const uint32_t rpw = rl_rows(C);
+    const uint32_t rpw = rl_rows(C), nwg = (a.nb + rpw - 1) / rpw;
     hipLaunchKernelGGL(k_rlgr_zero, dim3(1), dim3(256), 0, s, ws, 1u);
-    hipLaunchKernelGGL(k_rlgr_decode, dim3((a.nb + rpw - 1) / rpw), dim3(RLGR_THREADS), 0, s, a);
+    hipLaunchKernelGGL(k_rlgr_decode, dim3(nwg), dim3(RLGR_THREADS), 0, s, a);
+    if (nwg > RLGR_COUNTED) hipLaunchKernelGGL(k_rlgr_dec_info, dim3(1), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 

@@ -151,6 +151,21 @@ def test_dense_blocks_after_sparse_ones(bits):
     check(np.tile(turns, (1, 7)).astype(np.int32), 400)
 
 
+@pytest.mark.parametrize("waves", [511, 512, 513])
+def test_waves_around_the_counted_ones(waves):
+    """Decoding launches of up to 512 waves count them and end themselves, longer ones end in a launch of
+    their own; a damaged table is reported by both."""
+    dev = _dev()
+    Q = laplace_matrix(2 * waves, 40, seed=waves)
+    check(Q, 2)
+    s = gsc.rlgr_encode(torch.from_numpy(Q).to(dev), 2).check()
+    bad = s.buf[:s.nbytes()].clone()
+    bad[32:].view(torch.int32)[7] += 1
+    _, info = gsc.rlgr_decode(bad, 2 * waves, 40, 2)
+    torch.cuda.synchronize()
+    assert int(info[0].item()) == 5 and int(info[1].item()) == 2 * waves
+
+
 def test_table_claiming_more_words_than_32_bits_of_code_count():
     """A block of one word whose table claims 2^27 + 1 (2^32 + 32 bits) in a stream that is that long."""
     dev = _dev()
