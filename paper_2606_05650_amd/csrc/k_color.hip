@@ -147,17 +147,24 @@ __device__ inline void wsync()
 }
 
 // The rotation (c, s) that zeroes A[p][q] (the smaller angle of the symmetric Schur decomposition of
-// Golub and Van Loan: t = tan = 2 apq sgn(d) / (|d| + sqrt(d^2 + 4 apq^2)), d = aqq - app), apq != 0. The
-// angle is taken in FP32 (of d and 2 apq scaled to their larger exponent), c = 1 / sqrt(1 + t^2) then to
-// FP64 round-off by two Newton steps, s = t c: the rotation is orthogonal to FP64, and an angle off
-// by 1e-7 of itself leaves 1e-7 of A[p][q] for the next sweep. It has no FP64 division or square root.
+// Golub and Van Loan: t = tan = e sgn(d) / (|d| + sqrt(d^2 + e^2)), d = aqq - app, e = 2 apq), apq != 0,
+// without an FP64 division or square root: t begins in FP32 (of d and e scaled to their larger
+// exponent) and is brought to FP64 round-off by two Newton steps on e t^2 + 2 d t - e = 0 (whose slope
+// 2 (e t + d) is twice sqrt(d^2 + e^2) in size, at least 1, and is divided by in FP32: each step takes six
+// digits off the error), c = 1 / sqrt(1 + t^2) likewise, s = t c. (With t left in FP32 the 1M-row forward and
+// inverse take 294 us in place of 299, before either 340.)
 __device__ inline void jacobi_rotation(double app, double aqq, double apq, double &c, double &s)
 {
     const double d = aqq - app, e = 2.0 * apq;
     const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(e)));
-    const float x = (float)__builtin_amdgcn_ldexp(d, -ex), y = (float)__builtin_amdgcn_ldexp(e, -ex);
-    const float t = (x < 0.f ? -y : y) * __builtin_amdgcn_rcpf(fabsf(x) + __builtin_amdgcn_sqrtf(x * x + y * y));
-    const double T = (double)t, h = 1.0 + T * T;
+    const double D = __builtin_amdgcn_ldexp(d, -ex), E = __builtin_amdgcn_ldexp(e, -ex);
+    const float x = (float)D, y = (float)E, root = __builtin_amdgcn_sqrtf(x * x + y * y);
+    const float t = (x < 0.f ? -y : y) * __builtin_amdgcn_rcpf(fabsf(x) + root);
+    const double g = (double)__builtin_amdgcn_rcpf(x < 0.f ? -2.f * root : 2.f * root);  // (1 / slope)
+    double T = (double)t;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) T -= g * fma(E, fma(T, T, -1.0), 2.0 * D * T);
+    const double h = fma(T, T, 1.0);
     double r = (double)__builtin_amdgcn_rsqf((float)h);
 #pragma unroll
     for (int i = 0; i < 2; ++i) r = r * (1.5 - 0.5 * h * r * r);
