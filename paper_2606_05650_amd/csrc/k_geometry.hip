@@ -565,7 +565,8 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_pass(TileMap m, int pass)
         const uint32_t c = lane < 2u * NW ? s_tmp[lane] : 0u, wi = wave_incl_scan(c);
         const uint32_t wu = __builtin_amdgcn_readfirstlane(w);
         hist_excl = read_lane(wi - c, wu) + ih - vh;
-        if (dig) s_lstart[d] = read_lane(wi - c, NW + wu) - read_lane(wi, NW - 1) + ic - tile_cnt;
+        const uint32_t before = read_lane(wi - c, NW + wu) - read_lane(wi, NW - 1);
+        if (dig) s_lstart[d] = before + ic - tile_cnt;
     }
     __syncthreads();
     // keys to LDS in tile-local digit order: the keys leave the registers before the look-back,
@@ -860,7 +861,8 @@ __global__ __launch_bounds__(OCC_THREADS) void k_occupancy(TileMap m)
     if (tid / WAVE == OCC_THREADS / WAVE - 1) {
         const uint32_t lane = lane_id();
         const uint32_t hd = lane <= J ? cp(ctrl)->hist_D[lane] : 0u;  // (written by the dedup kernel)
-        const uint64_t size = lane < J ? (uint64_t)wave_incl_scan(hd) : 0ull;
+        const uint32_t heads = wave_incl_scan(hd);
+        const uint64_t size = lane < J ? heads : 0u;
         const uint64_t incl = wave_incl_scan(size);
         const uint64_t off = GSC_HEADER_BYTES + incl - size;
         if (lane <= J) s_off[lane] = off;
