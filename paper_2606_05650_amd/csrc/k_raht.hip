@@ -1004,7 +1004,9 @@ __device__ inline void done_add(GAS uint32_t *c, uint32_t v)
     __syncthreads();
     if (threadIdx.x == 0 && v) __hip_atomic_fetch_add(c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// The flag, in UP_FLAG_COPIES copies on lines of their own (after the words that the schedules use), that
+// The flag, in UP_FLAG_COPIES copies on lines of their own (after the words that the schedules use: a group
+// of at most UP_FLAG_WORD workgroups builds them, in the forward launch too, whose call may run the
+// inverse after it), that
 // S_2's inverse items are all done: the first-level workgroups wait on it rather than on the counter,
 // whose line the last items' additions would otherwise share with the loads of hundreds of waiters.
 constexpr uint32_t UP_FLAG_COPIES = 8, UP_FLAG_WORD = 512, UP_FLAG_STRIDE = 64;
@@ -1685,8 +1687,8 @@ __global__ __launch_bounds__(RAHT_THREADS) __attribute__((amdgpu_waves_per_eu(PE
     const uint32_t tid = threadIdx.x, items = m.start[m.F];
     // ---- the upper levels' schedules, by the first Gp workgroups
     uint32_t Gp = 0;
-    if (kmax >= 2) {
-        Gp = min(level_items(m, 2, 1, s_fs), gridDim.x);
+    if (kmax >= 2) {  // (their flags end where the inverse's flag copies begin, which are not cleared in between)
+        Gp = min(level_items(m, 2, 1, s_fs), min(gridDim.x, UP_FLAG_WORD));
         if (blockIdx.x < Gp) up_prelude_group(m, kmax, Gp, s_fs, *reinterpret_cast<PreScratch<PRE_EPT_UP> *>(s_y), ctr_word(m, PRE_DONE));
     }
     Frame1 fc(m);
