@@ -412,3 +412,31 @@ def test_rd_loss_without_a_private_name_of_torch(monkeypatch, where, name):
     monkeypatch.undo()
     for x, z in zip(got, want):
         assert abs(float(x) - float(z)) <= 1e-5 * abs(float(z))
+
+
+@pytest.mark.parametrize("n,C", [(3000, 56), (3000, 11), (257, 5), (1, 3)])
+@pytest.mark.parametrize("bad", [False, True])
+def test_padded_layer_clears_what_the_kernels_leave(n, C, bad):
+    """Rows past the voxel count are zero whatever the memory held, with rows of whole 16-byte pieces and
+    without; after a device-detected error (a position that is not finite) every row is, the count is
+    0 and the distortion NaN."""
+    from paper_2606_05650_amd.ste import SteCoderPadded, rd_loss
+    dev = _dev()
+    print(f"case n={n} C={C} bad={bad} padded layer", flush=True)
+    pos, attr = synth.make_duplicates_frame(n, seed=n + C, grid=8)
+    attr = np.ascontiguousarray(attr[:, :C])
+    p = gsc.make_params(4, C, GROUPED[:C])
+    nv = orc.ste_grad(pos, attr, 4, GROUPED[:C], 0.5, 0.01)["nv"]
+    tp = torch.from_numpy(pos).to(dev)
+    if bad:
+        tp[n // 2, 1] = float("nan")
+        nv = 0
+    ta = torch.from_numpy(attr).to(dev).requires_grad_(True)
+    dirty = [torch.full((n, C), float("nan"), device=dev) for _ in range(16)]
+    del dirty
+    y, a, r, nvt = SteCoderPadded.apply(ta, tp, p)
+    assert int(nvt.item()) == nv and (nv < n or n == 1)
+    for t in (y, a, r):
+        assert t.shape == (n, C) and not t[nv:].any() and bool(t[:nv].isfinite().all())
+    dist = rd_loss(y, a, r, torch.from_numpy(GROUPED[:C]).to(dev), 0.01, nv=nvt)[1]
+    assert bool(dist.isnan()) == bad
