@@ -53,11 +53,12 @@ constexpr int OCC_VPT = 2;              // voxels per thread
 constexpr int OCC_TILE = OCC_THREADS * OCC_VPT;
 
 constexpr int DEC_TILE = 4096;          // decoder: occupancy bytes per tile
-// Threads of a tile. A call's tiles (about 3.5 bytes per voxel) that number at most the compute units are
-// latency: 1024 threads with 4 bytes each (100K voxels: decode 91 -> 84 us); beyond, 256 threads with 16
-// bytes each keep more tiles resident (1M voxels: decode 246 us, with 1024 threads 258).
+// Threads of a tile. 1024 with 4 bytes each are the shorter chain (decode of 20K voxels 65 us against
+// 72 with 256 threads, 100K 79 and 86, 262K 103 and 109, 350K 124 and 128) while a call's tiles (about 3.5
+// bytes per voxel) are all resident, two to a CU; beyond, 256 threads with 16 bytes each keep
+// more tiles resident (500K 148 either way, 700K 178 against 183 with 1024 threads, 1M 238 and 248, 4M 755 and 813).
 constexpr int DEC_WIDE = 1024, DEC_NARROW = 256;
-constexpr int64_t DEC_WIDE_MAX = 1 << 18;  // voxels (the frames' capacities together)
+constexpr int64_t DEC_WIDE_MAX = 1 << 19;  // voxels (the frames' capacities together)
 
 constexpr int RT = 512;                 // RAHT tile: entries (eight 64-entry wave chunks)
 constexpr int RAHT_THREADS = 512;       // one wave per chunk

@@ -253,3 +253,24 @@ def test_adjoint_inverts_the_forward_over_the_upper_level_paths(nv, C):
     # (orthonormal: the energy is kept)
     e = (Y.double().square().sum() / A.double().square().sum()).item()
     assert abs(e - 1.0) <= 1e-5
+
+
+@pytest.mark.parametrize("J", [1, 9])
+def test_decoding_at_the_capacity_where_the_octree_tiles_change(J):
+    """Capacities of up to 2^19 voxels expand the octree with 1024 threads a tile, larger ones with 256:
+    the same stream decodes to the same frame, bit for bit."""
+    dev = torch.device("cuda:0")
+    pos, attr = synth.make_frame(9000, seed=J)
+    C = 5
+    print(f"case J={J} decode capacities", flush=True)
+    e = gsc.encode_frame(torch.from_numpy(pos).to(dev), torch.from_numpy(np.ascontiguousarray(attr[:, :C])).to(dev),
+                         gsc.make_params(J, C, synth.quant_steps(synth.STEPS_GROUPED)[:C])).check()
+    nv = e.n_vox()
+    got = []
+    for cap in (nv, 1 << 19, (1 << 19) + 1):
+        d = gsc.decode_frame(e.stream, J, C, cap, want_vox=True)
+        torch.cuda.synchronize()
+        assert int(d.info[0].item()) == 0 and int(d.info[1].item()) == nv
+        got.append([t[:nv].clone() for t in (d.pos, d.attr, d.vox)])
+    for other in got[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(got[0], other))
