@@ -12,8 +12,8 @@
  *   enqueues work on that stream and returns; results are valid once the stream has been
  *   synchronized.
  * - Concurrency: calls on one device must not run at the same time on different streams. The
- *   transform launches that run the upper RAHT levels (the forward, and the inverse of the upper
- *   levels) keep all their workgroups resident and order the levels by waiting on one another;
+ *   transform launches (the forward and the inverse, which also run the upper RAHT levels) keep
+ *   all their workgroups resident and order the levels by waiting on one another;
  *   a concurrent call's kernels can take the slots they wait for, and the call then fails with
  *   GSC_ERR_INTERNAL after a bounded wait. Serialize calls on a
  *   device (one stream, or events between streams); frames coded together belong in one batch

@@ -239,8 +239,8 @@ gsc_status run_forward(const Frame *fr, int F, const RahtCfg &cfg, bool last, bo
     return GSC_OK;
 }
 
-// The inverse: the upper levels in one launch (which first builds their schedules when `prelude`
-// is set, i.e. when no forward of this workspace has built them), then the first level.
+// The inverse, every level in one launch, which also builds the upper levels' schedules when `prelude`
+// is set, i.e. when no forward of this workspace has built them.
 gsc_status run_inverse(const Frame *fr, int F, const RahtCfg &cfg, bool prelude, bool *ended, hipStream_t s)
 {
     const int K = max_K(fr, F);

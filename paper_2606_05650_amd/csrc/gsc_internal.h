@@ -70,16 +70,16 @@ constexpr int NCLS = RT / 64 + 1;       // merge classes: local to one wave chun
 constexpr int SEG_N = NLVL * NCLS + 1;  // per-tile (level, class) segment starts + total
 constexpr int LSTART_N = SEG_N + 1;     // padded to an even count of u16
 
-// Upper tiling levels (k >= 2) run as one persistent launch per phase (schedules, forward,
-// inverse) of at most UP_GRID_MAX workgroups, which order the levels through per-workgroup
-// phase flags.
+// The upper tiling levels (k >= 2) run inside the transform launches, ordered through UP_GRID_MAX flag
+// words (the phases of the workgroups that build the levels' schedules, or the inverse's tile
+// counters, in the lower half; the inverse's flag copies in the upper one).
 constexpr uint32_t UP_GRID_MAX = 1024;
-constexpr uint32_t PHASE_PRELUDE = 0;  // flag base of the schedule launch
+constexpr uint32_t PHASE_PRELUDE = 0;  // flag base of the schedules
 // Counters of the transform launches, in DONE_WORDS words after the flags, zeroed by every
 // call: the finished items of every tiling level (forward: DONE_FWD + k, inverse: DONE_INV + k),
 // the upper items' tickets of the forward (TK_UPF), the workgroups done with the upper levels'
-// schedules (PRE_DONE), and the workgroups that have ended the first-level forward and inverse
-// launches (FIN_FWD, FIN_INV).
+// schedules (PRE_DONE), and the workgroups that have ended the forward and inverse launches (FIN_FWD,
+// FIN_INV).
 constexpr uint32_t DONE_WORDS = 128, DONE_FWD = 0, DONE_INV = 32, TK_UPF = 80, PRE_DONE = 81, FIN_FWD = 82,
                    FIN_INV = 83;
 static_assert(MAXK + 1 <= 32, "one completion counter per tiling level and direction");

@@ -291,7 +291,7 @@ __device__ inline void bbox_partial(const float *pos_, uint32_t n, uint32_t b, u
         }
     }
     // order-preserving uints (so that -0 < +0 as in an ordered comparison), reduced per wave
-    // with shuffles, then across the waves in LDS
+    // with lane moves, then across the waves in LDS
     constexpr int NW = BBOX_THREADS / WAVE;
     __shared__ uint32_t s_o[NW][7];
     const uint32_t w = threadIdx.x / WAVE;
@@ -966,7 +966,7 @@ __device__ inline bool header_ok_wave(FD &fd, const CAS gsc_header *h)
 }
 
 // One pass over all occupancy bytes: tile t holds bytes [t DEC_TILE, (t + 1) DEC_TILE) of the
-// stream's occupancy section, striped (byte s + r DEC_THREADS + tid), and finds each byte's
+// stream's occupancy section, striped (byte s + r THREADS + tid), and finds each byte's
 // child slots with a decoupled look-back over the tiles' set-bit counts. Checks: no byte is 0,
 // and the first byte of every level is the parent of the first node of the next level (its prefix
 // equals Q(d + 1)), and the bytes hold exactly |L_1| + ... + |L_J| set bits.

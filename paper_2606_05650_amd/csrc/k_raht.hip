@@ -508,14 +508,15 @@ hipError_t launch_prelude(const TileMap &m, int k, hipStream_t s)
     return hipGetLastError();
 }
 
-// ------------------------------------------------- upper levels: one persistent launch each
+// ------------------------------------- upper levels: inside the persistent transform launches
 // The upper sequences are small and their true sizes are known only on the device (the bound of
 // 6J + 2 open entries per tile is far above what real frames leave), so a launch per level and
-// per worst-case tile would mostly start idle workgroups. Instead one launch of G resident
-// workgroups visits the levels in order; at each level workgroup b takes the level's items
-// b, b + G, ... (items over all frames of the launch, frame by frame), and the levels are
-// ordered with per-workgroup phase flags. Item counts never grow from one level to the next
-// (S_{k+1} is a subset of S_k's entries), so workgroups beyond a level's count leave.
+// per worst-case tile would mostly start idle workgroups. Instead the resident workgroups of the
+// forward and of the inverse launch take the upper levels' items too (items over all frames of the
+// launch, frame by frame): the forward after its first-level items, the inverse before them.
+// Levels are ordered with completion counters, and where a group of workgroups builds all schedules
+// (up_prelude_group) with a phase flag per workgroup. Item counts never grow from one level to the
+// next (S_{k+1} is a subset of S_k's entries).
 
 // Items of level k over the frames of the launch (each frame: its tiles of S_k times np), with
 // the frames' first items in s_fs[0..F]; uniform. lvl_n[k], k >= 3, is read with device-coherent
@@ -1519,9 +1520,10 @@ __device__ inline void inv_up_item(const TileMap &m, uint32_t f, int k, uint32_t
 // are known when its loads are issued.
 // What bounds it is the rate of line requests of the sliced rows: a plain gather of 224-byte rows in two
 // 112-byte slices by as many workgroups takes 605 us at 4M rows and 123 us at 1M, of whole rows 410 and
-// 87 (this level: about 560 and 150, merges and quantizer included). Whole rows of a tile need twice the
-// LDS (one workgroup per CU, nothing to overlap its phases with) or tiles of 256 entries (tried with one
-// wave per chunk: 4M 1165 us against 1113, 1M 410 against 374; too few waves for the merges' latency).
+// 87 (this level: about 560 and 150, merges and quantizer included). Whole rows were tried in tiles of
+// 256 entries with one wave per chunk (4M 1165 us against 1113, 1M 410 against 374; eight waves a CU are
+// too few for the merges' latency); a 512-entry tile of whole rows needs the LDS of both workgroups of
+// a CU, and with sixteen waves for it has not been measured.
 // rows of a slice per thread: ceil(RT / floor(RT / CH4)), at most this for CH4 <= CH4_MAX1
 __host__ __device__ constexpr int rows_per_thread_max(int ch4max)
 {
