@@ -68,8 +68,8 @@ def alg_bytes(stage, n, nv, C):
 KERNEL_SOURCES = ("paper_2606_05650_amd/csrc/k_raht.hip", "paper_2606_05650_amd/csrc/gsc_device.h",
                   "paper_2606_05650_amd/csrc/gsc_internal.h")
 PMC_TRAFFIC = {"workload": "frame1M_J12",
-               "sources_sha256": "22fac2a4d02833184e319f62a3b67149132c3164f0380980a1957b33d1ecea90",
-               "raht_fwd1": 591519853, "raht_inv1": 481295317}
+               "sources_sha256": "2768fb33135679dc7afcf10b81339ad6a959d0668a7b0c7bdc07ad0e3a2c7132",
+               "raht_fwd1": 590953699, "raht_inv1": 481246382}
 KERNEL_NAMES = {"raht_fwd1": "k_raht_fwd", "raht_inv1": "k_raht_inv"}
 
 

@@ -19,7 +19,8 @@
 //
 // A chunk is a serial chain of K steps and a frame has few chunks (13.7 K of 256 bytes for the 3.5 MB
 // of a 1M frame: less than one wave per SIMD), so a step's latency bounds both directions. Chunks
-// of at most RANS_STAGE_K bytes are coded wholly from LDS, where the step is about 14 instructions:
+// of at most RANS_STAGE_K bytes are coded wholly from LDS (encoding: where the launch's waves are then still
+// resident at once), where the step is about 14 instructions:
 // the bytes that may follow are read (decode) or written (encode) two at a time at the byte
 // position, whether or not the step takes them, in parallel with the table lookup, and the state
 // is renormalised by one shift. 3.5 MB, chunks of 256: encoding 39 -> 26 us, decoding 59 -> 31 us (byte

@@ -22,7 +22,7 @@
 // always, so a branch costs both sides), a code of at most 31 (encoder) or 32 (decoder) bits is
 // handled as one word, and only longer codes (an escape, or a long quotient after a long run)
 // take a branch of their own. 1M x 56, blocks of 512: counting 294 -> 73 us (43 instructions per
-// value), writing 557 -> 150 us (about 95), decoding 1326 -> 235 us (about 135), against a coder that
+// value), writing 557 -> 150 us (about 95), decoding 1326 -> 229 us (about 135), against a coder that
 // branched on the mode, kept 64-bit bit buffers and (decoding) waited on a global load per word;
 // the matrix
 // (224 MB) and its code (22 MB) move at about a fifth of a copy's rate: issue slots bound all three.
