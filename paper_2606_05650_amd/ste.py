@@ -90,13 +90,15 @@ class _RdLoss(torch.autograd.Function):
     @staticmethod
     def forward(ctx, yhat, ahat, aref, steps, lam, nv):
         ctx.set_materialize_grads(False)
-        loss, dist, rate, ctx.count, diff = gsc.rd_loss_forward(yhat, ahat, aref, steps, lam, nv=nv)
-        if not ctx.needs_input_grad[1]:
-            ctx.mark_non_differentiable(dist, diff)
-        if not ctx.needs_input_grad[0]:
+        of_yhat, of_ahat = ctx.needs_input_grad[:2]
+        loss, dist, rate, ctx.count, diff = gsc.rd_loss_forward(yhat, ahat, aref, steps, lam, nv=nv, want_diff=of_ahat)
+        if not of_ahat:
+            ctx.mark_non_differentiable(dist)
+        if not of_yhat:
             ctx.mark_non_differentiable(rate)
         ctx.lam = lam
-        ctx.save_for_backward(yhat, diff, steps)
+        # (what a gradient does not read may change before the backward)
+        ctx.save_for_backward(yhat if of_yhat else None, diff, steps if of_yhat else None)
         return loss, dist, rate, diff
 
     @staticmethod

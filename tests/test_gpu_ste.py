@@ -440,3 +440,29 @@ def test_padded_layer_clears_what_the_kernels_leave(n, C, bad):
         assert t.shape == (n, C) and not t[nv:].any() and bool(t[:nv].isfinite().all())
     dist = rd_loss(y, a, r, torch.from_numpy(GROUPED[:C]).to(dev), 0.01, nv=nvt)[1]
     assert bool(dist.isnan()) == bad
+
+
+@pytest.mark.parametrize("which", ["yhat", "ahat"])
+def test_rd_loss_keeps_only_what_its_gradient_reads(which):
+    """With a gradient of ahat alone, yhat and the steps may be inference tensors or change before the
+    backward; with one of yhat alone, ahat and aref may."""
+    from paper_2606_05650_amd.ste import rd_loss
+    y, h, r, steps = _loss_inputs()
+    a, b, out = _leaves(_torch_rd_loss, torch.float64, y, h, r, steps)
+    out[0].backward()
+    want = (a if which == "yhat" else b).grad
+    with torch.inference_mode():
+        yi, hi, ri, si = (t.clone() for t in (y, h, r, steps))
+    for inference in (False, True):
+        leaf = (y if which == "yhat" else h).clone().requires_grad_(True)
+        if which == "yhat":
+            free = [hi, ri] if inference else [h.clone(), r.clone()]
+            loss = rd_loss(leaf, *free, steps, 0.01)[0]
+        else:
+            free = [yi, si] if inference else [y.clone(), steps.clone()]
+            loss = rd_loss(free[0], leaf, r, free[1], 0.01)[0]
+        if not inference:
+            for t in free:
+                t.zero_()
+        loss.backward()
+        assert (leaf.grad.double() - want).abs().max().item() <= 1e-6 * want.abs().max().item()
