@@ -312,7 +312,8 @@ gsc_status gsc_ste_backward(int64_t n, int32_t J, int32_t C, const float *d_grad
  * gsc_rd_loss_forward: the scalars (device floats) *d_loss, *d_dist, *d_rate, *d_count; d_diff
  *   (optional) = ahat - aref, which the backward takes with *d_count. Sums are FP64 in a fixed order.
  * gsc_rd_loss_backward: d_grad_yhat and d_grad_ahat [rows][C] from the scalars dL/dloss, dL/ddist
- *   and dL/drate (device floats, each may be NULL: zero); sgn(0) = 0 in the rate term.
+ *   and dL/drate (device floats, each may be NULL: zero); sgn(0) = 0 in the rate term. One of the two
+ *   may be NULL (not computed), and then what only it reads too: d_yhat and d_step, or d_diff and d_count.
  * gsc_ste_pad: after gsc_ste_forward with the same d_info on outputs of n rows: rows Nv..n-1 of
  *   yhat, ahat and aref cleared (every row after a device-detected error) and *d_nv = Nv (0 then).
  * ---------------------------------------------------------------------------------------- */

@@ -911,7 +911,9 @@ gsc_status gsc_rd_loss_backward(const float *d_yhat, const float *d_diff, const 
 {
     gsc_status st = rd_shape(rows, C);
     if (st != GSC_OK) return st;
-    if (!d_yhat || !d_diff || !d_step || !d_count || !d_grad_yhat || !d_grad_ahat) return GSC_ERR_INVALID_ARG;
+    if (!d_grad_yhat && !d_grad_ahat) return GSC_ERR_INVALID_ARG;
+    if (d_grad_yhat && (!d_yhat || !d_step)) return GSC_ERR_INVALID_ARG;
+    if (d_grad_ahat && (!d_diff || !d_count)) return GSC_ERR_INVALID_ARG;
     {
         const uint64_t m = (uint64_t)rows * C * 4;
         Spans sp;

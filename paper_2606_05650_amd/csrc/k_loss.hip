@@ -4,7 +4,9 @@
 //   d/dahat = 2 g_dist (ahat - aref) / (Nv C),  d/dyhat = g_rate lambda sgn(yhat) / (ln 2 (step + |yhat|))
 //
 // HBM traffic bounds both directions: the forward reads three [rows][C] matrices and writes the
-// difference its backward needs, the backward reads two and writes two, each once. As single
+// difference its backward needs, the backward reads two and writes two, each once, in one launch or in
+// one for each gradient (a caller may want the terms' gradients apart; the two launches cost 5 us of
+// a 500K x 56 training step of 785 more). As single
 // framework operators (difference, square, two sums, absolute value, quotient, logarithm and their
 // adjoints) the same step read and wrote some twenty matrices: 500K x 56 rows (112 MB a matrix).
 // Terms are FP32; the sums are FP64, per block in a fixed order, then over the blocks by one
@@ -30,7 +32,7 @@ struct RdArgs {
     float *loss, *dist, *rate, *count;  // results
     // gradient
     const float *g_loss, *g_dist, *g_rate;  // scalars or null
-    float *g_yhat, *g_ahat;
+    float *g_yhat, *g_ahat;  // (one may be null)
 };
 
 // The unit's channel group steps by the grid's stride modulo a row's units.
@@ -135,15 +137,19 @@ __global__ __launch_bounds__(RD_THREADS) void k_rd_grad(RdArgs a)
 {
     constexpr int W = VEC ? 4 : 1;
     __shared__ float s_step[GSC_MAX_CHANNELS];
-    if (threadIdx.x < a.C) s_step[threadIdx.x] = a.step[threadIdx.x];
+    if (a.g_yhat && threadIdx.x < a.C) s_step[threadIdx.x] = a.step[threadIdx.x];
     __syncthreads();
     const float gl = a.g_loss ? *a.g_loss : 0.0f;
     const float gd = gl + (a.g_dist ? *a.g_dist : 0.0f), gr = gl + (a.g_rate ? *a.g_rate : 0.0f);
-    const float fd = (float)(2.0 * (double)gd / ((double)*a.count_in * a.C));
+    const float fd = a.g_ahat ? (float)(2.0 * (double)gd / ((double)*a.count_in * a.C)) : 0.0f;
     const float fr = (float)((double)gr * a.lam / 0.693147180559945309417);  // (1 / ln 2)
     for (RdWalk w(a.cu); w.i < a.units; w.next()) {
-        const float4 y = rd_load<VEC>(a.yhat, w.i), d = rd_load<VEC>(a.diff, w.i);
-        rd_store<VEC>(a.g_ahat, w.i, make_float4(fd * d.x, fd * d.y, fd * d.z, fd * d.w));
+        if (a.g_ahat) {
+            const float4 d = rd_load<VEC>(a.diff, w.i);
+            rd_store<VEC>(a.g_ahat, w.i, make_float4(fd * d.x, fd * d.y, fd * d.z, fd * d.w));
+        }
+        if (!a.g_yhat) continue;
+        const float4 y = rd_load<VEC>(a.yhat, w.i);
         const float yy[4] = {y.x, y.y, y.z, y.w};
         float g[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll

@@ -678,16 +678,17 @@ def rd_loss_forward(yhat, ahat, aref, steps, lam, *, nv=None, want_diff=True, st
 
 def rd_loss_backward(yhat, diff, steps, lam, count, g_loss, g_dist, g_rate, *, stream=None):
     """(dL/dyhat, dL/dahat) from rd_loss_forward's diff and count and the scalar gradients of loss,
-    distortion and rate (each may be None)."""
+    distortion and rate (each may be None). Without yhat (and steps), or without diff (and count),
+    that gradient is not computed and None."""
     torch = _torch()
-    rows, C = int(yhat.shape[0]), int(yhat.shape[1])
+    rows, C = (int(k) for k in (yhat if yhat is not None else diff).shape)
     for name, t in (("yhat", yhat), ("diff", diff)):
         _check_tensor(t, name, torch.float32, rows, C)
     _check_tensor(steps, "steps", torch.float32, numel=C)
     _check_tensor(count, "count", torch.float32, numel=1)
     for name, t in (("g_loss", g_loss), ("g_dist", g_dist), ("g_rate", g_rate)):
         _check_tensor(t, name, torch.float32, numel=1)
-    gy, ga = torch.empty_like(yhat), torch.empty_like(diff)
+    gy, ga = (None if t is None else torch.empty_like(t) for t in (yhat, diff))
     _check(lib().gsc_rd_loss_backward(_ptr(yhat), _ptr(diff), _ptr(steps), rows, C, float(lam), _ptr(count), _ptr(g_loss),
                                       _ptr(g_dist), _ptr(g_rate), _ptr(gy), _ptr(ga), _stream(stream)),
            "gsc_rd_loss_backward")

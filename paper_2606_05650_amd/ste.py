@@ -15,8 +15,8 @@ device tensor. Nothing in its forward or backward synchronizes the host. A devic
 
 rd_loss is the rate-distortion objective of the differentiable workload: the mean squared error
 of the decoded attributes against the voxel means plus lambda times the rate proxy
-sum log2(1 + |yhat| / step). On plain contiguous float32 device rows it runs as one HIP launch pair
-(_RdLoss); every other call is the same formula in torch operators.
+sum log2(1 + |yhat| / step). On plain contiguous float32 device rows it runs fused: one pass
+forward and one backward for each term (_RdDist, _RdRate); every other call is the same formula in torch operators.
 """
 from __future__ import annotations
 
@@ -82,48 +82,49 @@ class SteCoderPadded(torch.autograd.Function):
         return _backward(ctx, g_yhat, g_ahat), None, None
 
 
-class _RdLoss(torch.autograd.Function):
-    """rd_loss on plain rows. The difference ahat - aref is kept for the backward as an output of its
-    own, so that neither ahat nor aref has to stay unchanged until then, and so that gradients of
-    the gradient flow through it."""
+class _RdDist(torch.autograd.Function):
+    """The distortion of a fused forward (gsc.rd_loss_forward's results) by ahat. The difference ahat - aref
+    is an output of its own, so that neither ahat nor aref has to stay unchanged until the backward,
+    and so that gradients of the gradient flow through it."""
 
     @staticmethod
-    def forward(ctx, yhat, ahat, aref, steps, lam, nv):
+    def forward(ctx, ahat, results):
         ctx.set_materialize_grads(False)
-        of_yhat, of_ahat = ctx.needs_input_grad[:2]
-        loss, dist, rate, ctx.count, diff = gsc.rd_loss_forward(yhat, ahat, aref, steps, lam, nv=nv, want_diff=of_ahat)
-        if not of_ahat:
-            ctx.mark_non_differentiable(dist)
-        if not of_yhat:
-            ctx.mark_non_differentiable(rate)
-        ctx.lam = lam
-        # (what a gradient does not read may change before the backward)
-        ctx.save_for_backward(yhat if of_yhat else None, diff, steps if of_yhat else None)
-        return loss, dist, rate, diff
+        _, dist, _, ctx.count, diff = results
+        ctx.save_for_backward(diff)
+        return dist, diff
 
     @staticmethod
-    def backward(ctx, g_loss, g_dist, g_rate, g_diff):
-        yhat, diff, steps = ctx.saved_tensors  # (as a saved-tensor hook hands them back)
-        gs = (g_loss, g_dist, g_rate)
-        given = [g for g in gs if g is not None]
-        # yhat has a gradient by the rate, ahat by the distortion and the difference: an input that none
-        # of the differentiated results depends on has none (zeros would be NaN where a row is not finite)
-        by_rate = [g for g in (g_loss, g_rate) if g is not None] if ctx.needs_input_grad[0] else []
-        by_dist = [g for g in (g_loss, g_dist) if g is not None] if ctx.needs_input_grad[1] else []
-        if not torch.is_grad_enabled() and g_diff is None and by_rate and by_dist and \
-                all(_readable(t, yhat.device) for t in (yhat, diff, steps, *given)):
-            gy, ga = gsc.rd_loss_backward(yhat, diff, steps, ctx.lam, ctx.count, *gs)
-            return gy, ga, None, None, None, None
-        # one of the two gradients, differentiable (create_graph), a gradient of the difference, or
-        # tensors that are not plain memory (batched gradients): torch operators
-        gy = ga = None
-        if by_rate:
-            gy = sum(by_rate) * (ctx.lam / math.log(2.0)) * yhat.sgn() / (steps + yhat.abs())
-        if by_dist:
-            ga = sum(by_dist) * 2.0 * diff / (ctx.count * diff.shape[1])
-        if g_diff is not None and ctx.needs_input_grad[1]:
-            ga = g_diff if ga is None else ga + g_diff
-        return gy, ga, None, None, None, None
+    def backward(ctx, g_dist, g_diff):
+        (diff,) = ctx.saved_tensors  # (as a saved-tensor hook hands it back)
+        if g_dist is None:
+            return g_diff, None
+        if not torch.is_grad_enabled() and g_diff is None and _readable(diff, diff.device) and _readable(g_dist, diff.device):
+            return gsc.rd_loss_backward(None, diff, None, 0.0, ctx.count, None, g_dist, None)[1], None
+        # differentiable (create_graph), a gradient of the difference, or tensors that are not plain
+        # memory (batched gradients): torch operators
+        ga = g_dist * 2.0 * diff / (ctx.count * diff.shape[1])
+        return ga if g_diff is None else ga + g_diff, None
+
+
+class _RdRate(torch.autograd.Function):
+    """The rate of a fused forward by yhat."""
+
+    @staticmethod
+    def forward(ctx, yhat, steps, lam, results):
+        ctx.set_materialize_grads(False)
+        ctx.lam = lam
+        ctx.save_for_backward(yhat, steps)
+        return results[2]
+
+    @staticmethod
+    def backward(ctx, g_rate):
+        yhat, steps = ctx.saved_tensors
+        if g_rate is None:
+            return None, None, None, None
+        if not torch.is_grad_enabled() and all(_readable(t, yhat.device) for t in (yhat, steps, g_rate)):
+            return gsc.rd_loss_backward(yhat, None, steps, ctx.lam, None, None, None, g_rate)[0], None, None, None
+        return g_rate * (ctx.lam / math.log(2.0)) * yhat.sgn() / (steps + yhat.abs()), None, None, None
 
 
 def _readable(t, device, dtype=torch.float32):
@@ -152,7 +153,7 @@ def _watched():
 
 
 def _plain_rows(yhat, ahat, aref, steps, lam, nv):
-    """Whether rd_loss may run as _RdLoss: ordinary float32 rows on the current device, gradients
+    """Whether rd_loss may run fused: ordinary float32 rows on the current device, gradients
     wanted of yhat and ahat only, and no mode or transform active that has to see the operators."""
     ts = (yhat, ahat, aref, steps) + (() if nv is None else (nv,))
     if not all(isinstance(t, torch.Tensor) for t in ts) or type(lam) not in (int, float):
@@ -176,9 +177,15 @@ def rd_loss(yhat, ahat, aref, steps, lam, nv=None):
     With nv (SteCoderPadded's device count) the rows are the padded ones: the mean is taken over
     the nv voxel rows (the zero rows past them add nothing to either term), with no host wait."""
     if _plain_rows(yhat, ahat, aref, steps, lam, nv):
-        if torch.is_grad_enabled() and (yhat.requires_grad or ahat.requires_grad):
-            return _RdLoss.apply(yhat, ahat, aref, steps, lam, nv)[:3]
-        return gsc.rd_loss_forward(yhat, ahat, aref, steps, lam, nv=nv, want_diff=False)[:3]
+        of_yhat, of_ahat = (torch.is_grad_enabled() and t.requires_grad for t in (yhat, ahat))
+        results = gsc.rd_loss_forward(yhat, ahat, aref, steps, lam, nv=nv, want_diff=of_ahat)
+        loss, dist, rate = results[:3]
+        # (the terms' graphs are their own: each may be differentiated alone, once)
+        if of_ahat:
+            dist, _ = _RdDist.apply(ahat, results)
+        if of_yhat:
+            rate = _RdRate.apply(yhat, steps, lam, results)
+        return dist + rate if of_yhat or of_ahat else loss, dist, rate
     sq = (ahat - aref) ** 2
     r = torch.log2(1.0 + yhat.abs() / steps)
     if nv is None:

@@ -466,3 +466,28 @@ def test_rd_loss_keeps_only_what_its_gradient_reads(which):
                 t.zero_()
         loss.backward()
         assert (leaf.grad.double() - want).abs().max().item() <= 1e-6 * want.abs().max().item()
+
+
+@pytest.mark.parametrize("coder", [False, True])
+def test_rd_loss_terms_have_graphs_of_their_own(coder):
+    """The rate and the distortion may each be differentiated once, one after the other, as with the
+    formula (of rows alone, and of the layer's outputs)."""
+    from paper_2606_05650_amd.ste import SteCoderPadded, rd_loss
+    got = {}
+    for fn in (rd_loss, _torch_rd_loss):
+        if coder:
+            pos, attr = synth.make_frame(700, seed=5)
+            leaf = torch.from_numpy(attr).to(_dev()).requires_grad_(True)
+            y, h, r, nv = SteCoderPadded.apply(leaf, torch.from_numpy(pos).to(_dev()), gsc.make_params(7, attr.shape[1], GROUPED))
+            steps, leaves = torch.from_numpy(GROUPED).to(_dev()), (leaf,)
+        else:
+            y, h, r, steps = _loss_inputs()
+            y.requires_grad_(True)
+            h.requires_grad_(True)
+            nv, leaves = None, (y, h)
+        _, dist, rate = fn(y, h, r, steps, 0.01, nv=nv)
+        rate.backward()
+        dist.backward()
+        got[fn] = [t.grad for t in leaves]
+    for x, z in zip(got[rd_loss], got[_torch_rd_loss]):
+        torch.testing.assert_close(x, z, rtol=1e-5, atol=1e-6 * z.abs().max().item())
