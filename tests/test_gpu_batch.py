@@ -57,6 +57,13 @@ def test_small_sequence_batch():
     _check_batch(_to_dev(frames), _params())
 
 
+@pytest.mark.parametrize("F", [1, 2, 16, 17, 33])
+def test_batches_around_the_setup_launches(F):
+    """A setup launch takes up to 16 frames; one frame, also one left over, takes the host's layout."""
+    frames = list(synth.make_sequence(F, 300, 3_000, seed=F))
+    _check_batch(_to_dev(frames), _params())
+
+
 @pytest.mark.slow
 def test_sequence_30_frames():
     """The 30-frame sequence (counts U[200K, 1.5M]) as one batch."""
